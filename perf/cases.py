@@ -1,6 +1,6 @@
 """The work a program has this library do, as cases that can be timed and compared.
 
-Five kinds of case, each a pass through the public entry points (binding.py, session.py, decoder.py):
+Four kinds of case, each a pass through the public entry points (binding.py, session.py, decoder.py):
 
   attention  every layer's Predict+Verify attention of one step over the paged cache: the decode
              step (a few queries), a prompt chunk or memory-token pass (up to 64 queries), and the
