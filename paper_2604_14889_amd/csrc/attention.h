@@ -8,7 +8,7 @@
 
 namespace ms {
 
-constexpr int kMaxRowwaveSplits = 16;
+constexpr int kMaxRowSplits = 16;   // shares of a (sequence, KV head) in the general kernel
 
 // Per-call sequence ids and the cache lengths the host knows (lower bounds while device-side commits
 // are outstanding), passed by value in the kernel argument block.
@@ -31,7 +31,7 @@ struct AttnArgs {
     float* ws;
     int n_q, n_verify, n_q_heads, n_kv_heads, group, max_pages;
     long page_elems;
-    int n_splits, chunk;
+    int n_splits, n_chunks;   // general kernel: shares of the tokens, chunks of the query rows
     float scale;
 };
 

@@ -1,5 +1,5 @@
-// Fused Predict+Verify attention: host entry point, the general one-wave-per-row kernel (any
-// supported dtype / head_dim / head grouping) and the split-KV combine.
+// Fused Predict+Verify attention: host entry point, the general kernel (any supported dtype /
+// head_dim / head grouping, fp32 arithmetic) and its split-KV combine.
 //
 // What is computed (MemoSight paper, Section 2.1.1 Predict and Verify; Section 2.3 "Compression
 // Attention" and "MTP Attention"): every query of the step -- the verify block followed by the
@@ -16,212 +16,436 @@
 
 namespace ms {
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// sin and cos of an fp32 angle of any size (RoPE angles reach 1e5 rad), correct to an fp32 ulp: the
+// reduction by pi/2 (two-term constant) and the Taylor series on [-pi/4, pi/4] (next terms below
+// 1e-11) are evaluated in fp64.
+__device__ __forceinline__ void sincos_f64(float x, float* sn, float* cs) {
+    const double xd = (double)x;
+    const double n = rint(xd * 0.63661977236758134308);
+    double r = fma(n, -1.57079632679489655800e+00, xd);
+    r = fma(n, -6.12323399573676603587e-17, r);
+    const double r2 = r * r;
+    double sp = fma(r2, -1.0 / 39916800.0, 1.0 / 362880.0);
+    sp = fma(r2, sp, -1.0 / 5040.0);
+    sp = fma(r2, sp, 1.0 / 120.0);
+    sp = fma(r2, sp, -1.0 / 6.0);
+    sp = fma(r * r2, sp, r);
+    double cp = fma(r2, 1.0 / 479001600.0, -1.0 / 3628800.0);
+    cp = fma(r2, cp, 1.0 / 40320.0);
+    cp = fma(r2, cp, -1.0 / 720.0);
+    cp = fma(r2, cp, 1.0 / 24.0);
+    cp = fma(r2, cp, -0.5);
+    cp = fma(r2, cp, 1.0);
+    const int q = (int)n & 3;
+    const double s1 = (q & 1) ? cp : sp, c1 = (q & 1) ? sp : cp;
+    *sn = (float)((q & 2) ? -s1 : s1);
+    *cs = (float)(((q + 1) & 2) ? -c1 : c1);
 }
 
-template <int D>
-__device__ __forceinline__ float dot_row(const float* __restrict__ k, const float* q_s) {
-    float acc = 0.f;
-#pragma unroll 4
-    for (int d = 0; d < D; d += 4) {
-        const float4 kv = *reinterpret_cast<const float4*>(k + d);
-        acc += kv.x * q_s[d] + kv.y * q_s[d + 1] + kv.z * q_s[d + 2] + kv.w * q_s[d + 3];
-    }
-    return acc;
-}
-template <int D>
-__device__ __forceinline__ float dot_row(const bf16_t* __restrict__ k, const float* q_s) {
-    float acc = 0.f;
-#pragma unroll 4
-    for (int d = 0; d < D; d += 8) {
-        const uint4 kv = *reinterpret_cast<const uint4*>(k + d);
-        const uint32_t w[4] = {kv.x, kv.y, kv.z, kv.w};
+// kN consecutive elements, a multiple of 8 bytes, as loaded.
+template <typename T, int kN>
+struct Raw {
+    static constexpr int kWords = kN * (int)sizeof(T) / 4;
+    uint32_t w[kWords];
+    __device__ __forceinline__ void load(const T* p) {
+        if constexpr (kWords % 4 == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc += __uint_as_float(w[e] << 16) * q_s[d + 2 * e];
-            acc += __uint_as_float(w[e] & 0xffff0000u) * q_s[d + 2 * e + 1];
+            for (int i = 0; i < kWords / 4; ++i) {
+                const uint4 v = reinterpret_cast<const uint4*>(p)[i];
+                w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
+            }
+        } else {
+            const uint2 v = *reinterpret_cast<const uint2*>(p);
+            w[0] = v.x; w[1] = v.y;
         }
     }
-    return acc;
+    __device__ __forceinline__ void clear_unless(bool keep) {
+#pragma unroll
+        for (int i = 0; i < kWords; ++i) w[i] = keep ? w[i] : 0u;
+    }
+    __device__ __forceinline__ float get(int e) const {   // e: a constant after unrolling
+        if constexpr (sizeof(T) == 4) return __uint_as_float(w[e]);
+        return (e & 1) ? __uint_as_float(w[e / 2] & 0xffff0000u) : __uint_as_float(w[e / 2] << 16);
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ void store4(T* p, float4 v);
+template <>
+__device__ __forceinline__ void store4<float>(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
+template <>
+__device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float4 v) {
+    uint2 u;
+    u.x = (uint32_t)float_to_bf16_bits(v.x) | ((uint32_t)float_to_bf16_bits(v.y) << 16);
+    u.y = (uint32_t)float_to_bf16_bits(v.z) | ((uint32_t)float_to_bf16_bits(v.w) << 16);
+    *reinterpret_cast<uint2*>(p) = u;
 }
 
-// One wave per (kv split, query row (i, h), sequence).  Lanes run over tokens for the scores and
-// over head_dim for the value accumulation.
-template <typename T, int D>
-__global__ __launch_bounds__(64) void pv_attn_rowwave(AttnArgs a, BatchMeta bm) {
-    const int sp = blockIdx.x, row = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-    const int i = row / a.n_q_heads, h = row % a.n_q_heads, g = h / a.group;
+constexpr int kGenWaves = 4;
+constexpr int kGenThreads = 64 * kGenWaves;
+
+// The general kernel: fp32 arithmetic throughout (both contractions on the fp32 matrix cores), any
+// supported dtype, head_dim and head grouping.  A workgroup of 4 waves takes one share of one
+// (sequence, KV head)'s tokens and 16 kRB of its query rows (rows = queries x grouped heads); the
+// tokens are the cached ones in 16-token tiles (a tile is a page) followed by the in-flight ones,
+// and wave w takes tiles w, w + 4, ... of the share.
+//
+// v_mfma_f32_16x16x4_f32 twice: S^T = K . Q^T (A rows = tokens, B columns = query rows), then O^T =
+// V^T . P^T.  The contraction index of the first is the head dimension in any order, so a lane reads
+// 16 bytes of its token's K row and feeds them to consecutive multiplications; the score registers
+// are the second product's B operand as they stand (register r holds token 4 (lane / 16) + r), and V
+// is read in whole rows, a lane's elements going to accumulators of their own.  Nothing but the
+// rotation table and the final merge of the four waves goes through LDS, and every cached byte is
+// read once per 16 kRB query rows.
+//
+// The kernel it replaces ran one wave per query row, which read the cache once per row and
+// reduced every score tile through LDS.  Measured per call with the combine: 16 sequences x 4000 tokens,
+// 16 / 4 heads of 64, bf16, 9 queries 567 -> 43 us; 4 sequences x 320 .. 1500 tokens, 8 / 8 heads of 64,
+// fp32, 7 queries 60 -> 14 us.  What bounds it: the fp32 matrix rate (256 FLOP per cycle and compute
+// unit) from two row blocks on; with one, the two launches and a chain of four memory round trips.
+template <typename T, int D, int kRB>
+__global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, BatchMeta bm) {
+    constexpr int kE = 16 / (int)sizeof(T);   // elements of a 16-byte load of K (or Q)
+    constexpr int kNC = D / (4 * kE);         // such loads per lane and tile: element e of load c is d = 4 kE c + kE (lane / 16) + e
+    constexpr int kEV = D / 16;               // V elements per lane and token: d = kEV (lane % 16) .. + kEV
+    constexpr int H2 = D / 2;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float2* cs = reinterpret_cast<float2*>(smem);   // [n_q][H2] cos, sin; later the waves' merge buffer
+    const int split = blockIdx.x, g = blockIdx.y / a.n_chunks, chunk = blockIdx.y % a.n_chunks, b = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, j = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int seq = bm.seq[b], L = a.d_len[seq];
     const int* pt = a.d_pt + (size_t)seq * a.max_pages;
-    const T* pool = (const T*)a.pool_layer;
-    constexpr int H2 = D / 2;
-    constexpr int EPL = D / 64;  // accumulator elements per lane
-    __shared__ float q_s[D];
-    __shared__ float p_s[64];
+    const T* pool = (const T*)a.pool_layer + (size_t)g * 2 * MS_PAGE_SIZE * D;
+    const int n_cache = (L + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE, n_tiles = n_cache + (a.n_q + 15) / 16;
+    // (the lengths are the device's: shares stay level when rows were committed that the host has not heard of)
+    const int t_lo = (int)((long)n_tiles * split / a.n_splits), t_hi = (int)((long)n_tiles * (split + 1) / a.n_splits);
+    const int n_rows = a.n_q * a.group;
+    const int row0 = 16 * kRB * chunk;
 
-    // rotate the query by its own position id and fold the softmax scale in
-    if (lane < H2) {
-        const T* qp = (const T*)a.q + (((size_t)b * a.n_q + i) * a.n_q_heads + h) * D;
-        const float x0 = to_float(qp[lane]), x1 = to_float(qp[lane + H2]);
-        float sn, cs;
-        sincosf((float)a.pos[b * a.n_q + i] * a.inv_freq[lane], &sn, &cs);
-        q_s[lane] = (x0 * cs - x1 * sn) * a.scale;
-        q_s[lane + H2] = (x1 * cs + x0 * sn) * a.scale;
+    Raw<T, kE> kr[kNC];
+    Raw<T, kEV> vr[4];
+    // K: token l16 of the tile's page; V: tokens 4 j + r
+    auto load_k = [&](int page) {
+        const T* p = pool + (size_t)page * a.page_elems + l16 * D + kE * j;
+#pragma unroll
+        for (int c = 0; c < kNC; ++c) kr[c].load(p + 4 * kE * c);
+    };
+    auto load_v = [&](int page) {
+        const T* p = pool + (size_t)page * a.page_elems + (MS_PAGE_SIZE + 4 * j) * D + kEV * l16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vr[r].load(p + r * D);
+    };
+    int t = t_lo + w;
+    const int t_cache = t_hi < n_cache ? t_hi : n_cache;   // cached tiles of the share end here
+    // Loads are unconditional: past the share's last cached tile that one is read again and not used (with
+    // nothing cached at all, whatever page the table's first entry names).
+    auto page_of = [&](int tile) { return pt[max(min(tile, t_cache - 1), 0)]; };
+    int page_next = page_of(t + kGenWaves);
+    {
+        const int page = page_of(t);
+        load_k(page);
+        load_v(page);
+    }
+    // raw query rows, 16 bytes at a time like K
+    float q[kRB][kNC * kE];
+    int qi[kRB];
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb) {
+        const int row = row0 + 16 * rb + l16 < n_rows ? row0 + 16 * rb + l16 : n_rows - 1;   // (rows past the end: computed, not stored)
+        qi[rb] = row / a.group;
+        const T* qp = (const T*)a.q + (((size_t)b * a.n_q + qi[rb]) * a.n_q_heads + g * a.group + row % a.group) * D + kE * j;
+#pragma unroll
+        for (int c = 0; c < kNC; ++c) {
+            Raw<T, kE> x;
+            x.load(qp + 4 * kE * c);
+#pragma unroll
+            for (int e = 0; e < kE; ++e) q[rb][c * kE + e] = x.get(e);
+        }
+    }
+    for (int i = tid; i < a.n_q * H2; i += kGenThreads) {
+        float sn, c;
+        sincos_f64((float)a.pos[b * a.n_q + i / H2] * a.inv_freq[i % H2], &sn, &c);
+        cs[i] = make_float2(c, sn);
     }
     __syncthreads();
-
-    float m = -INFINITY, l = 0.f, acc[EPL];
+    // element (c, e) pairs with (c + kNC / 2, e): d and d + D / 2
+    const float scale_log2 = a.scale * 1.44269504088896340736f;   // scores in log2 units
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-
-    const int t_begin = sp * a.chunk;
-    // (the chunks were cut from the lengths the host knew; rows committed on the device since then
-    // fall to the last split)
-    const int t_end = sp == a.n_splits - 1 ? L : min(L, t_begin + a.chunk);
-    for (int t0 = t_begin; t0 < t_end; t0 += 64) {
-        const int t = t0 + lane;
-        const bool valid = t < t_end;
-        float s = -INFINITY;
-        if (valid) {
-            const int page = pt[t >> 4];
-            s = dot_row<D>(pool + (size_t)page * a.page_elems + ((size_t)g * 2) * MS_PAGE_SIZE * D + (t & 15) * D, q_s);
-        }
-        const float m_new = fmaxf(m, wave_max(s));
-        const float p = valid ? expf(s - m_new) : 0.f;
-        const float corr = expf(m - m_new);
-        l = l * corr + wave_sum(p);
+    for (int rb = 0; rb < kRB; ++rb)
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] *= corr;
-        m = m_new;
-        p_s[lane] = p;
-        __syncthreads();
-        const int cnt = min(64, t_end - t0);
-        for (int tt = 0; tt < cnt; ++tt) {
-            const int tok = t0 + tt;
-            const int page = pt[tok >> 4];
-            const T* vp = pool + (size_t)page * a.page_elems + ((size_t)g * 2 + 1) * MS_PAGE_SIZE * D + (tok & 15) * D;
-            const float pp = p_s[tt];
+        for (int c = 0; c < kNC / 2; ++c)
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] += pp * to_float(vp[lane + 64 * e]);
-        }
-        __syncthreads();
-    }
-
-    if (sp == 0) {
-        // in-flight block: lane j holds in-flight token j
-        const int ctx = a.ctx_new ? a.ctx_new[b * a.n_q + i] : (i < a.n_verify ? i : a.n_verify);
-        const bool valid = lane < a.n_q && (lane < ctx || lane == i);
-        float s = -INFINITY;
-        if (valid) {
-            const T* kp = (const T*)a.k_new + (((size_t)b * a.n_q + lane) * a.n_kv_heads + g) * D;
-            const float posf = (float)a.pos[b * a.n_q + lane];
-            float dot = 0.f;
-            for (int d = 0; d < H2; ++d) {
-                float sn, cs;
-                sincosf(posf * a.inv_freq[d], &sn, &cs);
-                const float x0 = to_float(kp[d]), x1 = to_float(kp[d + H2]);
-                dot += q_s[d] * (x0 * cs - x1 * sn) + q_s[d + H2] * (x1 * cs + x0 * sn);
+            for (int e = 0; e < kE; ++e) {
+                const float2 f = cs[qi[rb] * H2 + 4 * kE * c + kE * j + e];
+                const float x0 = q[rb][c * kE + e], x1 = q[rb][(c + kNC / 2) * kE + e];
+                q[rb][c * kE + e] = (x0 * f.x - x1 * f.y) * scale_log2;
+                q[rb][(c + kNC / 2) * kE + e] = (x1 * f.x + x0 * f.y) * scale_log2;
             }
-            s = dot;
-        }
-        const float m_new = fmaxf(m, wave_max(s));  // the query always sees itself: finite
-        const float p = valid ? expf(s - m_new) : 0.f;
-        const float corr = expf(m - m_new);
-        l = l * corr + wave_sum(p);
+
+    float m[kRB], l[kRB];        // row maximum in use; this lane's part of the row sum
+    f32x4_t o[kRB][kEV];         // register rr of o[rb][e]: d = kEV (4 j + rr) + e of row l16
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] *= corr;
-        m = m_new;
-        p_s[lane] = p;
+    for (int rb = 0; rb < kRB; ++rb) {
+        m[rb] = -INFINITY;
+        l[rb] = 0.f;
+#pragma unroll
+        for (int e = 0; e < kEV; ++e) o[rb][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    // softmax weights of one tile's scores (in place), and what they do to the state
+    auto softmax = [&](f32x4_t& s, int rb) {
+        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mn = fmaxf(m[rb], mx);
+        const float mu = mn == -INFINITY ? 0.f : mn;   // nothing visible to the row so far
+        if (__any(mn > m[rb])) {
+            const float f = __builtin_amdgcn_exp2f(m[rb] - mu);
+            m[rb] = mn;
+            l[rb] *= f;
+#pragma unroll
+            for (int e = 0; e < kEV; ++e) o[rb][e] *= f;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] - mu);
+        l[rb] += (s[0] + s[1]) + (s[2] + s[3]);
+    };
+    auto pv = [&](const f32x4_t& p, int rb) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < kEV; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r].get(e), p[r], o[rb][e], 0, 0, 0);
+    };
+
+    for (; t < t_cache; t += kGenWaves) {
+        const int page = page_next;
+        page_next = page_of(t + 2 * kGenWaves);
+        f32x4_t s[kRB][2];   // two chains per block: consecutive multiplications do not wait for each other
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) s[rb][0] = s[rb][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < kNC; ++c)
+#pragma unroll
+            for (int e = 0; e < kE; ++e)
+#pragma unroll
+                for (int rb = 0; rb < kRB; ++rb)
+                    s[rb][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c].get(e), q[rb][c * kE + e], s[rb][e & 1], 0, 0, 0);
+        load_k(page);
+        const int valid = L - t * MS_PAGE_SIZE;
+        if (valid < MS_PAGE_SIZE)   // the last page: what follows the sequence's end may be anything
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vr[r].clear_unless(4 * j + r < valid);
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) {
+            s[rb][0] += s[rb][1];
+            if (valid < MS_PAGE_SIZE)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (4 * j + r >= valid) s[rb][0][r] = -INFINITY;
+            softmax(s[rb][0], rb);
+        }
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) pv(s[rb][0], rb);
+        load_v(page);
+    }
+    // in-flight tiles: the step's own keys (rotated here) and values, under the visibility rule
+    for (; t < t_hi; t += kGenWaves) {
+        const int tok0 = 16 * (t - n_cache);
+        const int tk = tok0 + l16 < a.n_q ? tok0 + l16 : a.n_q - 1;
+        const T* kp = (const T*)a.k_new + (((size_t)b * a.n_q + tk) * a.n_kv_heads + g) * D + kE * j;
+#pragma unroll
+        for (int c = 0; c < kNC; ++c) kr[c].load(kp + 4 * kE * c);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int tv = tok0 + 4 * j + r;
+            vr[r].load((const T*)a.v_new + (((size_t)b * a.n_q + (tv < a.n_q ? tv : a.n_q - 1)) * a.n_kv_heads + g) * D + kEV * l16);
+            vr[r].clear_unless(tv < a.n_q);
+        }
+        float k[kNC * kE];
+#pragma unroll
+        for (int c = 0; c < kNC / 2; ++c)
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                const float2 f = cs[tk * H2 + 4 * kE * c + kE * j + e];
+                const float x0 = kr[c].get(e), x1 = kr[c + kNC / 2].get(e);
+                k[c * kE + e] = x0 * f.x - x1 * f.y;
+                k[(c + kNC / 2) * kE + e] = x1 * f.x + x0 * f.y;
+            }
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb) {
+            f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < kNC * kE; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q[rb][c], s, 0, 0, 0);
+            const int i = qi[rb];
+            const int ctx = a.ctx_new ? a.ctx_new[b * a.n_q + i] : (i < a.n_verify ? i : a.n_verify);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int tok = tok0 + 4 * j + r;
+                if (!(tok < a.n_q && (tok < ctx || tok == i))) s[r] = -INFINITY;
+            }
+            softmax(s, rb);
+            pv(s, rb);
+        }
+    }
+
+    // ---- the four waves' states: maxima and sums of every wave, then O two row blocks (one at D = 128) at
+    // a time; wave rr folds register rr, i.e. d = kEV (4 j + rr) .. + kEV of every row ----
+    float* ml = reinterpret_cast<float*>(smem);                 // [wave][kRB * 16][2]
+    float* ob = ml + kGenWaves * kRB * 16 * 2;                  // [wave][rr][lane][kEV]
+    float mw[kRB][kGenWaves], m_all[kRB], l_all[kRB];
+    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb) {
+        l[rb] += __shfl_xor(l[rb], 16, 64);
+        l[rb] += __shfl_xor(l[rb], 32, 64);
+        if (j == 0) {
+            ml[((w * kRB + rb) * 16 + l16) * 2] = m[rb];
+            ml[((w * kRB + rb) * 16 + l16) * 2 + 1] = l[rb];
+        }
+    }
+#pragma unroll
+    for (int rb = 0; rb < kRB; ++rb) {
+        if (rb > 0) __syncthreads();
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+            for (int e4 = 0; e4 < kEV; e4 += 4)
+                *reinterpret_cast<float4*>(ob + ((w * 4 + rr) * (kEV / 4) + e4 / 4) * 256 + lane * 4) =
+                    make_float4(o[rb][e4][rr], o[rb][e4 + 1][rr], o[rb][e4 + 2][rr], o[rb][e4 + 3][rr]);
         __syncthreads();
-        for (int j = 0; j < a.n_q; ++j) {
-            const float pp = p_s[j];
-            if (pp == 0.f) continue;
-            const T* vp = (const T*)a.v_new + (((size_t)b * a.n_q + j) * a.n_kv_heads + g) * D;
+        m_all[rb] = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] += pp * to_float(vp[lane + 64 * e]);
+        for (int x = 0; x < kGenWaves; ++x) {
+            mw[rb][x] = ml[((x * kRB + rb) * 16 + l16) * 2];
+            m_all[rb] = fmaxf(m_all[rb], mw[rb][x]);
         }
-    }
-
-    const size_t orow = ((size_t)b * a.n_q + i) * a.n_q_heads + h;
-    if (a.n_splits == 1) {
-        T* op = (T*)a.out + orow * D;
-        const float inv = 1.f / l;
+        const float mu = m_all[rb] == -INFINITY ? 0.f : m_all[rb];
+        l_all[rb] = 0.f;
+        float4 acc[kEV / 4];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) op[lane + 64 * e] = from_float<T>(acc[e] * inv);
-    } else {
-        float* wp = a.ws + (orow * a.n_splits + sp) * (D + 2);
-        if (lane == 0) {
-            wp[0] = m;
-            wp[1] = l;
+        for (int e4 = 0; e4 < kEV / 4; ++e4) acc[e4] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int x = 0; x < kGenWaves; ++x) {
+            const float f = __builtin_amdgcn_exp2f(mw[rb][x] - mu);   // a wave without tiles: 2^-inf = 0
+            l_all[rb] += f * ml[((x * kRB + rb) * 16 + l16) * 2 + 1];
+#pragma unroll
+            for (int e4 = 0; e4 < kEV / 4; ++e4) {
+                const float4 v = *reinterpret_cast<const float4*>(ob + ((x * 4 + w) * (kEV / 4) + e4) * 256 + lane * 4);
+                acc[e4].x += f * v.x;
+                acc[e4].y += f * v.y;
+                acc[e4].z += f * v.z;
+                acc[e4].w += f * v.w;
+            }
         }
+        const int row = row0 + 16 * rb + l16;
+        if (row < n_rows) {
+            const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
+            const int d = kEV * (4 * j + w);
+            if (a.n_splits == 1) {
+                const float inv = 1.f / l_all[rb];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) wp[2 + lane + 64 * e] = acc[e];
+                for (int e4 = 0; e4 < kEV / 4; ++e4)
+                    store4<T>((T*)a.out + orow * D + d + 4 * e4,
+                              make_float4(acc[e4].x * inv, acc[e4].y * inv, acc[e4].z * inv, acc[e4].w * inv));
+            } else {
+                float* wp = a.ws + (orow * a.n_splits + split) * D + d;
+#pragma unroll
+                for (int e4 = 0; e4 < kEV / 4; ++e4) *reinterpret_cast<float4*>(wp + 4 * e4) = acc[e4];
+                if (w == 0 && j == 0) {
+                    float* mlp = a.ws + (size_t)gridDim.z * a.n_q * a.n_q_heads * a.n_splits * D + (orow * a.n_splits + split) * 2;
+                    *reinterpret_cast<float2*>(mlp) = make_float2(m_all[rb], l_all[rb]);
+                }
+            }
+        }
     }
 }
 
-// out = sum_s e^{m_s - m} acc_s / sum_s e^{m_s - m} l_s ; one wave per output row.
-template <typename T, int D>
-__global__ __launch_bounds__(64) void pv_attn_combine(const float* __restrict__ ws, void* __restrict__ out, int n_splits) {
-    const size_t orow = blockIdx.x;
-    const int lane = threadIdx.x;
-    constexpr int EPL = D / 64;
-    const float* wp = ws + orow * n_splits * (D + 2);
+// out = sum_s 2^(m_s - m) acc_s / sum_s 2^(m_s - m) l_s: a thread per four elements of a row, every
+// partial requested before the first is used.
+template <typename T, int D, int kMaxSplits>
+__global__ __launch_bounds__(256) void pv_attn_combine(const float* __restrict__ ws, void* __restrict__ out, int n_rows, int n_splits) {
+    const int row = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4), d = threadIdx.x % (D / 4) * 4;
+    if (row >= n_rows) return;
+    const float* op = ws + (size_t)row * n_splits * D + d;
+    const float2* ml = reinterpret_cast<const float2*>(ws + (size_t)n_rows * n_splits * D) + (size_t)row * n_splits;
+    float2 e[kMaxSplits];
+    float4 x[kMaxSplits];
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+        const int at = s < n_splits ? s : n_splits - 1;
+        e[s] = ml[at];
+        x[s] = *reinterpret_cast<const float4*>(op + (size_t)at * D);
+    }
     float m = -INFINITY;
-    for (int s = 0; s < n_splits; ++s) m = fmaxf(m, wp[s * (D + 2)]);
-    float l = 0.f, acc[EPL];
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    for (int s = 0; s < n_splits; ++s) {
-        const float* p = wp + s * (D + 2);
-        const float w = expf(p[0] - m);  // empty splits carry m = -inf, l = 0
-        l += w * p[1];
+    for (int s = 0; s < kMaxSplits; ++s) m = fmaxf(m, e[s].x);   // finite: one share holds the row's own token
+    float l = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += w * p[2 + lane + 64 * e];
+    for (int s = 0; s < kMaxSplits; ++s) {
+        const float f = s < n_splits ? __builtin_amdgcn_exp2f(e[s].x - m) : 0.f;   // shares nothing of which is visible carry m = -inf, l = 0
+        if (s >= n_splits) continue;
+        l += f * e[s].y;
+        acc.x += f * x[s].x;
+        acc.y += f * x[s].y;
+        acc.z += f * x[s].z;
+        acc.w += f * x[s].w;
     }
-    T* op = (T*)out + orow * D;
     const float inv = 1.f / l;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) op[lane + 64 * e] = from_float<T>(acc[e] * inv);
+    store4<T>((T*)out + (size_t)row * D + d, make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
 }
 
-static int rowwave_splits(int rows, int max_len, int* chunk) {
-    int want = (4096 + rows - 1) / rows;           // aim for a few thousand waves in flight
-    int by_len = (max_len + 255) / 256;            // at least 256 tokens per split
-    int s = want < by_len ? want : by_len;
-    if (s < 1) s = 1;
-    if (s > kMaxRowwaveSplits) s = kMaxRowwaveSplits;
-    int c = (max_len + s - 1) / s;
-    c = ((c + 63) / 64) * 64;
-    if (c < 64) c = 64;
-    *chunk = c;
-    return s;
+// Row blocks of 16 a workgroup takes at most: what the registers hold beside a tile.
+template <int D>
+constexpr int rows_max_blocks() { return D == 64 ? 4 : 2; }
+
+// Shares per (sequence, KV head, chunk of rows): enough workgroups for two per compute unit, at least a
+// tile for every wave.
+static int rows_splits(int wgs, int max_len, int n_q) {
+    const int tiles = (max_len + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE + (n_q + 15) / 16;
+    int s = (512 + wgs - 1) / wgs;
+    const int by_len = (tiles + kGenWaves - 1) / kGenWaves;
+    if (s > by_len) s = by_len;
+    return s < 1 ? 1 : (s > kMaxRowSplits ? kMaxRowSplits : s);
 }
 
-template <typename T, int D>
-static int launch_rowwave(ms_cache* c, AttnArgs& a, const BatchMeta& bm, int B, int max_len, hipStream_t stream) {
-    const int rows = a.n_q * a.n_q_heads;
-    a.n_splits = rowwave_splits(B * rows, max_len, &a.chunk);
-    c->launches += a.n_splits > 1 ? 2 : 1;
-    hipLaunchKernelGGL((pv_attn_rowwave<T, D>), dim3(a.n_splits, rows, B), dim3(64), 0, stream, a, bm);
+template <typename T, int D, int kRB>
+static int launch_rows_built(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, hipStream_t stream) {
+    const int merge = (kGenWaves * kRB * 16 * 2 + kGenWaves * 4 * D / 16 * 64) * (int)sizeof(float), table = a.n_q * D / 2 * (int)sizeof(float2);
+    hipLaunchKernelGGL((pv_attn_rows<T, D, kRB>), dim3(a.n_splits, a.n_kv_heads * a.n_chunks, B), dim3(kGenThreads), merge > table ? merge : table,
+                       stream, a, bm);
+    c->launches++;
     MS_HIP_TRY(hipGetLastError());
-    if (a.n_splits > 1) {
-        hipLaunchKernelGGL((pv_attn_combine<T, D>), dim3((unsigned)((size_t)B * rows)), dim3(64), 0, stream, a.ws, a.out,
-                           a.n_splits);
-        MS_HIP_TRY(hipGetLastError());
-    }
     return MS_OK;
 }
 
-size_t rowwave_workspace_bytes(const ms_cache* c, int B, int n_q) {
-    return (size_t)B * n_q * c->d.n_q_heads * kMaxRowwaveSplits * (c->d.head_dim + 2) * sizeof(float);
+template <typename T, int D>
+static int launch_general(ms_cache* c, AttnArgs& a, const BatchMeta& bm, int B, int max_len, hipStream_t stream) {
+    const int blocks = (a.n_q * a.group + 15) / 16;
+    a.n_chunks = (blocks + rows_max_blocks<D>() - 1) / rows_max_blocks<D>();
+    const int per = (blocks + a.n_chunks - 1) / a.n_chunks;
+    a.n_splits = rows_splits(B * a.n_kv_heads * a.n_chunks, max_len, a.n_q);
+    int rc = MS_OK;
+    if (per == 1) rc = launch_rows_built<T, D, 1>(c, a, bm, B, stream);
+    else if (per == 2) rc = launch_rows_built<T, D, 2>(c, a, bm, B, stream);
+    else if constexpr (D == 64) {
+        if (per == 3) rc = launch_rows_built<T, D, 3>(c, a, bm, B, stream);
+        else rc = launch_rows_built<T, D, 4>(c, a, bm, B, stream);
+    }
+    if (rc != MS_OK || a.n_splits == 1) return rc;
+    const int rows = B * a.n_q * a.n_q_heads;
+    const dim3 grid((unsigned)((rows + 1024 / D - 1) / (1024 / D)));
+    c->launches++;
+    if (a.n_splits <= 8) hipLaunchKernelGGL((pv_attn_combine<T, D, 8>), grid, dim3(256), 0, stream, a.ws, a.out, rows, a.n_splits);
+    else hipLaunchKernelGGL((pv_attn_combine<T, D, kMaxRowSplits>), grid, dim3(256), 0, stream, a.ws, a.out, rows, a.n_splits);
+    MS_HIP_TRY(hipGetLastError());
+    return MS_OK;
+}
+
+static size_t general_workspace_bytes(const ms_cache* c, int B, int n_q) {
+    return (size_t)B * n_q * c->d.n_q_heads * kMaxRowSplits * (c->d.head_dim + 2) * sizeof(float);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -267,7 +491,7 @@ extern "C" int ms_attention_set_deterministic(ms_cache* c, int on) {
 
 extern "C" size_t ms_attention_workspace_bytes(ms_cache* c, int B, int n_q) {
     if (!c || B < 1 || B > MS_MAX_BATCH || n_q < 1 || n_q > MS_MAX_QUERIES) return 0;
-    size_t need = mfma_eligible(c, n_q) ? mfma_workspace_bytes(c, B, n_q) : rowwave_workspace_bytes(c, B, n_q);
+    size_t need = mfma_eligible(c, n_q) ? mfma_workspace_bytes(c, B, n_q) : general_workspace_bytes(c, B, n_q);
     return (need + 255) & ~(size_t)255;
 }
 
@@ -324,15 +548,15 @@ extern "C" int ms_predict_verify_attention(ms_cache* c, int layer, int B, const 
     a.max_pages = c->d.max_pages_per_seq;
     a.page_elems = (long)c->page_elems;
     a.n_splits = 1;
-    a.chunk = 0;
+    a.n_chunks = 1;
     a.scale = scale != 0.f ? scale : 1.0f / sqrtf((float)c->d.head_dim);
     if ((((uintptr_t)q | (uintptr_t)k_new | (uintptr_t)v_new | (uintptr_t)out) & 15) != 0)
         MS_FAIL(MS_ERR_INVALID, "ms_predict_verify_attention: q, k_new, v_new and out must be 16-byte aligned");
     if (mfma_eligible(c, n_q)) return launch_mfma(c, a, bm, B, stream);
     const int D = c->d.head_dim;
     if (c->d.dtype == MS_F32)
-        return D == 64 ? launch_rowwave<float, 64>(c, a, bm, B, max_len, stream) : launch_rowwave<float, 128>(c, a, bm, B, max_len, stream);
-    return D == 64 ? launch_rowwave<bf16_t, 64>(c, a, bm, B, max_len, stream) : launch_rowwave<bf16_t, 128>(c, a, bm, B, max_len, stream);
+        return D == 64 ? launch_general<float, 64>(c, a, bm, B, max_len, stream) : launch_general<float, 128>(c, a, bm, B, max_len, stream);
+    return D == 64 ? launch_general<bf16_t, 64>(c, a, bm, B, max_len, stream) : launch_general<bf16_t, 128>(c, a, bm, B, max_len, stream);
 }
 
 extern "C" int ms_predict_verify_attention_static(ms_cache* c, int layer, int B, const int* seq_ids, int n_verify,
