@@ -223,10 +223,10 @@ int ms_predict_verify_attention_static(ms_cache* cache, int layer, int B, const 
                                        const int* ctx_new, float scale, void* out, void* stream);
 
 /* By default attention results are reproducible to rounding only: the streaming kernel (bf16,
- * head_dim 128) lets the waves of a workgroup take KV tiles first come, first served, so the
+ * head_dim 128, decode steps of more than a few short sequences) lets the waves of a workgroup take KV tiles first come, first served, so the
  * order in which a row's partial sums are added varies from call to call.  on != 0 fixes the
  * assignment instead: calls with the same inputs, cache contents and page tables then return the
- * same bits, a few percent slower.  The general kernel is always reproducible. */
+ * same bits, a few percent slower.  The other kernels are always reproducible. */
 int ms_attention_set_deterministic(ms_cache* cache, int on);
 
 /* Test hook for the failure path of the streaming kernel's split-KV combine.  In one launch the
@@ -238,7 +238,8 @@ int ms_attention_set_deterministic(ms_cache* cache, int on);
  * puts the counters back to zero.  This call forces that condition from the host: poll_limit > 0
  * replaces the bound (0 restores the default, about a second), and every pair's "published"
  * counter is set to published_bias (0 = the healthy state) behind the work already queued on
- * `stream`. */
+ * `stream`.  Until a call with two zeros, calls that a kernel without such counters would take run
+ * the streaming kernel too. */
 int ms_attention_fault_injection(ms_cache* cache, int poll_limit, int published_bias, void* stream);
 
 /* ---- greedy longest-prefix acceptance (footnote of Section 2.1.1) -------------------------- */
@@ -352,8 +353,8 @@ int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int vocab, int K
 
 /* ---- profiling ------------------------------------------------------------------------------- */
 
-/* From now on, every stride-th ms_predict_verify_attention call on this cache that runs the
- * streaming kernel (the first such call included) opens a timed span: one pair of HIP events
+/* From now on, every stride-th ms_predict_verify_attention call on this cache that runs a bf16
+ * matrix-core kernel (head_dim 128; the first such call included) opens a timed span: one pair of HIP events
  * around the launches of that call and of the span - 1 eligible calls after it (1 <= span <=
  * stride), for up to `capacity` spans; capacity 0 switches profiling off.  An event pair costs the
  * stream a few microseconds, which a span of back-to-back calls shares out and a stride keeps rare;

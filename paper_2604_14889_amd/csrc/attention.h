@@ -44,6 +44,11 @@ namespace ms {
 // attention.hip
 int static_scratch(int device, void** ptr);
 
+// attention_split.hip
+int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, int* n_splits);
+int launch_split(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, int share_tiles, int n_splits, hipStream_t stream);
+int split_allow_lds();
+
 // attention_mfma.hip
 bool mfma_eligible(const ms_cache* c, int n_q);
 size_t mfma_workspace_bytes(const ms_cache* c, int B, int n_q);

@@ -31,28 +31,11 @@
 #include <vector>
 
 #include "attention.h"
+#include "attention_tile.h"
 #include "ms_device.h"
 #include "ms_internal.h"
 
 namespace ms {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(16))) float f32x16_t;
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-typedef __attribute__((ext_vector_type(8))) short s16x8_t;
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-
-constexpr int kD = 128;
-constexpr int kRows = 64;               // query rows per KV head (padded)
-constexpr int kVRowBytes = 320;         // LDS bytes per V row: 256 + 64.  The transposed 8-byte reads of the PV operand
-                                        // take 64 bytes of 4 consecutive rows per 32 lanes: with a stride of 16 banks
-                                        // (mod 64) those fall on disjoint banks (288 left 22 % of the LDS cycles as conflicts)
-constexpr int kQRowBytes = 272;         // LDS bytes per rotated-Q row
-constexpr int kVTileBytes = kTile * kVRowBytes;
-constexpr float kRescaleThreshold = 24.0f;  // log2 units: P stays below 2^24
-constexpr int kPartFloats = 2 * kRows + kRows * kD;  // m[64], l[64], O[128 regs][64 lanes]
 
 // LDS map.  Stream phase: [Q tile][cos/sin table][in-flight K tile][one V tile per wave].  Merge
 // phase (overlays it): per wave 64 accumulator registers (two d blocks of both row blocks) + 4
@@ -104,38 +87,6 @@ struct MfmaArgs {
     float scale_log2;       // softmax scale * log2(e)
 };
 
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    f32x2_t f = {a, b};
-    bf16x2_t h = __builtin_convertvector(f, bf16x2_t);
-    return __builtin_bit_cast(uint32_t, h);
-}
-
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
-
-// sin and cos of an fp32 angle of any size (RoPE angles reach 1e5 rad): the reduction by pi/2 is
-// done in fp64 (two-term constant), the kernels on [-pi/4, pi/4] are the classic single-precision
-// minimax polynomials.  About 1e-7 absolute error, far below the bf16 rounding of the rotated rows,
-// and much cheaper than the library routine's large-argument path.
-__device__ __forceinline__ void sincos_reduced(float x, float* sn, float* cs) {
-    const double xd = (double)x;
-    const double n = rint(xd * 0.63661977236758134308);
-    double r = fma(n, -1.57079632679489655800e+00, xd);
-    r = fma(n, -6.12323399573676603587e-17, r);
-    const float t = (float)r, t2 = t * t;
-    const float sp = t + t * t2 * (-1.6666654611e-1f + t2 * (8.3321608736e-3f + t2 * -1.9515295891e-4f));
-    const float cp = 1.0f - 0.5f * t2 + t2 * t2 * (4.166664568298827e-2f + t2 * (-1.388731625493765e-3f + t2 * 2.443315711809948e-5f));
-    const int q = (int)n & 3;
-    const float s1 = (q & 1) ? cp : sp, c1 = (q & 1) ? sp : cp;
-    *sn = (q & 2) ? -s1 : s1;
-    *cs = ((q + 1) & 2) ? -c1 : c1;
-}
-
-// 16-byte non-temporal global load.
-__device__ __forceinline__ uint4 load_stream(const char* p) {
-    const u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-    return make_uint4(t.x, t.y, t.z, t.w);
-}
-
 // Partials travel between workgroups on different XCDs, whose L2 caches are not coherent with each
 // other.  They are written and read with device-scope relaxed atomic accesses (write-through /
 // cache-bypassing), which needs no cache write-back or invalidation; ordering comes from waiting
@@ -163,79 +114,11 @@ __device__ __forceinline__ void store_coherent4(__amdgpu_buffer_rsrc_t rs, uint3
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)byte_off, 0, kCoherentPolicy);
 }
 
-// Read-only, wave-uniform control data (the work plan, position ids) is read through the constant
-// address space: scalar loads, which return out of order with respect to the vector loads and so do
-// not queue behind the tile loads in flight.
-template <typename T>
-__device__ __forceinline__ T uniform_load(const T* p) {
-    return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
-}
-
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding
-// global load, which would stall the set-up phases on the tile loads already in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Registers of one 32-token tile in flight.
 struct TileRegs {
     uint4 k[8];  // K operand: token = lane % 32, d = 16 kk + 8 (lane / 32) .. + 8
     uint4 v[8];  // V rows as loaded: token = 4 r + lane / 16, d = 8 (lane % 16) .. + 8
 };
-
-// Page ids of a tile's two pages.  `tile` may lie past the segment: it is clamped, so that loads
-// stay unconditional (a fixed number of loads in flight lets the waits stay partial).
-__device__ __forceinline__ void tile_pages(const int* __restrict__ pt, int tile, int n_tiles, int t0, int last_page,
-                                           int& pa, int& pb) {
-    const int tc = tile < n_tiles ? tile : n_tiles - 1;
-    const int pg0 = (t0 >> 4) + 2 * tc;
-    pa = __builtin_amdgcn_readfirstlane(pt[pg0 < last_page ? pg0 : last_page]);
-    pb = __builtin_amdgcn_readfirstlane(pt[pg0 + 1 < last_page ? pg0 + 1 : last_page]);
-}
-
-// K operand of a tile straight from the pool.  Addresses are a uniform base plus a 32-bit byte
-// offset per lane (page_bytes * page id + lane part), which keeps the per-lane address state to one
-// register; layer pools of 4 GiB and more take the kBigPool build below.
-template <bool kBigPool>
-__device__ __forceinline__ void load_k(uint4 (&k)[8], const char* __restrict__ pool, int pa, int pb,
-                                       uint32_t page_bytes, uint32_t lane_off_k, int lane) {
-    if (!kBigPool) {
-        const uint32_t off = (uint32_t)((lane & 16) ? pb : pa) * page_bytes + lane_off_k;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) k[kk] = *reinterpret_cast<const uint4*>(pool + off + 32 * kk);
-    } else {
-        // layer pools of 4 GiB and more: the page's base is a 64-bit (wave-uniform) address, the
-        // half-waves pick theirs, the lane part stays a 32-bit offset
-        const char* base_a = pool + (size_t)(uint32_t)pa * page_bytes;
-        const char* base_b = pool + (size_t)(uint32_t)pb * page_bytes;
-        const char* base = (lane & 16) ? base_b : base_a;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) k[kk] = *reinterpret_cast<const uint4*>(base + lane_off_k + 32 * kk);
-    }
-}
-
-// V rows of a tile: tokens 4 rr + lane / 16 of page a (rr < 4) and of page b.  V is read exactly once
-// per call: streaming (non-temporal) loads keep it out of the caches.
-template <bool kBigPool>
-__device__ __forceinline__ void load_v(uint4 (&v)[8], const char* __restrict__ pool, int pa, int pb,
-                                       uint32_t page_bytes, uint32_t lane_off_v) {
-    if (kBigPool) {
-        const char* base_a = pool + (size_t)(uint32_t)pa * page_bytes;
-        const char* base_b = pool + (size_t)(uint32_t)pb * page_bytes;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) v[rr] = load_stream(base_a + lane_off_v + 4 * rr * kD * 2);
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) v[4 + rr] = load_stream(base_b + lane_off_v + 4 * rr * kD * 2);
-        return;
-    }
-    const uint32_t oa = (uint32_t)pa * page_bytes + lane_off_v, ob = (uint32_t)pb * page_bytes + lane_off_v;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) v[rr] = load_stream(pool + oa + 4 * rr * kD * 2);
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) v[4 + rr] = load_stream(pool + ob + 4 * rr * kD * 2);
-}
 
 struct WaveState {
     f32x16_t o[2][4];   // O^T accumulators: [row block][d block]; lane column = query row
@@ -324,23 +207,6 @@ __device__ __forceinline__ void qk_block_lds(f32x16_t& s, const char* kbase, con
         const bf16x8_t qb =
             __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qbase + rb * 32 * kQRowBytes + 32 * kk));
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qb, s, 0, 0, 0);
-    }
-}
-
-// Accumulator i of a lane holds token 8 (i / 4) + 4 (lane / 32) + i % 4 of the tile.
-__device__ __forceinline__ void mask_tail(f32x16_t& s, int valid, int hf) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        if (8 * (i >> 2) + 4 * hf + (i & 3) >= valid) s[i] = -INFINITY;
-}
-
-// Visibility of the in-flight tile (token j = in-flight query/key j): a row sees tokens below `lim`
-// and token `self` (lim = min(ctx, n_q), self = its own query index; padding rows: lim 0, self 0).
-__device__ __forceinline__ void mask_inflight(f32x16_t& s, int lim, int self, int hf) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int tok = 8 * (i >> 2) + 4 * hf + (i & 3);
-        s[i] = (tok < lim || tok == self) ? s[i] : -INFINITY;
     }
 }
 
@@ -1243,6 +1109,20 @@ int reset_arrival_counters(ms_cache* c, int published, hipStream_t stream) {
     return MS_OK;
 }
 
+// every prof_stride-th call opens a timed span of prof_span consecutive calls
+static int profile_open(ms_cache* c, hipStream_t stream) {
+    if (c->prof_open == 0 && c->prof_count < (int)c->prof_start.size() && c->prof_seen % c->prof_stride == 0) {
+        MS_HIP_TRY(hipEventRecord(c->prof_start[c->prof_count], stream));
+        c->prof_open = c->prof_span;
+    }
+    c->prof_seen++;
+    return MS_OK;
+}
+static int profile_close(ms_cache* c, hipStream_t stream) {
+    if (c->prof_open > 0 && --c->prof_open == 0) MS_HIP_TRY(hipEventRecord(c->prof_stop[c->prof_count++], stream));
+    return MS_OK;
+}
+
 int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hipStream_t stream) {
     // the kernels' LDS size is a per-device attribute: set once for every device the library meets
     static std::once_flag attr_once[kMaxAttrDevices];
@@ -1255,6 +1135,7 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
         for (const void* f : decode_builds)
             if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, Lds::kBytes);
         if (e == hipSuccess) e = hipFuncSetAttribute((const void*)pv_attn_mfma_wide, hipFuncAttributeMaxDynamicSharedMemorySize, WideLds::kBytes);
+        if (e == hipSuccess && split_allow_lds() != MS_OK) e = hipErrorInvalidValue;
         attr_result[c->device] = e;
     });
     if (attr_result[c->device] != hipSuccess)
@@ -1268,6 +1149,14 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
         if (rc != MS_OK) return rc;
         MS_FAIL(MS_ERR_HIP, "an earlier attention launch on this cache timed out waiting for split-KV partial results and left "
                             "output rows unwritten; the arrival counters have been reset, repeat the step");
+    }
+    const size_t part_bytes = (size_t)c->d.n_kv_heads * kPartFloats * sizeof(float);
+    int n_splits = 0;
+    const int share_tiles = c->stream_only ? 0 : split_share_tiles(c, bm.len, B, ga.n_q, mfma_workspace_bytes(c, B, ga.n_q) / part_bytes, &n_splits);
+    if (share_tiles > 0) {
+        if (int rc = profile_open(c, stream)) return rc;
+        if (int rc = launch_split(c, ga, bm, B, share_tiles, n_splits, stream)) return rc;
+        return profile_close(c, stream);
     }
     // plan: rebuilt only when the batch (ids, lengths) changed since the last call on this cache
     std::vector<int> key;
@@ -1322,12 +1211,7 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
     a.page_elems = ga.page_elems;
     a.scale_log2 = ga.scale * 1.44269504088896340736f;
     {
-        // every prof_stride-th call opens a timed span of prof_span consecutive calls
-        if (c->prof_open == 0 && c->prof_count < (int)c->prof_start.size() && c->prof_seen % c->prof_stride == 0) {
-            MS_HIP_TRY(hipEventRecord(c->prof_start[c->prof_count], stream));
-            c->prof_open = c->prof_span;
-        }
-        c->prof_seen++;
+        if (int rc = profile_open(c, stream)) return rc;
         const dim3 grid(c->plan_items, a.n_kv_heads);
         if (!mfma_wide_step(c, a.n_q)) {
             a.q0 = 0;
@@ -1349,9 +1233,8 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
             }
         }
         MS_HIP_TRY(hipGetLastError());
-        if (c->prof_open > 0 && --c->prof_open == 0) MS_HIP_TRY(hipEventRecord(c->prof_stop[c->prof_count++], stream));
     }
-    return MS_OK;
+    return profile_close(c, stream);
 }
 
 }  // namespace ms
@@ -1394,5 +1277,6 @@ extern "C" int ms_profile_read(ms_cache* c, float* ms_out, int cap, int* n) {
 extern "C" int ms_attention_fault_injection(ms_cache* c, int poll_limit, int published_bias, void* stream) {
     if (!c || poll_limit < 0) MS_FAIL(MS_ERR_INVALID, "ms_attention_fault_injection: bad argument");
     c->poll_limit = poll_limit;
+    c->stream_only = poll_limit > 0 || published_bias != 0;
     return ms::reset_arrival_counters(c, published_bias, (hipStream_t)stream);
 }

@@ -63,3 +63,57 @@ def test_general_kernel_row_blocks_chunks_and_page_tails(dtype, hq, hkv, d, nv, 
     n_q = nv + nf
     ctx = np.asarray([[(i * 7 + b) % (n_q + 1) for i in range(n_q)] for b in range(len(lengths))], np.int32)
     compare(sh, hq * 100 + nv, ctx)
+
+
+SPLIT = [
+    # Hq, Hkv, n_verify, n_foresight, lengths: bf16, head_dim 128, calls of the share-per-workgroup kernel
+    (28, 4, 4, 3, [0]),                                    # in-flight tile only
+    (28, 4, 5, 4, [1, 31, 32, 33]),                        # a tile with one page, a full tile, one token in the second
+    (28, 4, 1, 0, [16, 17, 48]),                           # a tile whose second page does not exist
+    (32, 8, 5, 4, [4100]),
+    (28, 4, 4, 3, [9000, 40]),                             # many shares, most of them empty for the second sequence
+    (16, 2, 8, 0, [700]),                                  # 64 rows
+    (4, 4, 16, 0, [130]),                                  # one row block
+    (28, 4, 10, 0, [65, 0]),                               # two chunks, the second with one query
+    (28, 4, 33, 0, [100]),                                 # two in-flight tiles, the second with one token
+    (28, 4, 64, 0, [1000, 15]),
+    (64, 1, 3, 2, [100]),                                  # 64 heads per KV head: a chunk per query
+    (48, 1, 64, 0, [40]),                                  # 64 chunks, unfilled rows in every one
+]
+
+
+@pytest.mark.parametrize("hq,hkv,nv,nf,lengths", SPLIT)
+def test_share_per_workgroup_kernel_tiles_chunks_and_shares(hq, hkv, nv, nf, lengths):
+    sh = W.AttnShape("split", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
+    got, again = compare(sh, hq * 100 + nv)
+    assert (got == again).all()
+    n_q = nv + nf
+    ctx = np.asarray([[(i * 7 + b) % (n_q + 1) for i in range(n_q)] for b in range(len(lengths))], np.int32)
+    compare(sh, hq * 100 + nv, ctx)
+
+
+def test_share_per_workgroup_kernel_follows_the_device_length_and_agrees_with_the_streaming_kernel():
+    """Rows committed on the device after the host last looked belong to the last share; the same call
+    forced onto the streaming kernel (fault injection with a generous bound) gives the same rows."""
+    import torch
+    M, S = _mods()
+    sh = W.AttnShape("grow", "bf16", 2, 28, 4, 128, 5, 4, [60, 500], 0.5, 1000000.0, slack_pages=1.0)
+    inp = W.attention_inputs(sh, 901)
+    ses, ora, ids = setup_pair(inp)
+    with ses:
+        pos = pids_for(inp, M)
+        q, kn, vn = (S.to_device(x, M.MS_BF16) for x in (inp.q, inp.k_new, inp.v_new))
+        p = S.ints_dev(pos).view(sh.batch, sh.n_q)
+        first = ses.attention(0, ids, 5, 4, q, kn, vn, p)
+        acc = S.ints_dev([5, 3])
+        for _ in range(4):
+            M.ms_commit_accepted_device(ses.cache, ids, acc, sh.n_q, 5, kn, vn, p)
+        lagging = ses.attention(0, ids, 5, 4, q, kn, vn, p)
+        assert not torch.equal(first, lagging)
+        M.ms_cache_sync(ses.cache)
+        assert ses.lengths(ids) == [80, 512]
+        caught_up = ses.attention(0, ids, 5, 4, q, kn, vn, p)
+        M.ms_attention_fault_injection(ses.cache, 1 << 22, 0)
+        streamed = ses.attention(0, ids, 5, 4, q, kn, vn, p)
+        for other in (caught_up, streamed):
+            check_out(S.to_host_f32(lagging), S.to_host_f32(other).astype(np.float64), "bf16", "after device-side commits")
