@@ -301,7 +301,7 @@ int ms_argmax_rows(const void* logits, int n, int vocab, long ld, int* out, void
  * [M][out_col[i + 1] - out_col[i]] bf16 tensor (out_col[0] = 0, out_col[n_out] = N, boundaries
  * multiples of 128) -- one fused Q/K/V projection fills three tensors.  N % 128 == 0,
  * K % (32 * split_k) == 0; A and W 16-byte, bias and destinations 8-byte aligned.
- * split_k > 1 divides K over that many workgroups per output tile (for few output tiles and a deep
+ * split_k > 1 divides K over up to that many workgroups per output tile (for few output tiles and a deep
  * K, such as the MLP down projection); the partial sums are added in a fixed order and the call
  * fails with MS_ERR_WORKSPACE without ms_gemm_workspace_bytes(M, N, K, split_k) bytes of 16-byte
  * aligned workspace.  With split_k == 1 that function returns what the call can use to split the

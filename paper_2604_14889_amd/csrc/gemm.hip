@@ -194,6 +194,94 @@ __device__ __forceinline__ void gemm_k_loop(char* smem, const uint16_t* const (&
 #undef MS_GEMM_STASH
 }
 
+// What a wave does with its 32 kMI rows x 64 columns of fp32 sums.  Accumulator i of a lane: n = n_wave +
+// 32 ni + 8 (i / 4) + 4 hf + i % 4, m = m_lane + 32 mi (hf = lane / 32; m_lane includes lane % 32).
+template <int kMode, int kMI>
+__device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x16_t (&acc)[2][kMI], bool to_partial, int k_part, int m_lane,
+                                                int n_wave, int hf) {
+    if (to_partial) {
+        const int p_col0 = kMode == kGemmAllPartial ? 0 : g.tail_col0, p_ld = g.N - p_col0;
+#pragma unroll
+        for (int mi = 0; mi < kMI; ++mi) {
+            const int m = m_lane + 32 * mi;
+            if (m >= g.M) continue;
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n = n_wave + 32 * ni + 8 * q + 4 * hf;
+                    *reinterpret_cast<float4*>(g.partial + ((size_t)k_part * g.M + m) * p_ld + (n - p_col0)) =
+                        make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
+                }
+        }
+        return;
+    }
+    if (kMode == kGemmArgmax) {
+        // group = the wave's 64 columns; a lane first folds its 32 of them, then the
+        // two half-waves (same row m, the other 4-column pieces) are folded through a lane exchange
+#pragma unroll
+        for (int mi = 0; mi < kMI; ++mi) {
+            unsigned long long best = 0ull;
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    best = key_max(best, argmax_key(acc[ni][mi][i], n_wave + 32 * ni + 8 * (i >> 2) + 4 * hf + (i & 3)));
+            const uint32_t lo = __shfl_xor((int)(uint32_t)best, 32, 64), hi = __shfl_xor((int)(uint32_t)(best >> 32), 32, 64);
+            best = key_max(best, ((unsigned long long)hi << 32) | lo);
+            const int m = m_lane + 32 * mi;
+            if (m < g.M && hf == 0) g.keys[(size_t)(n_wave / kGemmColGroup) * g.M + m] = best;
+        }
+        return;
+    }
+    if (kMode == kGemmSwiglu) {
+        // weight rows n_wave .. + 32 are gate rows, the next 32 the matching up rows: accumulators [0][mi]
+        // and [1][mi] hold gate and up of output column n_wave / 2 + ...
+#pragma unroll
+        for (int mi = 0; mi < kMI; ++mi) {
+            const int m = m_lane + 32 * mi;
+            if (m >= g.M) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = swiglu_value(acc[0][mi][4 * q + i], acc[1][mi][4 * q + i]);
+                uint2 pk;
+                pk.x = g_pack_bf16x2(o[0], o[1]);
+                pk.y = g_pack_bf16x2(o[2], o[3]);
+                *reinterpret_cast<uint2*>(g.out[0] + (size_t)m * (g.N / 2) + n_wave / 2 + 8 * q + 4 * hf) = pk;
+            }
+        }
+        return;
+    }
+    uint16_t* dst = nullptr;   // a wave's columns go to one destination: boundaries are multiples of 64
+    int col0 = 0, ld = 0;
+    pick_destination(g, n_wave, dst, col0, ld);
+#pragma unroll
+    for (int mi = 0; mi < kMI; ++mi) {
+        const int m = m_lane + 32 * mi;
+        if (m >= g.M) continue;
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n_wave + 32 * ni + 8 * q + 4 * hf;
+                float4 v = make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
+                if (g.bias) {
+                    const uint2 b = *reinterpret_cast<const uint2*>(g.bias + n);
+                    v.x += bf16_bits_to_float(b.x & 0xffffu);
+                    v.y += bf16_bits_to_float(b.x >> 16);
+                    v.z += bf16_bits_to_float(b.y & 0xffffu);
+                    v.w += bf16_bits_to_float(b.y >> 16);
+                }
+                uint2 pk;
+                pk.x = g_pack_bf16x2(v.x, v.y);
+                pk.y = g_pack_bf16x2(v.z, v.w);
+                *reinterpret_cast<uint2*>(dst + (size_t)m * ld + (n - col0)) = pk;
+            }
+    }
+}
+
 template <int kMode>
 __global__ __launch_bounds__(kGemmThreads) void gemm_tn_bf16(GemmArgs g) {
     constexpr bool kSplit = kMode == kGemmAllPartial;
@@ -270,88 +358,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_tn_bf16(GemmArgs g) {
     }
     if (mi_n == 0) return;   // nothing of the product in this wave's tile (no barrier follows)
 
-    // accumulator i of a lane: n = 8 (i / 4) + 4 (lane / 32) + i % 4, m = lane % 32 (within the 32 x 32 tile)
-    if (to_partial) {
-        const int p_col0 = kSplit ? 0 : g.tail_col0, p_ld = g.N - p_col0;
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
-            const int m = m0 + 128 * wm + 32 * mi + l32;
-            if (m >= g.M) continue;
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = n0 + 64 * wn + 32 * ni + 8 * q + 4 * hf;
-                    *reinterpret_cast<float4*>(g.partial + ((size_t)k_part * g.M + m) * p_ld + (n - p_col0)) =
-                        make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
-                }
-        }
-        return;
-    }
-    if (kMode == kGemmArgmax) {
-        // group = (column tile, wave column): 64 columns; a lane first folds its 32 of them, then the
-        // two half-waves (same row m, the other 4-column pieces) are folded through a lane exchange
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
-            unsigned long long best = 0ull;
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    best = key_max(best, argmax_key(acc[ni][mi][i], n0 + 64 * wn + 32 * ni + 8 * (i >> 2) + 4 * hf + (i & 3)));
-            const uint32_t lo = __shfl_xor((int)(uint32_t)best, 32, 64), hi = __shfl_xor((int)(uint32_t)(best >> 32), 32, 64);
-            best = key_max(best, ((unsigned long long)hi << 32) | lo);
-            const int m = m0 + 128 * wm + 32 * mi + l32;
-            if (m < g.M && hf == 0) g.keys[(size_t)(n_tile * 4 + wn) * g.M + m] = best;
-        }
-        return;
-    }
-    if (kMode == kGemmSwiglu) {
-        // weight rows 64 wn .. + 32 of the tile are gate rows, the next 32 the matching up rows:
-        // accumulators [0][mi] and [1][mi] hold gate and up of output column n0 / 2 + 32 wn + ...
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi) {
-            const int m = m0 + 128 * wm + 32 * mi + l32;
-            if (m >= g.M) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float o[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = swiglu_value(acc[0][mi][4 * q + i], acc[1][mi][4 * q + i]);
-                uint2 pk;
-                pk.x = g_pack_bf16x2(o[0], o[1]);
-                pk.y = g_pack_bf16x2(o[2], o[3]);
-                *reinterpret_cast<uint2*>(g.out[0] + (size_t)m * (g.N / 2) + n0 / 2 + 32 * wn + 8 * q + 4 * hf) = pk;
-            }
-        }
-        return;
-    }
-    uint16_t* dst = nullptr;   // a wave's columns go to one destination: boundaries are multiples of 64
-    int col0 = 0, ld = 0;
-    pick_destination(g, n0 + kGemmColGroup * wn, dst, col0, ld);
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
-        const int m = m0 + 128 * wm + 32 * mi + l32;
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = n0 + 64 * wn + 32 * ni + 8 * q + 4 * hf;
-                float4 v = make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
-                if (g.bias) {
-                    const uint2 b = *reinterpret_cast<const uint2*>(g.bias + n);
-                    v.x += bf16_bits_to_float(b.x & 0xffffu);
-                    v.y += bf16_bits_to_float(b.x >> 16);
-                    v.z += bf16_bits_to_float(b.y & 0xffffu);
-                    v.w += bf16_bits_to_float(b.y >> 16);
-                }
-                uint2 pk;
-                pk.x = g_pack_bf16x2(v.x, v.y);
-                pk.y = g_pack_bf16x2(v.z, v.w);
-                *reinterpret_cast<uint2*>(dst + (size_t)m * ld + (n - col0)) = pk;
-            }
-    }
+    store_wave_tile<kMode, 4>(g, acc, to_partial, k_part, m0 + 128 * wm + l32, n0 + kGemmColGroup * wn, hf);
 }
 
 // Sums the K parts of columns col0 .. N (partials [parts][M][N - col0]), adds the bias, rounds to
@@ -689,6 +696,173 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// 17 to 256 rows (a few sequences up to a batch of 32): every row in one tile, so that W leaves HBM
+// once and no tile row is empty.  The 256 x 256 tiles of gemm_tn_bf16 leave compute units without work at
+// these sizes (37888 columns: 148 workgroups) and keep too few weights in flight.
+//   * Tile 32 kWM kMI (M) x 128 (N), K in steps of 64 through as many LDS stages as the compute unit
+//     holds.  Both tiles are loaded straight into LDS (global_load_lds_dwordx4: no registers, no LDS
+//     store instructions), up to five steps ahead; one barrier per step.  A workgroup of 2 kWM waves; a
+//     wave owns 32 kMI rows x 64 columns (v_mfma_f32_32x32x16_bf16, W as the A operand), so a gate/up
+//     pair of the interleaved weight meets in one lane.
+//   * One workgroup per compute unit walks its units of work (whole column tiles, then K parts of the
+//     tiles of the last round) without ever draining its loads: the next unit's steps are asked for
+//     while this one's are multiplied.
+//   * An LDS-direct load fills 1 KB in lane order: 8 rows of 128 bytes.  The lanes fetch the 16-byte
+//     chunks of row r in the order c ^ (r / 2 % 8), which puts the operand reads of 16 consecutive
+//     rows on 16 different groups of four banks.
+//   * The loads are inline assembly: the compiler would make every LDS read wait for all of them.
+//     Their completion is counted by hand (vmcnt: each wave issues kLoads per step), and an LDS stage is
+//     refilled one barrier after its last reader.
+// What bounds it: a compute unit takes in about 32 bytes per ns over both tiles whatever their shape
+// (activations come from L2 but return in order behind the weights), so the weights' share
+// 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
+// kernel, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
+// 91 -> 67, 224 rows 101 -> 94; LM head 216 -> 170 (6.4 TB/s), 238 -> 195, 285 -> 243, 332 -> 336; down 36 ->
+// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.  Starting the workgroups at
+// different K steps (L2 channels) changed nothing.
+// ---------------------------------------------------------------------------------------------
+constexpr int kMidMaxRows = 256;
+constexpr int kMidBN = 128, kMidBK = 64;
+constexpr int mid_stage_bytes(int bm) { return (bm + kMidBN) * kMidBK * 2; }
+constexpr int mid_stages(int bm) { return 160 * 1024 / mid_stage_bytes(bm) < 6 ? 160 * 1024 / mid_stage_bytes(bm) : 6; }   // the whole LDS; six cover the latency
+
+// 64 lanes x 16 bytes from base + voff into LDS at lds .. lds + 1024, lane order.
+template <bool kStream>
+__device__ __forceinline__ void load_lds_1k(uint32_t lds, uint32_t voff, const void* base) {
+    if (kStream) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+// An address that is the same in every lane, in scalar registers.
+__device__ __forceinline__ const char* wave_uniform(const char* p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const char*)(((uint64_t)hi << 32) | lo);
+}
+template <int kN>
+__device__ __forceinline__ void wait_loads() {   // at most kN of this wave's loads are still on their way; its LDS reads are done
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kN) : "memory");
+}
+
+// The work of a launch: units 0 .. main_tiles are whole column tiles, the rest K parts of the tiles behind
+// them (all tiles in parts: main_tiles = 0).  Workgroup i takes units i, i + grid, ...
+struct MidUnits {
+    int tiles, main_tiles, parts, units;
+};
+struct MidUnit {
+    int n0, part, s_lo, s_hi;
+    bool whole;
+};
+__device__ __forceinline__ MidUnit mid_unit(const MidUnits& t, int u, int steps) {
+    MidUnit r;
+    r.whole = u < t.main_tiles;
+    const int tail = t.tiles - t.main_tiles, v = u - t.main_tiles;
+    r.part = r.whole ? 0 : v / tail;
+    r.n0 = (r.whole ? u : t.main_tiles + v % tail) * kMidBN;
+    r.s_lo = r.whole ? 0 : (int)((uint32_t)steps * r.part / t.parts);   // parts <= 64, steps < 2^25
+    r.s_hi = r.whole ? steps : (int)((uint32_t)steps * (r.part + 1) / t.parts);
+    return r;
+}
+
+template <int kMode, int kWM, int kMI>
+__global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUnits t) {
+    constexpr int kBM = 32 * kWM * kMI, kWaves = 2 * kWM, kS = mid_stages(kBM), kStage = mid_stage_bytes(kBM);
+    constexpr int kChunks = (kBM + kMidBN) / 8, kLoads = (kChunks + kWaves - 1) / kWaves;
+    static_assert((kS - 2) * kLoads < 64, "the load counter has six bits");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
+    const int steps = g.K / kMidBK;
+    // this wave's 1 KB chunks of a stage: chunk c = rows 8 c .. + 8 of the stage (A's rows, then W's); the
+    // last one may be loaded by two waves (the same bytes to the same place)
+    uint32_t voff[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int c = min(w + i * kWaves, kChunks - 1), row = 8 * c + (lane >> 3);
+        const int src = row < kBM ? min(row, g.M - 1) : row - kBM;   // rows past M: the last one again, never stored to the product
+        voff[i] = (uint32_t)src * (uint32_t)g.K * 2u + 16u * ((lane & 7) ^ ((row >> 1) & 7));
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    // the next step to ask for; it runs ahead of the one being multiplied, into the next unit too
+    int iu = blockIdx.x, i_buf = 0, in_flight = 0;
+    MidUnit ahead = mid_unit(t, iu, steps);
+    int i_step = ahead.s_lo;
+    auto issue = [&]() {
+        if (iu >= t.units) return;
+        const size_t k_bytes = (size_t)i_step * (kMidBK * 2);
+        const char* wb = wave_uniform(reinterpret_cast<const char*>(g.w + (size_t)ahead.n0 * g.K) + k_bytes);
+        const char* ab = wave_uniform(reinterpret_cast<const char*>(g.a) + k_bytes);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int c = min(w + i * kWaves, kChunks - 1);
+            const uint32_t lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)i_buf * kStage + 1024u * c);
+            if (8 * c < kBM) load_lds_1k<false>(lds, voff[i], ab);
+            else load_lds_1k<true>(lds, voff[i], wb);   // W passes through once
+        }
+        ++in_flight;
+        i_buf = i_buf + 1 == kS ? 0 : i_buf + 1;
+        if (++i_step == ahead.s_hi) {
+            iu += gridDim.x;
+            if (iu < t.units) {
+                ahead = mid_unit(t, iu, steps);
+                i_step = ahead.s_lo;
+            }
+        }
+    };
+    // operand addresses: 16 bytes at k = 16 kk + 8 hf of a row; the chunk 2 kk + hf of row r lies at (2 kk + hf) ^ (r / 2 % 8)
+    const char* a_op = smem + (32 * kMI * wm + l32) * (kMidBK * 2);   // (rows a multiple of 16 apart within a wave: one swizzle)
+    const char* w_op = smem + (kBM + 64 * wn + l32) * (kMidBK * 2);
+    const int swz = (l32 >> 1) & 7;
+#pragma unroll
+    for (int s = 0; s < kS - 1; ++s) issue();
+    int buf = 0;
+    for (int u = blockIdx.x; u < t.units; u += gridDim.x) {
+        const MidUnit cur = mid_unit(t, u, steps);
+        g_f32x16_t acc[2][kMI];
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < kMI; ++mi)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[ni][mi][i] = 0.f;
+        for (int s = cur.s_lo; s < cur.s_hi; ++s) {
+            // the oldest of the steps in flight has to be here (stores of an earlier unit only make the wait longer)
+            if (in_flight >= kS - 1) wait_loads<(kS - 2) * kLoads>();
+            else if (kS > 5 && in_flight == 4) wait_loads<3 * kLoads>();
+            else if (kS > 4 && in_flight == 3) wait_loads<2 * kLoads>();
+            else if (kS > 3 && in_flight == 2) wait_loads<kLoads>();
+            else wait_loads<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            --in_flight;
+            issue();   // into the stage that was multiplied before the barrier
+            const char* ab = a_op + buf * kStage;
+            const char* wb = w_op + buf * kStage;
+            buf = buf + 1 == kS ? 0 : buf + 1;
+            g_bf16x8_t wf[2][2], af[2][kMI];
+            auto fetch = [&](int kk, int set) {
+                const int at = ((2 * kk + hf) ^ swz) * 16;
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) wf[set][ni] = *reinterpret_cast<const g_bf16x8_t*>(wb + ni * 32 * (kMidBK * 2) + at);
+#pragma unroll
+                for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at);
+            };
+            fetch(0, 0);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                if (kk < 3) fetch(kk + 1, (kk + 1) & 1);   // the next operands are on their way while these are multiplied
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int mi = 0; mi < kMI; ++mi)
+                        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1][ni], af[kk & 1][mi], acc[ni][mi], 0, 0, 0);
+            }
+        }
+        store_wave_tile<kMode, kMI>(g, acc, !cur.whole, cur.part, 32 * kMI * wm + l32, cur.n0 + 64 * wn, hf);
+    }
+}
+
 static bool g_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Twice the compute units of the current device (the few-row kernel's workgroups per round; the
@@ -790,6 +964,82 @@ static SkinnyPlan skinny_plan(int M, int N, int K, int min_parts = 1) {
     return p;
 }
 
+// 17 to 256 rows: the launch shape of gemm_rows_bf16 (bm 0: the shape runs on another kernel).
+struct MidPlan {
+    int bm;
+    MidUnits units;
+    size_t workspace_bytes;
+};
+static MidPlan mid_plan(int M, int N, int K, int split_k) {
+    MidPlan p = {0, {0, 0, 1, 0}, 0};
+    if (M < 1 || M > kMidMaxRows || K % kMidBK || N % kMidBN || K / kMidBK < split_k) return p;
+    const int blocks = (M + 31) / 32;
+    p.bm = blocks <= 4 ? 32 * blocks : blocks <= 6 ? 192 : 256;
+    const int tiles = N / kMidBN;
+    p.units = {tiles, tiles, 1, tiles};
+    const int slots = gemm_slots() / 2, steps = K / kMidBK;
+    if (split_k > 1) {
+        // at most split_k parts: the number that leaves the shortest chain of steps, the fewest of equals
+        int parts = 2;
+        for (int c = 3; c <= split_k; ++c)
+            if ((long)((tiles * c + slots - 1) / slots) * parts < (long)((tiles * parts + slots - 1) / slots) * c) parts = c;
+        p.units = {tiles, 0, parts, tiles * parts};
+        p.workspace_bytes = (size_t)split_k * M * N * sizeof(float);
+        return p;
+    }
+    // The tiles of the last round are divided over K: as many parts as fill the chip if it is at most 60 %
+    // full; otherwise the number that leaves the shortest round, ceil(rem * parts / slots) / parts of a
+    // whole one (steps * 0.6 us), with a second launch and the partials' way to memory and back counted in.
+    const int rem = tiles % slots;
+    if (tiles <= slots || rem == 0) return p;
+    const int most = steps / 4 < 8 ? steps / 4 : 8;
+    int best = 1;
+    if (10 * rem <= 6 * slots) {
+        best = slots / rem < most ? slots / rem : most;
+    } else {
+        double best_us = 0.6 * steps;
+        for (int parts = 2; parts <= most; ++parts) {
+            const double us = 0.6 * steps * ((rem * parts + slots - 1) / slots) / parts + 5.0 + 2.0 * parts * M * rem * kMidBN * 4 / 4.0e6;
+            if (us < best_us) {
+                best_us = us;
+                best = parts;
+            }
+        }
+    }
+    if (best <= 1) return p;
+    p.units = {tiles, tiles - rem, best, tiles - rem + rem * best};
+    p.workspace_bytes = (size_t)best * M * rem * kMidBN * sizeof(float);
+    return p;
+}
+
+template <int kMode, int kWM, int kMI>
+static int mid_launch_built(const GemmArgs& g, const MidUnits& units, hipStream_t stream) {
+    constexpr int lds = mid_stages(32 * kWM * kMI) * mid_stage_bytes(32 * kWM * kMI);
+    static std::once_flag once[64];
+    static hipError_t result[64];
+    int dev = 0;
+    MS_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) MS_FAIL(MS_ERR_UNSUPPORTED, "device index %d outside [0, 64)", dev);
+    std::call_once(once[dev], [&] {
+        result[dev] = hipFuncSetAttribute((const void*)gemm_rows_bf16<kMode, kWM, kMI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
+    const int slots = gemm_slots() / 2;   // the LDS stages take a whole compute unit
+    hipLaunchKernelGGL((gemm_rows_bf16<kMode, kWM, kMI>), dim3(units.units < slots ? units.units : slots), dim3(128 * kWM), lds, stream, g, units);
+    return MS_OK;
+}
+template <int kMode>
+static int mid_launch(const GemmArgs& g, int bm, const MidUnits& units, hipStream_t stream) {
+    switch (bm) {
+        case 32: return mid_launch_built<kMode, 1, 1>(g, units, stream);
+        case 64: return mid_launch_built<kMode, 2, 1>(g, units, stream);
+        case 96: return mid_launch_built<kMode, 3, 1>(g, units, stream);
+        case 128: return mid_launch_built<kMode, 4, 1>(g, units, stream);
+        case 192: return mid_launch_built<kMode, 3, 2>(g, units, stream);
+        default: return mid_launch_built<kMode, 4, 2>(g, units, stream);
+    }
+}
+
 static int skinny_dispatch(const GemmArgs& g, const SkinnyPlan& v, hipStream_t stream, bool swiglu = false) {
     static bool lds_allowed[64] = {};   // per device: the builds may use more than the default 64 KB of dynamic LDS
     int dev = 0;
@@ -884,6 +1134,31 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
             return MS_OK;
         }
     }
+    MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
+    if (mid.bm) {
+        if (split_k > 1 && (!workspace || ws_bytes < mid.workspace_bytes || !g_aligned16(workspace)))
+            MS_FAIL(MS_ERR_WORKSPACE, "ms_gemm_bf16: split-K workspace of %zu bytes needed", mid.workspace_bytes);
+        if (split_k == 1 && norm) MS_FAIL(MS_ERR_INVALID, "ms_gemm_add_rmsnorm_bf16: split_k >= 2 needed above %d rows", kSkinnyMaxRows);
+        if (split_k == 1 && mid.workspace_bytes && (!workspace || ws_bytes < mid.workspace_bytes || !g_aligned16(workspace)))
+            mid.units = {mid.units.tiles, mid.units.tiles, 1, mid.units.tiles};   // no room for the parts: whole tiles throughout
+        const int tail = mid.units.tiles - mid.units.main_tiles, parts = mid.units.parts;
+        g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
+        g.tail_col0 = mid.units.main_tiles * kMidBN;
+        g.partial = tail ? (float*)workspace : nullptr;
+        const int rc = swiglu ? mid_launch<kGemmSwiglu>(g, mid.bm, mid.units, stream) : mid_launch<kGemmPlain>(g, mid.bm, mid.units, stream);
+        if (rc != MS_OK) return rc;
+        if (norm) {
+            hipLaunchKernelGGL(reduce_add_rmsnorm, dim3((unsigned)g.M), dim3(kNormThreads), 0, stream, (const float*)g.partial, parts, g.M, g.N,
+                               norm->h, norm->weight, norm->eps, norm->out);
+        } else if (tail) {
+            const size_t quads = (size_t)g.M * (g.N - g.tail_col0) / (swiglu ? 8 : 4);
+            const dim3 rgrid((unsigned)((quads + 255) / 256));
+            if (swiglu) hipLaunchKernelGGL((gemm_reduce<true>), rgrid, dim3(256), 0, stream, g, parts, g.tail_col0);
+            else hipLaunchKernelGGL((gemm_reduce<false>), rgrid, dim3(256), 0, stream, g, parts, g.tail_col0);
+        }
+        MS_HIP_TRY(hipGetLastError());
+        return MS_OK;
+    }
     if (int rc = gemm_allow_lds()) return rc;
     GemmPlan p = gemm_plan(g.M, g.N, g.K, split_k);
     if (split_k == 1 && p.tail_groups && (!workspace || ws_bytes < p.workspace_bytes || !g_aligned16(workspace))) {
@@ -936,7 +1211,8 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
 
 extern "C" size_t ms_gemm_workspace_bytes(int M, int N, int K, int split_k) {
     if (M < 1 || N < 1 || K < 1 || split_k < 1 || N % ms::kGemmNUnit || K % (ms::kGemmBK * split_k)) return 0;
-    const size_t tiled = ms::gemm_plan(M, N, K, split_k).workspace_bytes;
+    const ms::MidPlan mid = ms::mid_plan(M, N, K, split_k);
+    const size_t tiled = mid.bm ? mid.workspace_bytes : ms::gemm_plan(M, N, K, split_k).workspace_bytes;
     const size_t few = ms::skinny_plan(M, N, K).workspace_bytes;   // enough for either kernel
     return tiled > few ? tiled : few;
 }
@@ -1085,6 +1361,17 @@ extern "C" int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int v
         rc = skinny_dispatch(g, sk, stream);
         if (rc != MS_OK) return rc;
     } else {
+        const MidPlan mid = mid_plan(M, vocab, K, 1);
+        if (mid.bm) {
+            g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
+            g.tail_col0 = vocab;
+            const int tiles = mid.units.tiles;   // whole tiles throughout
+            rc = mid_launch<kGemmArgmax>(g, mid.bm, {tiles, tiles, 1, tiles}, stream);
+            if (rc != MS_OK) return rc;
+            hipLaunchKernelGGL(argmax_finish, dim3((unsigned)M), dim3(256), 0, stream, (const unsigned long long*)workspace, groups, M, out);
+            MS_HIP_TRY(hipGetLastError());
+            return MS_OK;
+        }
         rc = gemm_allow_lds();
         if (rc != MS_OK) return rc;
         const GemmPlan p = gemm_plan(M, vocab, K, 1);

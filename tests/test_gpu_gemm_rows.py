@@ -1,0 +1,86 @@
+"""The projections at 17 to 256 rows (one row tile, K in steps of 64, loads straight into LDS): edges of
+the row blocks, K ranges shorter than the pipeline, uneven K parts, the divided last round.  Against the
+fp64 product; one bf16 rounding (2^-8 with a safety factor) plus the fp32 accumulation error."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(m, n, k, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    a = torch.empty(m, k, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    w = torch.empty(n, k, dtype=torch.bfloat16, device="cuda").normal_(0.0, k ** -0.5, generator=gen)
+    return gen, a, w, a.double() @ w.double().t().contiguous()
+
+
+def _close(got, ref, extra=0.0):
+    got, ref = got.double(), ref
+    assert torch.isfinite(got).all()
+    bound = 2.0 ** -8 * ref.abs() + 1e-5 * ref.abs().max() + extra
+    worst = float(((got - ref).abs() - bound).max())
+    assert worst <= 0, worst
+
+
+ROWS = [17, 31, 32, 33, 56, 64, 65, 96, 97, 128, 129, 160, 192, 193, 224, 255, 256]
+
+
+@pytest.mark.parametrize("m", ROWS)
+def test_rows_times_steps_and_parts(m):
+    from paper_2604_14889_amd import binding as M
+    # K steps of 64: one, fewer than the LDS stages, more; K parts that do not divide the steps evenly
+    for n, k, split in ((128, 64, 1), (256, 128, 1), (384, 192, 3), (128, 256, 2), (256, 320, 5), (640, 448, 2), (256, 1152, 4), (256, 2368, 2)):
+        gen, a, w, ref = _inputs(m, n, k, m * 100 + k)
+        bias = torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+        need = M.ms_gemm_workspace_bytes(m, n, k, split)
+        assert need == (split * m * n * 4 if split > 1 else 0)
+        ws = torch.full((max(need, 16),), 255, dtype=torch.uint8, device="cuda")     # NaN wherever a part is not written
+        cut = 128 if n > 128 else n
+        outs = [torch.full((m, c), float("nan"), dtype=torch.bfloat16, device="cuda") for c in ((cut, n - cut) if n > cut else (n,))]
+        M.ms_gemm_bf16(a, w, bias, outs, split, ws)
+        _close(torch.cat(outs, dim=1), ref + bias.double())
+
+
+@pytest.mark.parametrize("m,n,k", [(64, 66560, 512), (100, 33408, 1024), (200, 33408, 512), (256, 66048, 640), (17, 65664 + 128, 512)])
+def test_divided_last_round_and_whole_tiles_without_workspace(m, n, k):
+    """More tiles than fit the chip at once: the few left over are divided over K."""
+    from paper_2604_14889_amd import binding as M
+    gen, a, w, ref = _inputs(m, n, k, m + n)
+    need = M.ms_gemm_workspace_bytes(m, n, k, 1)
+    assert need > 0
+    for ws in (torch.full((need,), 255, dtype=torch.uint8, device="cuda"), None):
+        out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.ms_gemm_bf16(a, w, None, [out], 1, ws)
+        _close(out, ref)
+    # SwiGLU over the same product: gate and up rows interleaved in blocks of 32
+    blocks = ref.view(m, n // 64, 2, 32)
+    gate, up = blocks[:, :, 0].reshape(m, n // 2), blocks[:, :, 1].reshape(m, n // 2)
+    want = gate * torch.sigmoid(gate) * up
+    for ws in (torch.full((need,), 255, dtype=torch.uint8, device="cuda"), None):
+        act = torch.full((m, n // 2), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.ms_gemm_swiglu_bf16(a, w, act, ws)
+        _close(act, want, 2e-5 * (gate.abs() + 1) * (up.abs() + 1))
+
+
+@pytest.mark.parametrize("m", [17, 56, 96, 128, 192, 224])
+def test_greedy_token_and_norm_tail(m):
+    from paper_2604_14889_amd import binding as M
+    gen, a, w, ref = _inputs(m, 1280, 704, m)
+    out = torch.full((m,), -1, dtype=torch.int32, device="cuda")
+    M.ms_lm_head_argmax_bf16(a, w, out, torch.empty(M.ms_lm_head_argmax_workspace_bytes(m, 1280, 704), dtype=torch.uint8, device="cuda"))
+    top = ref.topk(2, dim=1)
+    clear = top.values[:, 0] - top.values[:, 1] > 1e-4 * ref.abs().max()
+    assert clear.sum() > 0.8 * m and (out.long() == top.indices[:, 0])[clear].all()
+    # the norm behind the product: the same bits as the product, then the norm
+    g = torch.empty(1280, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    h = torch.empty(m, 1280, device="cuda").normal_(generator=gen)
+    ws = torch.empty(M.ms_gemm_add_rmsnorm_workspace_bytes(m, 1280, 704, 2), dtype=torch.uint8, device="cuda")
+    h1, h2 = h.clone(), h.clone()
+    o1, o2, d = (torch.empty(m, 1280, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    M.ms_gemm_add_rmsnorm_bf16(a, w, h1, g, 1e-6, o1, 2, ws)
+    M.ms_gemm_bf16(a, w, None, [d], 2, ws)
+    M.ms_add_rmsnorm(h2, d, g, 1e-6, o2)
+    assert torch.equal(h1, h2) and torch.equal(o1.view(torch.int16), o2.view(torch.int16))
+    _close(d, ref)
