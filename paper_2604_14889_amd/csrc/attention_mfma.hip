@@ -90,13 +90,16 @@ struct MfmaArgs {
 // Partials travel between workgroups on different XCDs, whose L2 caches are not coherent with each
 // other.  They are written and read with device-scope relaxed atomic accesses (write-through /
 // cache-bypassing), which needs no cache write-back or invalidation; ordering comes from waiting
-// for the stores (workgroup barrier) before the arrival count is bumped.
+// for the stores (stores_done, then the workgroup barrier) before the arrival count is bumped.
 __device__ __forceinline__ void store_coherent(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ float load_coherent(const float* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Waits until this thread's stores have been performed.  A workgroup barrier alone does not: its
+// release is of workgroup scope, for which the compiler leaves stores to device memory outstanding.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // 16-byte accesses with the same cache policy (the bit device-scope atomics carry: the other XCDs'
 // L2s are bypassed), through a buffer descriptor over the partials: one instruction per float4
 // instead of two 8-byte atomics.  byte_off < 2 GiB.
@@ -605,7 +608,8 @@ __global__ __launch_bounds__(kThreads) void pv_attn_mfma_stream(MfmaArgs a) {
                 store_coherent(part + 32 * rb + (lane_m & 31), own_m);
                 store_coherent(part + kRows + 32 * rb + (lane_m & 31), own_l);
             }
-            __syncthreads();   // waits for every thread's partial stores
+            stores_done();     // each thread's partial stores, before any of them is counted
+            __syncthreads();
             if (tid == 0) __hip_atomic_fetch_add(ctr + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             if (tid == 0) {
@@ -951,7 +955,8 @@ __global__ __launch_bounds__(kThreads) void pv_attn_mfma_wide(MfmaArgs a) {
                                             make_float4(st.o[rb][db][4 * i4], st.o[rb][db][4 * i4 + 1], st.o[rb][db][4 * i4 + 2], st.o[rb][db][4 * i4 + 3]));
                 }
             }
-            __syncthreads();   // waits for every thread's partial stores
+            stores_done();     // each thread's partial stores, before any of them is counted
+            __syncthreads();
             if (tid == 0) __hip_atomic_fetch_add(ctr + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             if (tid == 0) {
