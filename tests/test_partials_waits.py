@@ -7,7 +7,12 @@ from tests.test_kernel_resources import compiled_kernels
 
 
 def test_partial_stores_are_waited_for_before_they_are_counted():
-    text, kernels = compiled_kernels("attention_mfma.hip")
+    assert waited_counts("attention_mfma.hip") >= 5      # four decode builds and the wide kernel
+    assert waited_counts("attention_split.hip") >= 1
+
+
+def waited_counts(source):
+    text, kernels = compiled_kernels(source)
     lines = text.split("\n")
     checked = 0
     for name in kernels:
@@ -26,4 +31,4 @@ def test_partial_stores_are_waited_for_before_they_are_counted():
                 continue
             assert any("s_waitcnt vmcnt(0)" in body[j] for j in range(stores[-1], barrier)), (name, i)
             checked += 1
-    assert checked >= 5      # four decode builds and the wide kernel
+    return checked
