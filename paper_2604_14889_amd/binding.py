@@ -152,13 +152,22 @@ def _sized(cache, t, what: str, n_elems: int, elem_size: Optional[int] = None) -
     if t.numel() < n_elems or t.element_size() != want:
         raise MsError(MS_ERR_INVALID, f"{what}: expected at least {n_elems} elements of {want} bytes, got "
                                       f"{t.numel()} of {t.element_size()}")
-    return _dev(t)
+    if not (t.is_cuda and t.is_contiguous()):
+        raise ValueError("expected a contiguous device tensor")
+    return t.data_ptr()
+
+
+# The current device and the raw handle of its current stream without building Stream objects: 0.2 us
+# instead of 3.6, which every call pays that is not told a stream.
+_raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream) -> Optional[int]:
     if type(stream) is int:                           # a raw hipStream_t value
         return stream or None
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device()) or None
         if not torch.cuda.is_available():
             return None
         return torch.cuda.current_stream().cuda_stream or None

@@ -92,6 +92,22 @@ __global__ void patch_page_table(int* __restrict__ d_pt, int* __restrict__ d_len
     else d_pt[(size_t)seq * max_pages + idx] = val;
 }
 
+// The same for a few triples that travel in the kernel arguments: one launch, no staging copy (an import
+// of 16 pages: 15 us of host time with the copy and its event, 5 without).
+constexpr int kInlineTriples = 160;
+struct InlineTriples {
+    int n;
+    int t[3 * kInlineTriples];
+};
+__global__ __launch_bounds__(kInlineTriples) void patch_page_table_inline(int* __restrict__ d_pt, int* __restrict__ d_len, InlineTriples p,
+                                                                          int max_pages) {
+    const int i = threadIdx.x;
+    if (i >= p.n) return;
+    const int seq = p.t[3 * i], idx = p.t[3 * i + 1], val = p.t[3 * i + 2];
+    if (idx < 0) d_len[seq] = val;
+    else d_pt[(size_t)seq * max_pages + idx] = val;
+}
+
 struct ScatterArgs {
     void* pool;
     const int* d_pt;
@@ -370,6 +386,16 @@ int check_seq(const ms_cache* c, int seq, const char* what) {
 int flush_page_table_patches(ms_cache* c, hipStream_t stream) {
     const size_t per = StageRing::kSlotBytes / (3 * sizeof(int));
     size_t n = c->pending_pt.size() / 3, done = 0;
+    if (n > 0 && n <= (size_t)kInlineTriples) {
+        InlineTriples p;
+        p.n = (int)n;
+        memcpy(p.t, c->pending_pt.data(), n * 3 * sizeof(int));
+        memset(p.t + 3 * n, 0, sizeof(p.t) - n * 3 * sizeof(int));
+        c->launches++;
+        hipLaunchKernelGGL(patch_page_table_inline, dim3(1), dim3(kInlineTriples), 0, stream, c->d_pt, c->d_len, p, c->d.max_pages_per_seq);
+        MS_HIP_TRY(hipGetLastError());
+        done = n;
+    }
     while (done < n) {
         size_t cnt = std::min(per, n - done);
         void* dev = nullptr;
@@ -387,14 +413,16 @@ int flush_page_table_patches(ms_cache* c, hipStream_t stream) {
 
 int reconcile(ms_cache* c) {
     if (!c->deferred) return MS_OK;
+    // the log can hold at most reserved_pages entries: one wait for everything that is needed
+    const int most = c->reserved_pages < (int)c->free_list.size() ? c->reserved_pages : (int)c->free_list.size();
+    int* state = c->h_reconcile;
+    int* lens = c->h_reconcile + 2 + kFreeListCap;
+    MS_HIP_TRY(hipMemcpyAsync(state, c->d_commit_state, (2 + most) * sizeof(int), hipMemcpyDeviceToHost, c->deferred_stream));
+    MS_HIP_TRY(hipMemcpyAsync(lens, c->d_len, c->d.max_seqs * sizeof(int), hipMemcpyDeviceToHost, c->deferred_stream));
     MS_HIP_TRY(hipStreamSynchronize(c->deferred_stream));
-    int used = 0;
-    MS_HIP_TRY(hipMemcpy(&used, c->d_commit_state, sizeof(int), hipMemcpyDeviceToHost));
-    if (used < 0 || used > (int)c->free_list.size()) MS_FAIL(MS_ERR_HIP, "device-side commit state is corrupt (%d pages taken of %zu listed)", used, c->free_list.size());
-    std::vector<int> who(used), lens(c->d.max_seqs);
-    if (used > 0) MS_HIP_TRY(hipMemcpy(who.data(), c->d_commit_state + 2, used * sizeof(int), hipMemcpyDeviceToHost));
-    MS_HIP_TRY(hipMemcpy(lens.data(), c->d_len, lens.size() * sizeof(int), hipMemcpyDeviceToHost));
-    if (!c->apply_device_commits(who.data(), used, c->free_list, lens.data()))
+    const int used = state[0];
+    if (used < 0 || used > most) MS_FAIL(MS_ERR_HIP, "device-side commit state is corrupt (%d pages taken of %zu listed)", used, c->free_list.size());
+    if (!c->apply_device_commits(state + 2, used, c->free_list, lens))
         MS_FAIL(MS_ERR_HIP, "device-side commit state is corrupt (a page of the log is not free, or its sequence is not live)");
     c->pending_growth.assign(c->d.max_seqs, 0);
     c->reserved_pages = 0;
@@ -599,6 +627,10 @@ int ms_cache_create(const ms_cache_desc* desc, ms_cache** out) {
         return fail(MS_ERR_HIP);
     }
     *c->h_error = 0;
+    if (hipHostMalloc((void**)&c->h_reconcile, (size_t)(2 + kFreeListCap + desc->max_seqs) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+        set_error("allocating the read-back buffer of device-side commits failed");
+        return fail(MS_ERR_HIP);
+    }
     *out = c;
     return MS_OK;
 }
@@ -615,6 +647,7 @@ int ms_cache_destroy(ms_cache* c) {
     if (c->d_plan) (void)hipFree(c->d_plan);
     if (c->d_arrive) (void)hipFree(c->d_arrive);
     if (c->h_error) (void)hipHostFree(c->h_error);
+    if (c->h_reconcile) (void)hipHostFree(c->h_reconcile);
     for (hipEvent_t e : c->prof_start) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->prof_stop) (void)hipEventDestroy(e);
     delete c;
@@ -801,10 +834,12 @@ int ms_commit_accepted_device(ms_cache* c, int B, const int* seq_ids, const int*
     SeqIds ids;
     memset(&ids, 0, sizeof(ids));
     for (int b = 0; b < B; ++b) {
-        ids.seq[b] = seq_ids[b];
-        c->pending_growth[seq_ids[b]] += n_max;
+        // what the rows this call may add can take beyond what the earlier ones may have taken
+        const int s = seq_ids[b], held = c->len[s] + c->pending_growth[s];
+        ids.seq[b] = s;
+        c->pending_growth[s] += n_max;
+        c->reserved_pages += pages_for((long)held + n_max) - pages_for(held);
     }
-    c->reserved_pages += B;
     c->deferred = true;
     c->deferred_stream = stream;
     c->launches++;

@@ -75,6 +75,7 @@ struct ms_cache : ms::HostTables {
     int* d_free = nullptr;       // device [kFreeListCap]: free pages in ascending order, as uploaded at the last reconcile
     int* d_commit_state = nullptr;  // device: {pages taken from d_free so far, layers arrived}, then [kFreeListCap] the sequence
                                  // that took each page, in order, then one arrival counter per layer (64 ints apart)
+    int* h_reconcile = nullptr;  // pinned: the commit state and the lengths as read back when the host catches up
     std::vector<int> free_list;  // host copy of what d_free holds
     bool free_list_valid = false;
     int reserved_pages = 0;      // upper bound of the pages device-side commits may have taken since the last reconcile
