@@ -697,7 +697,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// 17 to 256 rows (a few sequences up to a batch of 32): every row in one tile, so that W leaves HBM
+// Up to 256 rows (one sequence up to a batch of 32): every row in one tile, so that W leaves HBM
 // once and no tile row is empty.  The 256 x 256 tiles of gemm_tn_bf16 leave compute units without work at
 // these sizes (37888 columns: 148 workgroups) and keep too few weights in flight.
 //   * Tile 32 kWM kMI (M) x 128 (N), K in steps of 64 through as many LDS stages as the compute unit
@@ -719,13 +719,12 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
 // kernel, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
 // 91 -> 67, 224 rows 101 -> 94; LM head 216 -> 170 (6.4 TB/s), 238 -> 195, 285 -> 243, 332 -> 336; down 36 ->
-// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.  Starting the workgroups at
-// different K steps (L2 channels) changed nothing.
+// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27. 
 // ---------------------------------------------------------------------------------------------
 constexpr int kMidMaxRows = 256;
 constexpr int kMidBN = 128, kMidBK = 64;
-constexpr int mid_stage_bytes(int bm) { return (bm + kMidBN) * kMidBK * 2; }
-constexpr int mid_stages(int bm) { return 160 * 1024 / mid_stage_bytes(bm) < 6 ? 160 * 1024 / mid_stage_bytes(bm) : 6; }   // the whole LDS; six cover the latency
+constexpr int mid_stage_bytes(int rows) { return (rows + kMidBN) * kMidBK * 2; }
+constexpr int mid_stages(int rows) { return 160 * 1024 / mid_stage_bytes(rows) < 8 ? 160 * 1024 / mid_stage_bytes(rows) : 8; }   // the whole LDS
 
 // 64 lanes x 16 bytes from base + voff into LDS at lds .. lds + 1024, lane order.
 template <bool kStream>
@@ -742,6 +741,18 @@ __device__ __forceinline__ const char* wave_uniform(const char* p) {
 template <int kN>
 __device__ __forceinline__ void wait_loads() {   // at most kN of this wave's loads are still on their way; its LDS reads are done
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kN) : "memory");
+}
+
+// At most n steps of kLoads loads are still on their way (kMost: the most there can be).
+template <int kMost, int kLoads>
+__device__ __forceinline__ void wait_steps(int n) {
+    static_assert(kMost * kLoads < 64, "the load counter has six bits");
+    if constexpr (kMost == 0) {
+        wait_loads<0>();
+    } else {
+        if (n >= kMost) wait_loads<kMost * kLoads>();
+        else wait_steps<kMost - 1, kLoads>(n);
+    }
 }
 
 // The work of a launch: units 0 .. main_tiles are whole column tiles, the rest K parts of the tiles behind
@@ -764,11 +775,13 @@ __device__ __forceinline__ MidUnit mid_unit(const MidUnits& t, int u, int steps)
     return r;
 }
 
-template <int kMode, int kWM, int kMI>
+// kRowsA: rows of A kept in a stage (all of the tile's, or 8 or 16 of 32: the other operand rows then
+// repeat them and their products are not stored).
+template <int kMode, int kWM, int kMI, int kRowsA = 32 * kWM * kMI>
 __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUnits t) {
-    constexpr int kBM = 32 * kWM * kMI, kWaves = 2 * kWM, kS = mid_stages(kBM), kStage = mid_stage_bytes(kBM);
-    constexpr int kChunks = (kBM + kMidBN) / 8, kLoads = (kChunks + kWaves - 1) / kWaves;
-    static_assert((kS - 2) * kLoads < 64, "the load counter has six bits");
+    constexpr int kWaves = 2 * kWM, kS = mid_stages(kRowsA), kStage = mid_stage_bytes(kRowsA);
+    constexpr int kChunks = (kRowsA + kMidBN) / 8, kLoads = (kChunks + kWaves - 1) / kWaves;
+    static_assert(kRowsA == 32 * kWM * kMI || (kWM * kMI == 1 && kRowsA < 32), "fewer rows than the tile's: one block of 32");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
@@ -779,14 +792,20 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
         const int c = min(w + i * kWaves, kChunks - 1), row = 8 * c + (lane >> 3);
-        const int src = row < kBM ? min(row, g.M - 1) : row - kBM;   // rows past M: the last one again, never stored to the product
+        const int src = row < kRowsA ? min(row, g.M - 1) : row - kRowsA;   // rows past M: the last one again, never stored to the product
         voff[i] = (uint32_t)src * (uint32_t)g.K * 2u + 16u * ((lane & 7) ^ ((row >> 1) & 7));
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     // the next step to ask for; it runs ahead of the one being multiplied, into the next unit too
     int iu = blockIdx.x, i_buf = 0, in_flight = 0;
     MidUnit ahead = mid_unit(t, iu, steps);
-    int i_step = ahead.s_lo;
+    // Whole tiles are walked from different steps on, round and round: with K a power of two the rows of
+    // both operands lie a multiple of the L2 channels' interleave apart, and workgroups in step with each
+    // other would ask the same few channels (K = 4096, 7 rows: gate/up 48 -> 41 us, LM head of 128256 197 ->
+    // 166 us; K = 3584: no change).  K parts start apart by themselves.  Not for the greedy token: equal
+    // weight rows in different tiles have to give equal sums, so that the lowest column wins.
+    auto first_step = [&]() { return ahead.s_lo + (kMode != kGemmArgmax && ahead.whole ? (int)((uint32_t)steps * (blockIdx.x >> 3 & 31) >> 5) : 0); };
+    int i_step = first_step(), i_left = ahead.s_hi - ahead.s_lo;
     auto issue = [&]() {
         if (iu >= t.units) return;
         const size_t k_bytes = (size_t)i_step * (kMidBK * 2);
@@ -796,23 +815,26 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
         for (int i = 0; i < kLoads; ++i) {
             const int c = min(w + i * kWaves, kChunks - 1);
             const uint32_t lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)i_buf * kStage + 1024u * c);
-            if (8 * c < kBM) load_lds_1k<false>(lds, voff[i], ab);
+            if (8 * c < kRowsA) load_lds_1k<false>(lds, voff[i], ab);
             else load_lds_1k<true>(lds, voff[i], wb);   // W passes through once
         }
         ++in_flight;
         i_buf = i_buf + 1 == kS ? 0 : i_buf + 1;
-        if (++i_step == ahead.s_hi) {
+        if (++i_step == ahead.s_hi) i_step = ahead.s_lo;
+        if (--i_left == 0) {
             iu += gridDim.x;
             if (iu < t.units) {
                 ahead = mid_unit(t, iu, steps);
-                i_step = ahead.s_lo;
+                i_step = first_step();
+                i_left = ahead.s_hi - ahead.s_lo;
             }
         }
     };
-    // operand addresses: 16 bytes at k = 16 kk + 8 hf of a row; the chunk 2 kk + hf of row r lies at (2 kk + hf) ^ (r / 2 % 8)
-    const char* a_op = smem + (32 * kMI * wm + l32) * (kMidBK * 2);   // (rows a multiple of 16 apart within a wave: one swizzle)
-    const char* w_op = smem + (kBM + 64 * wn + l32) * (kMidBK * 2);
-    const int swz = (l32 >> 1) & 7;
+    // operand addresses: 16 bytes at k = 16 kk + 8 hf of a row; the chunk 2 kk + hf of the stage's row r lies at (2 kk + hf) ^ (r / 2 % 8)
+    const int l_a = kRowsA < 32 ? l32 & (kRowsA - 1) : l32;
+    const char* a_op = smem + (32 * kMI * wm + l_a) * (kMidBK * 2);   // (rows a multiple of 16 apart within a wave: one swizzle)
+    const char* w_op = smem + (kRowsA + 64 * wn + l32) * (kMidBK * 2);
+    const int swz = ((kRowsA + l32) >> 1) & 7, swz_a = (l_a >> 1) & 7;
 #pragma unroll
     for (int s = 0; s < kS - 1; ++s) issue();
     int buf = 0;
@@ -827,11 +849,7 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
                 for (int i = 0; i < 16; ++i) acc[ni][mi][i] = 0.f;
         for (int s = cur.s_lo; s < cur.s_hi; ++s) {
             // the oldest of the steps in flight has to be here (stores of an earlier unit only make the wait longer)
-            if (in_flight >= kS - 1) wait_loads<(kS - 2) * kLoads>();
-            else if (kS > 5 && in_flight == 4) wait_loads<3 * kLoads>();
-            else if (kS > 4 && in_flight == 3) wait_loads<2 * kLoads>();
-            else if (kS > 3 && in_flight == 2) wait_loads<kLoads>();
-            else wait_loads<0>();
+            wait_steps<kS - 2, kLoads>(in_flight - 1);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             --in_flight;
@@ -841,11 +859,11 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
             buf = buf + 1 == kS ? 0 : buf + 1;
             g_bf16x8_t wf[2][2], af[2][kMI];
             auto fetch = [&](int kk, int set) {
-                const int at = ((2 * kk + hf) ^ swz) * 16;
+                const int at = ((2 * kk + hf) ^ swz) * 16, at_a = ((2 * kk + hf) ^ swz_a) * 16;
 #pragma unroll
                 for (int ni = 0; ni < 2; ++ni) wf[set][ni] = *reinterpret_cast<const g_bf16x8_t*>(wb + ni * 32 * (kMidBK * 2) + at);
 #pragma unroll
-                for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at);
+                for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at_a);
             };
             fetch(0, 0);
 #pragma unroll
@@ -974,7 +992,7 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     MidPlan p = {0, {0, 0, 1, 0}, 0};
     if (M < 1 || M > kMidMaxRows || K % kMidBK || N % kMidBN || K / kMidBK < split_k) return p;
     const int blocks = (M + 31) / 32;
-    p.bm = blocks <= 4 ? 32 * blocks : blocks <= 6 ? 192 : 256;
+    p.bm = M <= 8 ? 8 : M <= 16 ? 16 : blocks <= 4 ? 32 * blocks : blocks <= 6 ? 192 : 256;
     const int tiles = N / kMidBN;
     p.units = {tiles, tiles, 1, tiles};
     const int slots = gemm_slots() / 2, steps = K / kMidBK;
@@ -1012,25 +1030,27 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     return p;
 }
 
-template <int kMode, int kWM, int kMI>
+template <int kMode, int kWM, int kMI, int kRowsA = 32 * kWM * kMI>
 static int mid_launch_built(const GemmArgs& g, const MidUnits& units, hipStream_t stream) {
-    constexpr int lds = mid_stages(32 * kWM * kMI) * mid_stage_bytes(32 * kWM * kMI);
+    constexpr int lds = mid_stages(kRowsA) * mid_stage_bytes(kRowsA);
     static std::once_flag once[64];
     static hipError_t result[64];
     int dev = 0;
     MS_HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= 64) MS_FAIL(MS_ERR_UNSUPPORTED, "device index %d outside [0, 64)", dev);
     std::call_once(once[dev], [&] {
-        result[dev] = hipFuncSetAttribute((const void*)gemm_rows_bf16<kMode, kWM, kMI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        result[dev] = hipFuncSetAttribute((const void*)gemm_rows_bf16<kMode, kWM, kMI, kRowsA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
     const int slots = gemm_slots() / 2;   // the LDS stages take a whole compute unit
-    hipLaunchKernelGGL((gemm_rows_bf16<kMode, kWM, kMI>), dim3(units.units < slots ? units.units : slots), dim3(128 * kWM), lds, stream, g, units);
+    hipLaunchKernelGGL((gemm_rows_bf16<kMode, kWM, kMI, kRowsA>), dim3(units.units < slots ? units.units : slots), dim3(128 * kWM), lds, stream, g, units);
     return MS_OK;
 }
 template <int kMode>
 static int mid_launch(const GemmArgs& g, int bm, const MidUnits& units, hipStream_t stream) {
     switch (bm) {
+        case 8: return mid_launch_built<kMode, 1, 1, 8>(g, units, stream);
+        case 16: return mid_launch_built<kMode, 1, 1, 16>(g, units, stream);
         case 32: return mid_launch_built<kMode, 1, 1>(g, units, stream);
         case 64: return mid_launch_built<kMode, 2, 1>(g, units, stream);
         case 96: return mid_launch_built<kMode, 3, 1>(g, units, stream);
@@ -1104,7 +1124,16 @@ static int gemm_allow_lds() {
 // Launches the tiles (and the reduction of the parts, if any).  g holds operands and destinations.
 static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, size_t ws_bytes, hipStream_t stream,
                        const NormTail* norm = nullptr) {
-    if (swiglu) {   // few rows: four tiles per wave, the whole K in one part
+    MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
+    // Up to 16 rows: gemm_rows_bf16 where its units fill three quarters of the chip and the workspace holds
+    // their partials, the few-row kernel otherwise (narrow outputs without split_k, no workspace).  us per
+    // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16: 7 rows gate/up 49 / 46, LM head 168 /
+    // 162, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.9 / 12.5 (252 units); 14 rows 52 / 47, 186 / 169, 38 /
+    // 29, 14.6 / 13.0, 14.3 / 13.6.
+    const bool mid_room = !mid.workspace_bytes || (workspace && ws_bytes >= mid.workspace_bytes && g_aligned16(workspace));
+    const bool mid_first = mid.bm && mid_room && !(norm && split_k == 1) && 8 * mid.units.units >= 3 * gemm_slots();
+    if (g.M <= kSkinnyMaxRows && mid_first) {
+    } else if (swiglu) {   // few rows: four tiles per wave, the whole K in one part
         SkinnyPlan sk = skinny_plan(g.M, g.N, g.K);
         if (sk.parts == 1 && g.N % 256 == 0) {
             sk.nt = 4;
@@ -1134,7 +1163,6 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
             return MS_OK;
         }
     }
-    MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
     if (mid.bm) {
         if (split_k > 1 && (!workspace || ws_bytes < mid.workspace_bytes || !g_aligned16(workspace)))
             MS_FAIL(MS_ERR_WORKSPACE, "ms_gemm_bf16: split-K workspace of %zu bytes needed", mid.workspace_bytes);
@@ -1354,24 +1382,24 @@ extern "C" int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int v
     for (int i = 1; i <= kGemmMaxOut; ++i) g.out_col[i] = vocab;
     g.partial = nullptr;
     g.keys = (unsigned long long*)workspace;
-    const int groups = argmax_groups(M, vocab, K);
+    int groups = argmax_groups(M, vocab, K);
     const SkinnyPlan sk = skinny_plan(M, vocab, K);
-    if (sk.parts == 1) {
+    const MidPlan mid = mid_plan(M, vocab, K, 1);
+    const int tiles = mid.units.tiles;
+    // Up to 16 rows by the rule of gemm_launch, except that rows of W a multiple of 2 KB apart (see the
+    // kernel's first_step) leave up to 8 rows to the few-row kernel: K = 3584 7 rows 172 -> 161 us, 14 rows 189 ->
+    // 165, K = 4096 7 rows 201 -> 198, 2 rows 187 -> 196.  (The 64-column groups take no more workspace.)
+    if (mid.bm && (sk.parts != 1 || (8 * tiles >= 3 * gemm_slots() && (M > 8 || K % 1024)))) {
+        groups = vocab / kGemmColGroup;
+        g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
+        g.tail_col0 = vocab;
+        rc = mid_launch<kGemmArgmax>(g, mid.bm, {tiles, tiles, 1, tiles}, stream);   // whole tiles throughout
+        if (rc != MS_OK) return rc;
+    } else if (sk.parts == 1) {
         g.tail_first = g.tail_blocks = g.tail_k = g.tail_col0 = 0;
         rc = skinny_dispatch(g, sk, stream);
         if (rc != MS_OK) return rc;
     } else {
-        const MidPlan mid = mid_plan(M, vocab, K, 1);
-        if (mid.bm) {
-            g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
-            g.tail_col0 = vocab;
-            const int tiles = mid.units.tiles;   // whole tiles throughout
-            rc = mid_launch<kGemmArgmax>(g, mid.bm, {tiles, tiles, 1, tiles}, stream);
-            if (rc != MS_OK) return rc;
-            hipLaunchKernelGGL(argmax_finish, dim3((unsigned)M), dim3(256), 0, stream, (const unsigned long long*)workspace, groups, M, out);
-            MS_HIP_TRY(hipGetLastError());
-            return MS_OK;
-        }
         rc = gemm_allow_lds();
         if (rc != MS_OK) return rc;
         const GemmPlan p = gemm_plan(M, vocab, K, 1);

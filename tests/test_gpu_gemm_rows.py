@@ -24,7 +24,7 @@ def _close(got, ref, extra=0.0):
     assert worst <= 0, worst
 
 
-ROWS = [17, 31, 32, 33, 56, 64, 65, 96, 97, 128, 129, 160, 192, 193, 224, 255, 256]
+ROWS = [1, 8, 9, 16, 17, 31, 32, 33, 56, 64, 65, 96, 97, 128, 129, 160, 192, 193, 224, 255, 256]
 
 
 @pytest.mark.parametrize("m", ROWS)
@@ -35,12 +35,32 @@ def test_rows_times_steps_and_parts(m):
         gen, a, w, ref = _inputs(m, n, k, m * 100 + k)
         bias = torch.empty(n, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
         need = M.ms_gemm_workspace_bytes(m, n, k, split)
-        assert need == (split * m * n * 4 if split > 1 else 0)
+        assert m <= 16 or need == (split * m * n * 4 if split > 1 else 0)
         ws = torch.full((max(need, 16),), 255, dtype=torch.uint8, device="cuda")     # NaN wherever a part is not written
         cut = 128 if n > 128 else n
         outs = [torch.full((m, c), float("nan"), dtype=torch.bfloat16, device="cuda") for c in ((cut, n - cut) if n > cut else (n,))]
         M.ms_gemm_bf16(a, w, bias, outs, split, ws)
         _close(torch.cat(outs, dim=1), ref + bias.double())
+
+
+@pytest.mark.parametrize("m", [1, 7, 8, 9, 16])
+def test_few_rows_with_enough_units_for_the_chip(m):
+    """Up to 16 rows run here where the K parts or the columns fill the chip (else on the few-row kernel)."""
+    from paper_2604_14889_amd import binding as M
+    for n, k, split in ((4608, 3584, 7), (3584, 2304, 8), (37888, 512, 1), (33024, 192, 1)):
+        gen, a, w, ref = _inputs(m, n, k, m * 7 + k)
+        need = M.ms_gemm_workspace_bytes(m, n, k, split)
+        for ws in (torch.full((max(need, 16),), 255, dtype=torch.uint8, device="cuda"), None):
+            if ws is None and split > 1:
+                continue
+            out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+            M.ms_gemm_bf16(a, w, None, [out], split, ws)
+            _close(out, ref)
+    tok = torch.full((m,), -1, dtype=torch.int32, device="cuda")
+    M.ms_lm_head_argmax_bf16(a, w, tok, torch.empty(M.ms_lm_head_argmax_workspace_bytes(m, n, k), dtype=torch.uint8, device="cuda"))
+    top = ref.topk(2, dim=1)
+    clear = top.values[:, 0] - top.values[:, 1] > 1e-4 * ref.abs().max()
+    assert (tok.long() == top.indices[:, 0])[clear].all() and clear.sum() >= 0.8 * m
 
 
 @pytest.mark.parametrize("m,n,k", [(64, 66560, 512), (100, 33408, 1024), (200, 33408, 512), (256, 66048, 640), (17, 65664 + 128, 512)])
