@@ -11,12 +11,27 @@
 #include <mutex>
 
 #include "attention.h"
+#include "attention_tile.h"
 #include "ms_device.h"
 #include "ms_internal.h"
 
 namespace ms {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t g_u32x4_t;
+
+// Three bfloat16 terms whose sum is the fp32 value exactly (8 + 8 + 8 bits of mantissa), two values at a
+// time in a register: t[0] + t[1] + t[2].
+__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t (&t)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        t[i] = pack_bf16x2(a, b);
+        if (i < 2) {
+            a -= __uint_as_float(t[i] << 16);
+            b -= __uint_as_float(t[i] & 0xffff0000u);
+        }
+    }
+}
 
 // sin and cos of an fp32 angle of any size (RoPE angles reach 1e5 rad), correct to an fp32 ulp: the
 // reduction by pi/2 (two-term constant) and the Taylor series on [-pi/4, pi/4] (next terms below
@@ -92,7 +107,7 @@ constexpr int kGenThreads = 64 * kGenWaves;
 // tokens are the cached ones in 16-token tiles (a tile is a page) followed by the in-flight ones,
 // and wave w takes tiles w, w + 4, ... of the share.
 //
-// v_mfma_f32_16x16x4_f32 twice: S^T = K . Q^T (A rows = tokens, B columns = query rows), then O^T =
+// fp32 caches: v_mfma_f32_16x16x4_f32 twice: S^T = K . Q^T (A rows = tokens, B columns = query rows), then O^T =
 // V^T . P^T.  The contraction index of the first is the head dimension in any order, so a lane reads
 // 16 bytes of its token's K row and feeds them to consecutive multiplications; the score registers
 // are the second product's B operand as they stand (register r holds token 4 (lane / 16) + r), and V
@@ -100,17 +115,24 @@ constexpr int kGenThreads = 64 * kGenWaves;
 // rotation table and the final merge of the four waves goes through LDS, and every cached byte is
 // read once per 16 kRB query rows.
 //
+// bf16 caches: the same layouts on the bf16 matrix cores, which are sixteen times as fast.  K and V are
+// bf16 already; rotated queries and softmax weights are written as three bf16 terms each, whose sum is
+// the fp32 value bit for bit, so the products are the fp32 ones at three multiplications instead of one
+// (error against 64 bits unchanged, 1.7e-3 = the rounding of the result).
+//
 // The kernel it replaces ran one wave per query row, which read the cache once per row and
 // reduced every score tile through LDS.  Measured per call with the combine: 16 sequences x 4000 tokens,
-// 16 / 4 heads of 64, bf16, 9 queries 567 -> 43 us; 4 sequences x 320 .. 1500 tokens, 8 / 8 heads of 64,
-// fp32, 7 queries 60 -> 14 us.  What bounds it: the fp32 matrix rate (256 FLOP per cycle and compute
-// unit) from two row blocks on; with one, the two launches and a chain of four memory round trips.
+// 16 / 4 heads of 64, bf16, 9 queries 567 -> 29 us (43 with the fp32 matrix instructions); 4 sequences x
+// 320 .. 1500 tokens, 8 / 8 heads of 64, fp32, 7 queries 60 -> 12 us.  What bounds it: the fp32 matrix
+// rate (256 FLOP per cycle and compute unit) on fp32 caches from two row blocks on, the vector work on the
+// scores on bf16 caches; with one block, the two launches and a chain of four memory round trips.
 template <typename T, int D, int kRB>
 __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, BatchMeta bm) {
     constexpr int kE = 16 / (int)sizeof(T);   // elements of a 16-byte load of K (or Q)
     constexpr int kNC = D / (4 * kE);         // such loads per lane and tile: element e of load c is d = 4 kE c + kE (lane / 16) + e
     constexpr int kEV = D / 16;               // V elements per lane and token: d = kEV (lane % 16) .. + kEV
     constexpr int H2 = D / 2;
+    constexpr bool kBf16 = sizeof(T) == 2;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     float2* cs = reinterpret_cast<float2*>(smem);   // [n_q][H2] cos, sin; later the waves' merge buffer
     const int split = blockIdx.x, g = blockIdx.y / a.n_chunks, chunk = blockIdx.y % a.n_chunks, b = blockIdx.z;
@@ -149,8 +171,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
         load_k(page);
         load_v(page);
     }
-    // raw query rows, 16 bytes at a time like K
+    // query rows, 16 bytes at a time like K; after the rotation fp32 (fp32 caches) or three bf16 terms
     float q[kRB][kNC * kE];
+    uint32_t qt[kBf16 ? kRB : 1][kNC][3][4];
     int qi[kRB];
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb) {
@@ -185,6 +208,35 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
                 q[rb][(c + kNC / 2) * kE + e] = (x1 * f.x + x0 * f.y) * scale_log2;
             }
 
+    if constexpr (kBf16) {
+#pragma unroll
+        for (int rb = 0; rb < kRB; ++rb)
+#pragma unroll
+            for (int c = 0; c < kNC; ++c)
+#pragma unroll
+                for (int e = 0; e < kE; e += 2) {
+                    uint32_t t3[3];
+                    split_bf16x3(q[rb][c * kE + e], q[rb][c * kE + e + 1], t3);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) qt[rb][c][i][e / 2] = t3[i];
+                }
+    }
+    // element x of a query row in fp32: the three terms' sum is exact
+    auto q_f32 = [&](int rb, int x) -> float {
+        if constexpr (kBf16) {
+            float v = 0.f;
+#pragma unroll
+            for (int i = 2; i >= 0; --i) {
+                uint32_t w = qt[rb][x / kE][i][x % kE / 2];
+                asm volatile("" : "+v"(w));   // (worked out where it is used, not kept in registers across the stream)
+                v += (x & 1) ? __uint_as_float(w & 0xffff0000u) : __uint_as_float(w << 16);
+            }
+            return v;
+        } else {
+            return q[rb][x];
+        }
+    };
+
     float m[kRB], l[kRB];        // row maximum in use; this lane's part of the row sum
     f32x4_t o[kRB][kEV];         // register rr of o[rb][e]: d = kEV (4 j + rr) + e of row l16
 #pragma unroll
@@ -212,11 +264,35 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
         for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] - mu);
         l[rb] += (s[0] + s[1]) + (s[2] + s[3]);
     };
+    uint2 va[kBf16 ? kEV : 1];   // bf16: V^T operands, a lane's four tokens of element e
+    auto pack_v = [&]() {
+        if constexpr (kBf16) {
+#pragma unroll
+            for (int e = 0; e < kEV; ++e) {
+                const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+                va[e].x = __builtin_amdgcn_perm(vr[1].w[e / 2], vr[0].w[e / 2], sel);
+                va[e].y = __builtin_amdgcn_perm(vr[3].w[e / 2], vr[2].w[e / 2], sel);
+            }
+        }
+    };
     auto pv = [&](const f32x4_t& p, int rb) {
+        if constexpr (kBf16) {
+            uint32_t t01[3], t23[3];
+            split_bf16x3(p[0], p[1], t01);
+            split_bf16x3(p[2], p[3], t23);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+            for (int i = 2; i >= 0; --i) {   // smallest terms first
+                const s16x4_t pb = __builtin_bit_cast(s16x4_t, make_uint2(t01[i], t23[i]));
 #pragma unroll
-            for (int e = 0; e < kEV; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r].get(e), p[r], o[rb][e], 0, 0, 0);
+                for (int e = 0; e < kEV; ++e)
+                    o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, va[e]), pb, o[rb][e], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int e = 0; e < kEV; ++e) o[rb][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r].get(e), p[r], o[rb][e], 0, 0, 0);
+        }
     };
 
     for (; t < t_cache; t += kGenWaves) {
@@ -225,6 +301,20 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
         f32x4_t s[kRB][2];   // two chains per block: consecutive multiplications do not wait for each other
 #pragma unroll
         for (int rb = 0; rb < kRB; ++rb) s[rb][0] = s[rb][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if constexpr (kBf16) {
+#pragma unroll
+            for (int i = 2; i >= 0; --i)   // smallest terms first
+#pragma unroll
+                for (int c = 0; c < kNC; ++c) {
+                    const g_u32x4_t kw = {kr[c].w[0], kr[c].w[1], kr[c].w[2], kr[c].w[3]};
+#pragma unroll
+                    for (int rb = 0; rb < kRB; ++rb) {
+                        const g_u32x4_t qw = {qt[rb][c][i][0], qt[rb][c][i][1], qt[rb][c][i][2], qt[rb][c][i][3]};
+                        s[rb][c & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kw), __builtin_bit_cast(bf16x8_t, qw),
+                                                                               s[rb][c & 1], 0, 0, 0);
+                    }
+                }
+        } else {
 #pragma unroll
         for (int c = 0; c < kNC; ++c)
 #pragma unroll
@@ -232,6 +322,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
 #pragma unroll
                 for (int rb = 0; rb < kRB; ++rb)
                     s[rb][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[c].get(e), q[rb][c * kE + e], s[rb][e & 1], 0, 0, 0);
+        }
         load_k(page);
         const int valid = L - t * MS_PAGE_SIZE;
         if (valid < MS_PAGE_SIZE)   // the last page: what follows the sequence's end may be anything
@@ -246,6 +337,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
                     if (4 * j + r >= valid) s[rb][0][r] = -INFINITY;
             softmax(s[rb][0], rb);
         }
+        pack_v();
 #pragma unroll
         for (int rb = 0; rb < kRB; ++rb) pv(s[rb][0], rb);
         load_v(page);
@@ -263,6 +355,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
             vr[r].load((const T*)a.v_new + (((size_t)b * a.n_q + (tv < a.n_q ? tv : a.n_q - 1)) * a.n_kv_heads + g) * D + kEV * l16);
             vr[r].clear_unless(tv < a.n_q);
         }
+        pack_v();
         float k[kNC * kE];
 #pragma unroll
         for (int c = 0; c < kNC / 2; ++c)
@@ -277,7 +370,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
         for (int rb = 0; rb < kRB; ++rb) {
             f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < kNC * kE; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q[rb][c], s, 0, 0, 0);
+            for (int c = 0; c < kNC * kE; ++c) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[c], q_f32(rb, c), s, 0, 0, 0);
             const int i = qi[rb];
             const int ctx = a.ctx_new ? a.ctx_new[b * a.n_q + i] : (i < a.n_verify ? i : a.n_verify);
 #pragma unroll
