@@ -991,6 +991,7 @@ struct MidPlan {
 static MidPlan mid_plan(int M, int N, int K, int split_k) {
     MidPlan p = {0, {0, 0, 1, 0}, 0};
     if (M < 1 || M > kMidMaxRows || K % kMidBK || N % kMidBN || K / kMidBK < split_k) return p;
+    if (K > 1 << 22) return p;   // a tile's rows are addressed with 32-bit byte offsets
     const int blocks = (M + 31) / 32;
     p.bm = M <= 8 ? 8 : M <= 16 ? 16 : blocks <= 4 ? 32 * blocks : blocks <= 6 ? 192 : 256;
     const int tiles = N / kMidBN;
