@@ -369,8 +369,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
 }
 
 // Folds the shares' partials in their order, normalises and writes the bf16 rows.  A workgroup takes one
-// 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with eight
-// partials requested at a time.
+// 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with kBatch
+// partials requested in one memory round trip.
+template <int kBatch>
 __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
     const int rb = blockIdx.x >> 2, db = blockIdx.x & 3, g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
     const int lane = threadIdx.x & 63, i4 = threadIdx.x >> 6, hf = lane >> 5, row = 32 * rb + (lane & 31);
@@ -381,7 +382,6 @@ __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
     const int at = 2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4;
     float m = -INFINITY, l = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    constexpr int kBatch = 8;
     for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
         float pm[kBatch], pl[kBatch];
         float4 px[kBatch];
@@ -489,7 +489,10 @@ int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, in
     hipLaunchKernelGGL(pv_attn_mfma_split, dim3(n_splits, a.n_kv_heads, B * a.n_chunks), dim3(kSplitThreads), split_lds_bytes(a.n_q), stream, a);
     if (n_splits > 1 && !a.arrive) {
         c->launches++;
-        hipLaunchKernelGGL(pv_attn_mfma_fold, dim3(8, a.n_kv_heads, B * a.n_chunks), dim3(256), 0, stream, a);
+        const dim3 grid(8, a.n_kv_heads, B * a.n_chunks);
+        if (n_splits <= 8) hipLaunchKernelGGL(pv_attn_mfma_fold<8>, grid, dim3(256), 0, stream, a);
+        else if (n_splits <= 16) hipLaunchKernelGGL(pv_attn_mfma_fold<16>, grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL(pv_attn_mfma_fold<32>, grid, dim3(256), 0, stream, a);
     }
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;
