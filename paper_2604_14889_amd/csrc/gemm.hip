@@ -26,8 +26,10 @@
 // whole tile's time.  The gate/up projection of the MLP can apply SwiGLU in the epilogue: with the
 // weight rows interleaved in blocks of 32 (gate block, up block), a lane holds gate and up of the
 // same output element in two accumulators and writes silu(gate) * up directly.
-// Steps of at most 16 rows (one or two sequences) are bound by reading W once and run on a second
-// kernel, further down, that streams 16 weight rows per wave through the matrix cores.
+// Steps of up to 256 rows are bound by bringing W to the compute units and run on a second kernel,
+// further down (gemm_rows_bf16), that computes row tiles of the step's own height.  A third kernel, for
+// at most 16 rows, streams 16 weight rows per wave through the matrix cores; it keeps the products that
+// give the second one too few workgroups (narrow outputs without a K split or a workspace).
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -718,8 +720,8 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // (activations come from L2 but return in order behind the weights), so the weights' share
 // 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
 // kernel, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
-// 91 -> 67, 224 rows 101 -> 94; LM head 216 -> 170 (6.4 TB/s), 238 -> 195, 285 -> 243, 332 -> 336; down 36 ->
-// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27. 
+// 91 -> 67, 224 rows 101 -> 94; LM head 216 -> 170 (6.4 TB/s), 238 -> 195, 285 -> 243; down 36 ->
+// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMidMaxRows = 256;
 constexpr int kMidBN = 128, kMidBK = 64;
@@ -997,6 +999,14 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     const int tiles = N / kMidBN;
     p.units = {tiles, tiles, 1, tiles};
     const int slots = gemm_slots() / 2, steps = K / kMidBK;
+    // Wide outputs that fill the chip with 256 x 256 tiles too: above 128 rows those bring in fewer bytes per
+    // column.  us here / there, 152064 columns: 128 rows 243 / 285, 160 rows 324 / 307, 192 rows 315 / 319, 208 rows
+    // 337 / 327, 224 rows 340 / 338, 256 rows 348 / 358; 128256 columns, K = 4096: 160 rows 301 / 297, 192 rows
+    // 294 / 307, 208 rows 325 / 314, 256 rows 327 / 329.
+    if (split_k == 1 && M > 128 && tiles >= 2 * slots) {
+        p.bm = 0;
+        return p;
+    }
     if (split_k > 1) {
         // at most split_k parts: the number that leaves the shortest chain of steps, the fewest of equals
         int parts = 2;

@@ -104,3 +104,16 @@ def test_greedy_token_and_norm_tail(m):
     M.ms_add_rmsnorm(h2, d, g, 1e-6, o2)
     assert torch.equal(h1, h2) and torch.equal(o1.view(torch.int16), o2.view(torch.int16))
     _close(d, ref)
+
+
+@pytest.mark.parametrize("m", [128, 129, 256])
+def test_wide_outputs_that_fill_the_chip_on_either_kernel(m):
+    """65664 columns are more than two row-tile units per compute unit: above 128 rows the 256 x 256 tiles take them."""
+    from paper_2604_14889_amd import binding as M
+    n, k = 65664, 128
+    gen, a, w, ref = _inputs(m, n, k, m)
+    need = M.ms_gemm_workspace_bytes(m, n, k, 1)
+    for ws in (torch.full((max(need, 16),), 255, dtype=torch.uint8, device="cuda"), None):
+        out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.ms_gemm_bf16(a, w, None, [out], 1, ws)
+        _close(out, ref)
