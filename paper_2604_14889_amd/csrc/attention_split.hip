@@ -370,7 +370,8 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
 
 // Folds the shares' partials in their order, normalises and writes the bf16 rows.  A workgroup takes one
 // 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with kBatch
-// partials requested in one memory round trip.
+// partials requested in one memory round trip.  Bound by those round trips: 26 shares (one sequence of
+// 4096 tokens, 7 queries) in four trips of 8 or one of 32: 17.4 / 16.7 us per call of both launches.
 template <int kBatch>
 __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
     const int rb = blockIdx.x >> 2, db = blockIdx.x & 3, g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
@@ -424,15 +425,18 @@ static int split_chunks(int group, int n_q) { return (n_q + kRows / group - 1) /
 // units, us per call with the second launch against the kernel that would take the call otherwise
 // (7 queries, 28 / 4 heads unless said):
 //   decode  1 x 1000 tokens 15 / 18, 1 x 4096 17 / 21, 1 x 16000 23 / 32, 4 x 4096 19 / 24, 8 x 4096
-//           26 / 29, 16 x 2048 26 / 26; 32 x 2048 39 / 35, 16 x 8000 62 / 54; 32 / 8 heads 4 x 4096
-//           25 / 28, 8 x 4096 38 / 35: up to 4096 (tile, KV head) pairs the latency chain is what
-//           counts, above it the bytes (each row block's wave loads the tile for itself).  Below four
-//           shares per (sequence, KV head) the streaming kernel's eight waves per share hide more
-//           (32 x 500 tokens: 20 / 19)
+//           26 / 29, 16 x 2048 26 / 26; 32 x 2048 39 / 35, 16 x 8000 62 / 54.  The streaming kernel's last
+//           workgroup folds 256 / pairs shares by itself, this kernel's waves read the cache once per row
+//           block: the fewer the (sequence, KV head) pairs, the more (tile, KV head) pairs it takes until
+//           the bytes count.  9 queries: 4 pairs 1 x 96000 57 / 64, 1 x 128000 71 / 74; 8 pairs 2 x 40000 47 /
+//           51, 2 x 64000 68 / 65; 16 pairs 4 x 16000 38 / 40, 4 x 20000 46 / 46, 4 x 24000 52 / 50; 24 pairs
+//           3 x 10000 38 / 37; 32 pairs 8 x 6000 31 / 33, 8 x 8000 38 / 38; 64 pairs 16 x 3000 32 / 31: the
+//           break-even falls with the root of the pairs.  Below four shares per pair the streaming
+//           kernel's eight waves per share hide more (32 x 500 tokens: 20 / 19)
 //   wide    64 queries: 1 x 100 16 / 35, 1 x 2000 19 / 140, 4 x 2000 35 / 109, 8 x 4000 87 / 114, 32 / 8
 //           heads 8 x 4000 91 / 97; 41 queries: 8 x 4000 68 / 100.  2.7 ns per (tile, KV head, chunk)
 //           there; the wide kernel reads the cache once and is ahead from about 32768 of them on
-constexpr long kSplitMaxTiles = 4096, kSplitMaxPairs = 64, kSplitMaxWideTiles = 32768;
+constexpr long kSplitMaxTiles = 32768, kSplitMaxPairs = 64, kSplitMaxWideTiles = 32768;   // decode: over the root of the pairs
 int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, int* n_splits) {
     const long chunks = split_chunks(c->group, n_q), n_new = (n_q + kTile - 1) / kTile;
     long tiles = 0, longest = 0;
@@ -443,7 +447,11 @@ int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t
     }
     const long base = B * chunks * c->d.n_kv_heads;   // workgroups per share
     const long work = tiles * c->d.n_kv_heads * chunks;
-    if (chunks == 1 && n_q <= kSplitDecodeQueries ? work > kSplitMaxTiles || base > kSplitMaxPairs : work > kSplitMaxWideTiles) return 0;
+    if (chunks == 1 && n_q <= kSplitDecodeQueries) {
+        if (base > kSplitMaxPairs || work > kSplitMaxTiles || work * work * base > kSplitMaxTiles * kSplitMaxTiles) return 0;
+    } else if (work > kSplitMaxWideTiles) {
+        return 0;
+    }
     // one workgroup per compute unit; two where one would leave a quarter of the chip idle
     const long per = longest + n_new;
     long s = std::max(1L, c->n_cus / base);

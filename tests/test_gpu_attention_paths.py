@@ -72,6 +72,7 @@ SPLIT = [
     (28, 4, 1, 0, [16, 17, 48]),                           # a tile whose second page does not exist
     (32, 8, 5, 4, [4100]),
     (28, 4, 4, 3, [9000, 40]),                             # many shares, most of them empty for the second sequence
+    (28, 4, 4, 3, [12000]),                                # more shares than one round trip of the second launch takes
     (16, 2, 8, 0, [700]),                                  # 64 rows
     (4, 4, 16, 0, [130]),                                  # one row block
     (28, 4, 10, 0, [65, 0]),                               # two chunks, the second with one query
