@@ -98,6 +98,86 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float4 v) {
     *reinterpret_cast<uint2*>(p) = u;
 }
 
+// One query row over cached tokens c0 .. c1 and in-flight tokens f0 .. f1, by one wave: a product at a
+// time in fp32, tokens (lanes) for the scores and head dimensions for the values.  In-flight tokens without
+// weight are left out.  Leaves the row's maximum (log2 units), its sum and elements lane + 64 e of O.
+template <typename T, int D>
+__device__ void attend_row(const AttnArgs& a, int b, int g, int row, const int* pt, int c0, int c1, int f0, int f1, float* q_s, float& m, float& l,
+                           float (&acc)[D / 64]) {
+    constexpr int H2 = D / 2, kE = D / 64;
+    const int lane = threadIdx.x & 63, i = row / a.group;
+    const float scale_log2 = a.scale * 1.44269504088896340736f;
+    __builtin_amdgcn_wave_barrier();   // (the row before this one has been read)
+    if (lane < H2) {
+        const T* qp = (const T*)a.q + (((size_t)b * a.n_q + i) * a.n_q_heads + g * a.group + row % a.group) * D;
+        const float x0 = to_float(qp[lane]), x1 = to_float(qp[lane + H2]);
+        float sn, cs;
+        sincos_f64((float)a.pos[b * a.n_q + i] * a.inv_freq[lane], &sn, &cs);
+        q_s[lane] = (x0 * cs - x1 * sn) * scale_log2;
+        q_s[lane + H2] = (x1 * cs + x0 * sn) * scale_log2;
+    }
+    __builtin_amdgcn_wave_barrier();
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int e = 0; e < kE; ++e) acc[e] = 0.f;
+    auto weigh = [&](float s, bool valid) -> float {
+        float mn = s;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mn = fmaxf(mn, __shfl_xor(mn, o, 64));
+        mn = fmaxf(m, mn);
+        const float mu = mn == -INFINITY ? 0.f : mn, f = __builtin_amdgcn_exp2f(m - mu), p = valid ? __builtin_amdgcn_exp2f(s - mu) : 0.f;
+        m = mn;
+        float sum = p;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        l = l * f + sum;
+#pragma unroll
+        for (int e = 0; e < kE; ++e) acc[e] *= f;
+        return p;
+    };
+    for (int t0 = c0; t0 < c1; t0 += 64) {
+        const int tok = t0 + lane;
+        float s = -INFINITY;
+        if (tok < c1) {
+            const T* kp = (const T*)a.pool_layer + (size_t)pt[tok / MS_PAGE_SIZE] * a.page_elems + ((size_t)g * 2 * MS_PAGE_SIZE + tok % MS_PAGE_SIZE) * D;
+            s = 0.f;
+            for (int d = 0; d < D; ++d) s += to_float(kp[d]) * q_s[d];
+        }
+        const float p = weigh(s, tok < c1);
+        for (int tt = 0; tt < 64 && t0 + tt < c1; ++tt) {
+            const int at = t0 + tt;
+            const T* vp = (const T*)a.pool_layer + (size_t)pt[at / MS_PAGE_SIZE] * a.page_elems + (((size_t)g * 2 + 1) * MS_PAGE_SIZE + at % MS_PAGE_SIZE) * D;
+            const float pp = __shfl(p, tt, 64);
+#pragma unroll
+            for (int e = 0; e < kE; ++e) acc[e] += pp * to_float(vp[lane + 64 * e]);
+        }
+    }
+    if (f0 >= f1) return;
+    const int tok = f0 + lane, ctx = a.ctx_new ? a.ctx_new[b * a.n_q + i] : (i < a.n_verify ? i : a.n_verify);
+    const bool valid = tok < f1 && (tok < ctx || tok == i);
+    float s = -INFINITY;
+    if (valid) {
+        const T* kp = (const T*)a.k_new + (((size_t)b * a.n_q + tok) * a.n_kv_heads + g) * D;
+        const float pos = (float)a.pos[b * a.n_q + tok];
+        s = 0.f;
+        for (int d = 0; d < H2; ++d) {
+            float sn, cs;
+            sincos_f64(pos * a.inv_freq[d], &sn, &cs);
+            const float x0 = to_float(kp[d]), x1 = to_float(kp[d + H2]);
+            s += q_s[d] * (x0 * cs - x1 * sn) + q_s[d + H2] * (x1 * cs + x0 * sn);
+        }
+    }
+    const float p = weigh(s, valid);
+    for (int tt = 0; tt < f1 - f0; ++tt) {
+        const float pp = __shfl(p, tt, 64);
+        if (pp == 0.f) continue;
+        const T* vp = (const T*)a.v_new + (((size_t)b * a.n_q + f0 + tt) * a.n_kv_heads + g) * D;
+#pragma unroll
+        for (int e = 0; e < kE; ++e) acc[e] += pp * to_float(vp[lane + 64 * e]);
+    }
+}
+
 constexpr int kGenWaves = 4;
 constexpr int kGenThreads = 64 * kGenWaves;
 
@@ -387,8 +467,11 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
     // a time; wave rr folds register rr, i.e. d = kEV (4 j + rr) .. + kEV of every row ----
     float* ml = reinterpret_cast<float*>(smem);                 // [wave][kRB * 16][2]
     float* ob = ml + kGenWaves * kRB * 16 * 2;                  // [wave][rr][lane][kEV]
+    int* redo = reinterpret_cast<int*>(ob + kGenWaves * 4 * kEV * 64);   // [kRB * 16] rows that came out NaN
+    bool nan_seen = false;
     float mw[kRB][kGenWaves], m_all[kRB], l_all[kRB];
     __syncthreads();
+    if (tid < 16 * kRB) redo[tid] = 0;
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb) {
         l[rb] += __shfl_xor(l[rb], 16, 64);
@@ -433,6 +516,13 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
             }
         }
         const int row = row0 + 16 * rb + l16;
+        float sum = l_all[rb];
+#pragma unroll
+        for (int e4 = 0; e4 < kEV / 4; ++e4) sum += (acc[e4].x + acc[e4].y) + (acc[e4].z + acc[e4].w);
+        if (sum != sum && row < n_rows) {
+            redo[16 * rb + l16] = 1;
+            nan_seen = true;
+        }
         if (row < n_rows) {
             const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
             const int d = kEV * (4 * j + w);
@@ -452,6 +542,26 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
                 }
             }
         }
+    }
+    // Keys or values that are not finite: the matrix products multiply tokens a row does not see by a weight of
+    // zero, and three-term operands infinities by terms of zero.  Both are NaN where the inputs may not call for
+    // it, so such rows are worked out again, a product at a time (nothing is live here: the registers of the
+    // kernel above are not affected).
+    if (!__syncthreads_or(nan_seen)) return;
+    for (int r = w; r < 16 * kRB; r += kGenWaves) {
+        if (!redo[r]) continue;
+        const int row = row0 + r, cached = n_cache * MS_PAGE_SIZE;
+        float mr, lr, acc[D / 64];
+        attend_row<T, D>(a, b, g, row, pt, min(t_lo * MS_PAGE_SIZE, L), min(t_hi * MS_PAGE_SIZE, L), max(t_lo * MS_PAGE_SIZE - cached, 0),
+                         min(t_hi * MS_PAGE_SIZE - cached, a.n_q), ob + w * D, mr, lr, acc);
+        const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) {
+            if (a.n_splits == 1) ((T*)a.out)[orow * D + lane + 64 * e] = from_float<T>(acc[e] * (1.f / lr));
+            else a.ws[(orow * a.n_splits + split) * D + lane + 64 * e] = acc[e];
+        }
+        if (a.n_splits > 1 && lane == 0)
+            *reinterpret_cast<float2*>(a.ws + (size_t)gridDim.z * a.n_q * a.n_q_heads * a.n_splits * D + (orow * a.n_splits + split) * 2) = make_float2(mr, lr);
     }
 }
 
@@ -506,7 +616,7 @@ static int rows_splits(int wgs, int max_len, int n_q) {
 
 template <typename T, int D, int kRB>
 static int launch_rows_built(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, hipStream_t stream) {
-    const int merge = (kGenWaves * kRB * 16 * 2 + kGenWaves * 4 * D / 16 * 64) * (int)sizeof(float), table = a.n_q * D / 2 * (int)sizeof(float2);
+    const int merge = (kGenWaves * kRB * 16 * 2 + kGenWaves * 4 * D / 16 * 64 + kRB * 16) * (int)sizeof(float), table = a.n_q * D / 2 * (int)sizeof(float2);
     hipLaunchKernelGGL((pv_attn_rows<T, D, kRB>), dim3(a.n_splits, a.n_kv_heads * a.n_chunks, B), dim3(kGenThreads), merge > table ? merge : table,
                        stream, a, bm);
     c->launches++;

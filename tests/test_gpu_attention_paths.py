@@ -118,3 +118,42 @@ def test_share_per_workgroup_kernel_follows_the_device_length_and_agrees_with_th
         streamed = ses.attention(0, ids, 5, 4, q, kn, vn, p)
         for other in (caught_up, streamed):
             check_out(S.to_host_f32(lagging), S.to_host_f32(other).astype(np.float64), "bf16", "after device-side commits")
+
+
+NOT_FINITE = [
+    # dtype, Hq, Hkv, D, n_verify, n_foresight, lengths: one and several shares, one and several chunks of rows
+    ("f32", 8, 8, 64, 4, 3, [30]),
+    ("f32", 8, 2, 128, 7, 2, [400, 15]),
+    ("bf16", 16, 4, 64, 5, 4, [700, 31]),
+    ("bf16", 7, 1, 64, 20, 0, [100]),
+    ("bf16", 66, 1, 128, 1, 2, [300]),
+]
+
+
+@pytest.mark.parametrize("where", ["v_new", "cached_v", "cached_k"])
+@pytest.mark.parametrize("dtype,hq,hkv,d,nv,nf,lengths", NOT_FINITE)
+def test_general_kernel_keeps_infinities_where_they_belong(dtype, hq, hkv, d, nv, nf, lengths, where):
+    """An infinite or NaN value of an in-flight token reaches the rows that see the token and no others; an
+    infinite cached value its own column; a score of -infinity has no weight."""
+    M, _ = _mods()
+    sh = W.AttnShape("inf", dtype, len(lengths), hq, hkv, d, nv, nf, lengths, 1.0 if dtype == "f32" else 0.5, 10000.0)
+    inp = W.attention_inputs(sh, 902, hq)
+    inf, nan = (np.uint16(0x7F80), np.uint16(0x7FC0)) if dtype == "bf16" else (np.float32(np.inf), np.float32(np.nan))
+    neg = np.uint16(0xFF80) if dtype == "bf16" else np.float32(-np.inf)
+    if where == "v_new":
+        inp.v_new[:, -1, :, 5] = inf                       # the last token: only its own rows see it
+        inp.v_new[0, nv - 1, 0, 3] = nan
+    else:
+        page = inp.page_tables[0][0]
+        inp.pool[0, page, :, 1 if where == "cached_v" else 0, 3, 7] = inf if where == "cached_v" else neg
+    ses, ora, ids = setup_pair(inp)
+    with ses:
+        pos = pids_for(inp, M)
+        got = run_gpu_attention(ses, inp, ids, pos).astype(np.float64)
+        with np.errstate(invalid="ignore"):
+            want = oracle_attention(ora, inp, ids, pos)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+    finite = np.isfinite(want)
+    assert finite.sum() >= 0.3 * want.size and not finite.all()
+    check_out(got, np.where(finite, want, np.nan), dtype, f"{where} {sh}"[:200])
