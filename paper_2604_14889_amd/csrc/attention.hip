@@ -98,6 +98,9 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float4 v) {
     *reinterpret_cast<uint2*>(p) = u;
 }
 
+constexpr int kGenWaves = 4;
+constexpr int kGenThreads = 64 * kGenWaves;
+
 // One query row over cached tokens c0 .. c1 and in-flight tokens f0 .. f1, by one wave: a product at a
 // time in fp32, tokens (lanes) for the scores and head dimensions for the values.  In-flight tokens without
 // weight are left out.  Leaves the row's maximum (log2 units), its sum and elements lane + 64 e of O.
@@ -178,8 +181,43 @@ __device__ void attend_row(const AttnArgs& a, int b, int g, int row, const int* 
     }
 }
 
-constexpr int kGenWaves = 4;
-constexpr int kGenThreads = 64 * kGenWaves;
+// Rows `redo` of a pv_attn_rows workgroup (bits 0 .. 16 kRB) again, this wave's elements of them.  The arguments are
+// read from memory once more, so that nothing is kept in registers for this during the kernel.
+template <typename T, int D, int kRB>
+__device__ __forceinline__ void redo_rows(uint64_t redo, const float* ml, float* q_s) {
+    constexpr int kEV = D / 16;
+    const AttnArgs* ap = (const AttnArgs*)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+v"(ap));
+    const AttnArgs& a = *ap;
+    const int seq = reinterpret_cast<const BatchMeta*>(ap + 1)->seq[blockIdx.z], L = a.d_len[seq], lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int* pt = a.d_pt + (size_t)seq * a.max_pages;
+    const int split = blockIdx.x, g = blockIdx.y / a.n_chunks, b = blockIdx.z, row0 = 16 * kRB * (blockIdx.y % a.n_chunks);
+    const int n_cache = (L + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE, n_tiles = n_cache + (a.n_q + 15) / 16, cached = n_cache * MS_PAGE_SIZE;
+    const int lo = (int)((long)n_tiles * split / a.n_splits) * MS_PAGE_SIZE, hi = (int)((long)n_tiles * (split + 1) / a.n_splits) * MS_PAGE_SIZE;
+    for (; redo != 0; redo &= redo - 1) {
+        const int r = __builtin_ctzll(redo), row = row0 + r;
+        float mr, lr, acc[D / 64], m_row = -INFINITY, l_row = 0.f;
+        attend_row<T, D>(a, b, g, row, pt, min(lo, L), min(hi, L), max(lo - cached, 0), min(hi - cached, a.n_q), q_s, mr, lr, acc);
+        for (int x = 0; x < kGenWaves; ++x) {   // the row's maximum as the kernel stored it, and whether its sum is NaN
+            m_row = fmaxf(m_row, ml[(x * kRB * 16 + r) * 2]);
+            l_row += ml[(x * kRB * 16 + r) * 2 + 1];
+        }
+        const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
+        // a sum that is NaN is every wave's; else only columns are, and the partial goes by the maximum stored
+        // (if that is a number: a row may see nothing in a share)
+        const bool all = l_row != l_row;
+        const float f = a.n_splits == 1 ? 1.f / lr : all || m_row == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mr - m_row);
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) {
+            const int d = lane + 64 * e;
+            if ((d / kEV & 3) != w) continue;
+            if (a.n_splits == 1) ((T*)a.out)[orow * D + d] = from_float<T>(acc[e] * f);
+            else a.ws[(orow * a.n_splits + split) * D + d] = acc[e] * f;
+        }
+        if (a.n_splits > 1 && all && w == 0 && lane == 0)
+            *reinterpret_cast<float2*>(a.ws + (size_t)gridDim.z * a.n_q * a.n_q_heads * a.n_splits * D + (orow * a.n_splits + split) * 2) = make_float2(mr, lr);
+    }
+}
 
 // The general kernel: fp32 arithmetic throughout (both contractions on the fp32 matrix cores), any
 // supported dtype, head_dim and head grouping.  A workgroup of 4 waves takes one share of one
@@ -467,11 +505,10 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
     // a time; wave rr folds register rr, i.e. d = kEV (4 j + rr) .. + kEV of every row ----
     float* ml = reinterpret_cast<float*>(smem);                 // [wave][kRB * 16][2]
     float* ob = ml + kGenWaves * kRB * 16 * 2;                  // [wave][rr][lane][kEV]
-    int* redo = reinterpret_cast<int*>(ob + kGenWaves * 4 * kEV * 64);   // [kRB * 16] rows that came out NaN
-    bool nan_seen = false;
+    float* qr = ob + kGenWaves * 4 * kEV * 64;                  // [wave][D] a query row worked out again
+    uint64_t redo = 0;   // rows of which this wave's part came out NaN
     float mw[kRB][kGenWaves], m_all[kRB], l_all[kRB];
     __syncthreads();
-    if (tid < 16 * kRB) redo[tid] = 0;
 #pragma unroll
     for (int rb = 0; rb < kRB; ++rb) {
         l[rb] += __shfl_xor(l[rb], 16, 64);
@@ -519,10 +556,9 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
         float sum = l_all[rb];
 #pragma unroll
         for (int e4 = 0; e4 < kEV / 4; ++e4) sum += (acc[e4].x + acc[e4].y) + (acc[e4].z + acc[e4].w);
-        if (sum != sum && row < n_rows) {
-            redo[16 * rb + l16] = 1;
-            nan_seen = true;
-        }
+        uint64_t nan = __ballot(sum != sum && row < n_rows);   // (lanes 16 apart hold the same row)
+        nan |= nan >> 32;
+        redo |= ((nan | nan >> 16) & 0xffff) << 16 * rb;
         if (row < n_rows) {
             const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
             const int d = kEV * (4 * j + w);
@@ -545,24 +581,8 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
     }
     // Keys or values that are not finite: the matrix products multiply tokens a row does not see by a weight of
     // zero, and three-term operands infinities by terms of zero.  Both are NaN where the inputs may not call for
-    // it, so such rows are worked out again, a product at a time (nothing is live here: the registers of the
-    // kernel above are not affected).
-    if (!__syncthreads_or(nan_seen)) return;
-    for (int r = w; r < 16 * kRB; r += kGenWaves) {
-        if (!redo[r]) continue;
-        const int row = row0 + r, cached = n_cache * MS_PAGE_SIZE;
-        float mr, lr, acc[D / 64];
-        attend_row<T, D>(a, b, g, row, pt, min(t_lo * MS_PAGE_SIZE, L), min(t_hi * MS_PAGE_SIZE, L), max(t_lo * MS_PAGE_SIZE - cached, 0),
-                         min(t_hi * MS_PAGE_SIZE - cached, a.n_q), ob + w * D, mr, lr, acc);
-        const size_t orow = ((size_t)b * a.n_q + row / a.group) * a.n_q_heads + g * a.group + row % a.group;
-#pragma unroll
-        for (int e = 0; e < D / 64; ++e) {
-            if (a.n_splits == 1) ((T*)a.out)[orow * D + lane + 64 * e] = from_float<T>(acc[e] * (1.f / lr));
-            else a.ws[(orow * a.n_splits + split) * D + lane + 64 * e] = acc[e];
-        }
-        if (a.n_splits > 1 && lane == 0)
-            *reinterpret_cast<float2*>(a.ws + (size_t)gridDim.z * a.n_q * a.n_q_heads * a.n_splits * D + (orow * a.n_splits + split) * 2) = make_float2(mr, lr);
-    }
+    // it, so a wave works such rows out again, a product at a time, and stores its part of them.
+    if (redo != 0) redo_rows<T, D, kRB>(redo, ml, qr + w * D);
 }
 
 // out = sum_s 2^(m_s - m) acc_s / sum_s 2^(m_s - m) l_s: a thread per four elements of a row, every
@@ -616,7 +636,7 @@ static int rows_splits(int wgs, int max_len, int n_q) {
 
 template <typename T, int D, int kRB>
 static int launch_rows_built(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, hipStream_t stream) {
-    const int merge = (kGenWaves * kRB * 16 * 2 + kGenWaves * 4 * D / 16 * 64 + kRB * 16) * (int)sizeof(float), table = a.n_q * D / 2 * (int)sizeof(float2);
+    const int merge = (kGenWaves * kRB * 16 * 2 + kGenWaves * 4 * D / 16 * 64 + kGenWaves * D) * (int)sizeof(float), table = a.n_q * D / 2 * (int)sizeof(float2);
     hipLaunchKernelGGL((pv_attn_rows<T, D, kRB>), dim3(a.n_splits, a.n_kv_heads * a.n_chunks, B), dim3(kGenThreads), merge > table ? merge : table,
                        stream, a, bm);
     c->launches++;

@@ -127,6 +127,7 @@ NOT_FINITE = [
     ("bf16", 16, 4, 64, 5, 4, [700, 31]),
     ("bf16", 7, 1, 64, 20, 0, [100]),
     ("bf16", 66, 1, 128, 1, 2, [300]),
+    ("f32", 4, 4, 64, 64, 0, [16]),                        # two shares, in the second of which the first rows see nothing
 ]
 
 
