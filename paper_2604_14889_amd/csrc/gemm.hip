@@ -777,12 +777,17 @@ __device__ __forceinline__ MidUnit mid_unit(const MidUnits& t, int u, int steps)
     return r;
 }
 
+// Where the four ranges of a whole tile's K steps begin (steps a multiple of 32): about a quarter each, at
+// different distances from a multiple of 4 KB (32 steps) of a weight row.
+__device__ __forceinline__ int mid_range_begin(int steps, int i) { return i == 4 ? steps : i * (steps / 4 + (steps < 128 ? steps / 16 : 8)); }
+
 // kRowsA: rows of A kept in a stage (all of the tile's, or 8 or 16 of 32: the other operand rows then
 // repeat them and their products are not stored).
 template <int kMode, int kWM, int kMI, int kRowsA = 32 * kWM * kMI>
 __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUnits t) {
     constexpr int kWaves = 2 * kWM, kS = mid_stages(kRowsA), kStage = mid_stage_bytes(kRowsA);
     constexpr int kChunks = (kRowsA + kMidBN) / 8, kLoads = (kChunks + kWaves - 1) / kWaves;
+    constexpr bool kRanges = kMode != kGemmSwiglu && kMI == 1;   // (two row blocks per wave: not the registers for it)
     static_assert(kRowsA == 32 * kWM * kMI || (kWM * kMI == 1 && kRowsA < 32), "fewer rows than the tile's: one block of 32");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
@@ -801,12 +806,23 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     // the next step to ask for; it runs ahead of the one being multiplied, into the next unit too
     int iu = blockIdx.x, i_buf = 0, in_flight = 0;
     MidUnit ahead = mid_unit(t, iu, steps);
-    // Whole tiles are walked from different steps on, round and round: with K a power of two the rows of
-    // both operands lie a multiple of the L2 channels' interleave apart, and workgroups in step with each
-    // other would ask the same few channels (K = 4096, 7 rows: gate/up 48 -> 41 us, LM head of 128256 197 ->
-    // 166 us; K = 3584: no change).  K parts start apart by themselves.  Not for the greedy token: equal
-    // weight rows in different tiles have to give equal sums, so that the lowest column wins.
-    auto first_step = [&]() { return ahead.s_lo + (kMode != kGemmArgmax && ahead.whole ? (int)((uint32_t)steps * (blockIdx.x >> 3 & 31) >> 5) : 0); };
+    // With rows of both operands a multiple of 4 KB apart (steps a multiple of 32), workgroups in step with each
+    // other would ask the same few L2 channels: they start their units at different steps and wrap around.  The
+    // order of a column's additions must not depend on the tile it is in, so that equal weight rows give equal
+    // logits and the lowest column wins: plain whole tiles start at one of four places between which the sums are
+    // kept apart (mid_range_begin), long K parts at a place that goes by their number.  SwiGLU's outputs are not
+    // compared with each other: a sum per tile, 32 places.  us in step / spread: K = 4096, gate/up 7 rows 48 / 41,
+    // LM head of 128256 columns 9 rows 202 / 172, 64 rows 224 / 195; K = 2048, 65536 columns, 16 rows 59 / 52; 8192 x
+    // 8192 in 4 parts, 17 rows 35 / 31.  Other K gain nothing and would pay for the ranges (K = 3584, LM head, 1
+    // row 165 / 169; K = 5120, 32000 columns, 7 rows 53 / 55).
+    const bool spread = steps % 32 == 0;
+    const int place = blockIdx.x >> 3 & 31;
+    auto first_step = [&]() {
+        if (kMode == kGemmSwiglu && ahead.whole) return (int)((uint32_t)steps * place >> 5);
+        if (!spread) return ahead.s_lo;
+        if (!ahead.whole) return ahead.s_lo + (ahead.s_hi - ahead.s_lo >= 32 ? 8 * (ahead.part & 3) : 0);
+        return kRanges ? mid_range_begin(steps, place & 3) : 0;
+    };
     int i_step = first_step(), i_left = ahead.s_hi - ahead.s_lo;
     auto issue = [&]() {
         if (iu >= t.units) return;
@@ -849,35 +865,61 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
             for (int mi = 0; mi < kMI; ++mi)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[ni][mi][i] = 0.f;
-        for (int s = cur.s_lo; s < cur.s_hi; ++s) {
-            // the oldest of the steps in flight has to be here (stores of an earlier unit only make the wait longer)
-            wait_steps<kS - 2, kLoads>(in_flight - 1);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            --in_flight;
-            issue();   // into the stage that was multiplied before the barrier
-            const char* ab = a_op + buf * kStage;
-            const char* wb = w_op + buf * kStage;
-            buf = buf + 1 == kS ? 0 : buf + 1;
-            g_bf16x8_t wf[2][2], af[2][kMI];
-            auto fetch = [&](int kk, int set) {
-                const int at = ((2 * kk + hf) ^ swz) * 16, at_a = ((2 * kk + hf) ^ swz_a) * 16;
+        auto multiply = [&](int n) {
+            for (int s = 0; s < n; ++s) {
+                // the oldest of the steps in flight has to be here (stores of an earlier unit only make the wait longer)
+                wait_steps<kS - 2, kLoads>(in_flight - 1);
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                --in_flight;
+                issue();   // into the stage that was multiplied before the barrier
+                const char* ab = a_op + buf * kStage;
+                const char* wb = w_op + buf * kStage;
+                buf = buf + 1 == kS ? 0 : buf + 1;
+                g_bf16x8_t wf[2][2], af[2][kMI];
+                auto fetch = [&](int kk, int set) {
+                    const int at = ((2 * kk + hf) ^ swz) * 16, at_a = ((2 * kk + hf) ^ swz_a) * 16;
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) wf[set][ni] = *reinterpret_cast<const g_bf16x8_t*>(wb + ni * 32 * (kMidBK * 2) + at);
+                    for (int ni = 0; ni < 2; ++ni) wf[set][ni] = *reinterpret_cast<const g_bf16x8_t*>(wb + ni * 32 * (kMidBK * 2) + at);
 #pragma unroll
-                for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at_a);
-            };
-            fetch(0, 0);
+                    for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at_a);
+                };
+                fetch(0, 0);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                if (kk < 3) fetch(kk + 1, (kk + 1) & 1);   // the next operands are on their way while these are multiplied
-                __builtin_amdgcn_sched_barrier(0);
+                for (int kk = 0; kk < 4; ++kk) {
+                    if (kk < 3) fetch(kk + 1, (kk + 1) & 1);   // the next operands are on their way while these are multiplied
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
+                    for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
-                    for (int mi = 0; mi < kMI; ++mi)
-                        acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1][ni], af[kk & 1][mi], acc[ni][mi], 0, 0, 0);
+                        for (int mi = 0; mi < kMI; ++mi)
+                            acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1][ni], af[kk & 1][mi], acc[ni][mi], 0, 0, 0);
+                }
             }
+        };
+        if (!kRanges || !spread || !cur.whole) {
+            multiply(cur.s_hi - cur.s_lo);
+        } else {
+            g_f32x16_t range[4][2];   // sums of the four ranges of K, whichever came first
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) range[i][ni] = acc[ni][0];
+#pragma nounroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = (place + q) & 3;
+                multiply(mid_range_begin(steps, r + 1) - mid_range_begin(steps, r));
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (r == i) range[i][ni] = acc[ni][0];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[ni][0][i] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) acc[ni][0] = ((range[0][ni] + range[1][ni]) + range[2][ni]) + range[3][ni];
         }
         store_wave_tile<kMode, kMI>(g, acc, !cur.whole, cur.part, 32 * kMI * wm + l32, cur.n0 + 64 * wn, hf);
     }
@@ -1136,6 +1178,12 @@ static int gemm_allow_lds() {
 static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, size_t ws_bytes, hipStream_t stream,
                        const NormTail* norm = nullptr) {
     MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
+    // A plain product without split_k at up to 16 rows may be logits: every column's sum is taken the same way
+    // (whole tiles throughout), so that equal weight rows give equal logits.
+    if (!swiglu && split_k == 1 && g.M <= kSkinnyMaxRows && mid.bm) {
+        mid.units = {mid.units.tiles, mid.units.tiles, 1, mid.units.tiles};
+        mid.workspace_bytes = 0;
+    }
     // Up to 16 rows: gemm_rows_bf16 where its units fill three quarters of the chip and the workspace holds
     // their partials, the few-row kernel otherwise (narrow outputs without split_k, no workspace).  us per
     // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16: 7 rows gate/up 49 / 46, LM head 168 /
@@ -1397,10 +1445,8 @@ extern "C" int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int v
     const SkinnyPlan sk = skinny_plan(M, vocab, K);
     const MidPlan mid = mid_plan(M, vocab, K, 1);
     const int tiles = mid.units.tiles;
-    // Up to 16 rows by the rule of gemm_launch, except that rows of W a multiple of 2 KB apart (see the
-    // kernel's first_step) leave up to 8 rows to the few-row kernel: K = 3584 7 rows 172 -> 161 us, 14 rows 189 ->
-    // 165, K = 4096 7 rows 201 -> 198, 2 rows 187 -> 196.  (The 64-column groups take no more workspace.)
-    if (mid.bm && (sk.parts != 1 || (8 * tiles >= 3 * gemm_slots() && (M > 8 || K % 1024)))) {
+    // Up to 16 rows by the rule of gemm_launch.  (The 64-column groups take no more workspace.)
+    if (mid.bm && (sk.parts != 1 || 8 * tiles >= 3 * gemm_slots())) {
         groups = vocab / kGemmColGroup;
         g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
         g.tail_col0 = vocab;

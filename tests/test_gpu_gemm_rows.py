@@ -117,3 +117,26 @@ def test_wide_outputs_that_fill_the_chip_on_either_kernel(m):
         out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
         M.ms_gemm_bf16(a, w, None, [out], 1, ws)
         _close(out, ref)
+
+
+@pytest.mark.parametrize("m", [1, 7, 8, 9, 16, 17, 64, 128])
+def test_equal_weight_rows_give_equal_logits(m):
+    """Greedy decoding over logits takes the lowest of equal maxima: copies of a weight row have to give the same
+    bits in whatever column tile they are.  Above 16 rows the last, partly filled round of tiles is divided over K
+    when there is a workspace for it, so only the full rounds agree there."""
+    from paper_2604_14889_amd import binding as M
+    tiles = torch.cuda.get_device_properties(0).multi_processor_count
+    for n, k in ((128 * (tiles + 40), 1024), (128 * (2 * tiles + 7), 640)):
+        gen, a, w, _ = _inputs(m, 128, k, m + k)
+        w = w.repeat(n // 128, 1)                            # every column tile holds the same rows
+        need = M.ms_gemm_workspace_bytes(m, n, k, 1)
+        for ws in (torch.empty(max(need, 16), dtype=torch.uint8, device="cuda"), None):
+            out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+            M.ms_gemm_bf16(a, w, None, [out], 1, ws)
+            full = n if m <= 16 or ws is None else n // 128 // tiles * tiles * 128
+            same = out.view(torch.int16).view(m, n // 128, 128)[:, :full // 128]
+            assert torch.equal(same, same[:, :1].expand_as(same)), (m, n, k)
+            if full == n:
+                tok = torch.empty(m, dtype=torch.int32, device="cuda")
+                M.ms_argmax_rows(out, n, tok)
+                assert int(tok.max()) < 128
