@@ -461,7 +461,7 @@ def attention_workload(args, sh, steps, warmup, want_cpu, ragged):
         "decode_tokens_per_s": round(accepted / (t1 - t0), 1),
         "accepted_per_step_per_seq": round(accepted / steps / B, 3),
         "roofline": {
-            "kernel": "pv_attn_mfma_stream",
+            "kernel": M.ms_attention_last_kernel(ses.cache),
             "bound": "hbm",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS,
@@ -559,7 +559,7 @@ def wide_step_bench(args):
         "kernel_launches_per_call": launches,
         "call_us": round(call_ms * 1e3, 2),
         "matrix_core_tflops": round(per_call_flops / (call_ms * 1e-3) / 1e12, 1),
-        "roofline": {"kernel": "pv_attn_mfma_wide" if launches >= 1 and (nq > 16 or nq * (Hq // Hkv) > 64) else "pv_attn_mfma_stream",
+        "roofline": {"kernel": M.ms_attention_last_kernel(ses.cache),
                      "bound": "hbm", "achieved": round(per_call_bytes / (call_ms * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(per_call_bytes / (call_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None,
                      "avg_kernel_ms": round(call_ms, 5), "launches": len(kern_ms) * NL, "launches_per_event_pair": NL,
@@ -686,7 +686,7 @@ def compaction_bench(args):
             "pages_released_per_call": B * (seg // 16), "pages_taken_per_call": B * (-(-n_mem // 16)),
             "timing": "HIP events on the call's stream around one call (includes the launch latency); host = time inside the call",
         },
-        "roofline": {"kernel": "pv_attn_mfma_stream", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+        "roofline": {"kernel": M.ms_attention_last_kernel(ses.cache), "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None, "avg_kernel_ms": round(kern_avg_ms, 5),
                      "launches": len(kern_ms) * NL, "launches_per_event_pair": NL, "algorithmic_bytes_per_launch": per_launch_bytes},
         "cpu_baseline": None,
@@ -822,7 +822,8 @@ def decode_step_bench(args):
                     "SwiGLU, down projection with the residual add and the next norm), LM head, greedy tokens, accept, commit: every kernel is "
                     "this library's; random weights, so about one token per sequence is accepted per step; "
                     + ("accept lengths read back by the host before the commit" if host_commit else "commit on the device, no synchronisation in the step"),
-            "projections": "few-row matrix-core kernel" if B * nq <= 16 else "tiled matrix-core GEMM",
+            "projections": "row tiles (few-row kernel where they leave the chip idle)" if B * nq <= 16 else
+                           "row tiles (LM head above 128 rows on 256 x 256 tiles)" if B * nq <= 256 else "256 x 256 tiles",
         },
         "query_tokens_per_s": round(B * nq * args.steps / (t1 - t0), 1),
         "committed_per_step_per_seq": round(state["committed"] / args.steps / B, 3),
@@ -830,7 +831,7 @@ def decode_step_bench(args):
         "attention_share_of_step": round(attn_ms / ms_per_step, 4),
         "weight_bytes_streamed_per_step": int(n_params * 2),
         "roofline": {
-            "kernel": "pv_attn_mfma_stream", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+            "kernel": M.ms_attention_last_kernel(ses.cache), "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
             "avg_kernel_ms": round(kern_avg_ms, 5), "launches": len(kern_ms),
             "algorithmic_bytes_per_launch": per_launch_bytes,
@@ -912,7 +913,7 @@ def projections_bench(args):
         weights = copies(n, kk)
         us = timed(fn, weights)
         flops = 2.0 * rows * n * kk
-        row = {"projection": name, "rows": rows, "N": n, "K": kk, "call": what, "us": round(us, 1), "pflops": round(flops / us / 1e9, 3),
+        row = {"projection": name, "rows": rows, "N": n, "K": kk, "call": what, "kernel": M.ms_gemm_last_kernel(), "us": round(us, 1), "pflops": round(flops / us / 1e9, 3),
                "frac_of_2.5_pflops": round(flops / us / 1e9 / 2.5, 3), "weight_gbps": round(n * kk * 2 / us / 1e3, 1)}
         if args.library_reference:   # a reference, not on any path of the library: the bare product through torch.mm
             ref = torch.empty(rows, n, dtype=torch.bfloat16, device=dev)
@@ -929,7 +930,7 @@ def projections_bench(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": f"qwen2.5-7b_projections_rows{rows}", "note": "ms_per_step = 28 blocks' four projections + the LM head, stand-alone times added up"},
         "projections": table,
-        "roofline": {"kernel": "gemm_tn_bf16 (+ its reduction kernels)", "bound": "mfma", "achieved": round(flops_total / us_total / 1e6, 1),
+        "roofline": {"kernel": "+".join(sorted({r["kernel"] for r in table})) + " (and their reduction kernels)", "bound": "mfma", "achieved": round(flops_total / us_total / 1e6, 1),
                      "peak": 2500.0, "unit": "TFLOP/s", "frac": round(flops_total / us_total / 1e6 / 2500.0, 4), "traffic": None},
         "cpu_baseline": None,
     }

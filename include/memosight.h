@@ -367,6 +367,13 @@ int ms_profile_attention(ms_cache* cache, int capacity, int stride, int span);
  * recorded (complete ones only: a span still open is dropped).  Resets the count. */
 int ms_profile_read(ms_cache* cache, float* ms_out, int cap, int* n);
 
+/* Names of the kernel(s) the last ms_predict_verify_attention call on this cache launched, joined by
+ * "+" if there were two; "" before the first.  ms_gemm_last_kernel: the kernel of the calling
+ * thread's last projection (its reduction not named).  For reports and tests: which kernel takes a
+ * call is no part of the interface. */
+const char* ms_attention_last_kernel(ms_cache* cache);
+const char* ms_gemm_last_kernel(void);
+
 /* A plain streaming read of device memory at `src` (16-byte aligned) on `stream`: the first
  * `bytes` bytes rounded down to a multiple of 32 KiB (*bytes_read, if not NULL, receives that
  * count; less than 32 KiB launches nothing), MS_READ_PROBE_BLOCKS_PER_CU workgroups of 256 threads

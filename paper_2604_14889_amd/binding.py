@@ -88,6 +88,8 @@ _SIGS = {
     "ms_lm_head_argmax_workspace_bytes": (_SZ, [_I, _I, _I]),
     "ms_lm_head_argmax_bf16": (_I, [_P, _P, _I, _I, _I, _P, _P, _SZ, _P]),
     "ms_gemm_bf16": (_I, [_P, _P, _P, _I, _I, _I, _I, C.POINTER(_P), _IP, _I, _P, _SZ, _P]),
+    "ms_attention_last_kernel": (C.c_char_p, [_P]),
+    "ms_gemm_last_kernel": (C.c_char_p, []),
     "ms_profile_attention": (_I, [_P, _I, _I, _I]),
     "ms_profile_read": (_I, [_P, C.POINTER(C.c_float), _I, _IP]),
     "ms_hbm_read_probe": (_I, [_P, C.c_size_t, _I, _P, _P, C.POINTER(C.c_size_t)]),
@@ -444,6 +446,14 @@ def ms_peak_pages(cache) -> int:
     n = C.c_int(0)
     _check(lib.ms_peak_pages(cache, C.byref(n)))
     return n.value
+
+
+def ms_attention_last_kernel(cache) -> str:
+    return lib.ms_attention_last_kernel(cache).decode()
+
+
+def ms_gemm_last_kernel() -> str:
+    return lib.ms_gemm_last_kernel().decode()
 
 
 def ms_launch_count(cache) -> int:

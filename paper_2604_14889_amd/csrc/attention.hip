@@ -657,6 +657,7 @@ static int launch_general(ms_cache* c, AttnArgs& a, const BatchMeta& bm, int B, 
         if (per == 3) rc = launch_rows_built<T, D, 3>(c, a, bm, B, stream);
         else rc = launch_rows_built<T, D, 4>(c, a, bm, B, stream);
     }
+    c->last_attention = a.n_splits == 1 ? "pv_attn_rows" : "pv_attn_rows+pv_attn_combine";
     if (rc != MS_OK || a.n_splits == 1) return rc;
     const int rows = B * a.n_q * a.n_q_heads;
     const dim3 grid((unsigned)((rows + 1024 / D - 1) / (1024 / D)));
@@ -711,6 +712,8 @@ extern "C" int ms_attention_set_deterministic(ms_cache* c, int on) {
     c->deterministic = on != 0;
     return MS_OK;
 }
+
+extern "C" const char* ms_attention_last_kernel(ms_cache* c) { return c ? c->last_attention : ""; }
 
 extern "C" size_t ms_attention_workspace_bytes(ms_cache* c, int B, int n_q) {
     if (!c || B < 1 || B > MS_MAX_BATCH || n_q < 1 || n_q > MS_MAX_QUERIES) return 0;

@@ -1195,12 +1195,14 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
             auto kern = c->deterministic ? (big ? pv_attn_mfma_stream<false, true> : pv_attn_mfma_stream<false, false>)
                                          : (big ? pv_attn_mfma_stream<true, true> : pv_attn_mfma_stream<true, false>);
             c->launches++;
+            c->last_attention = "pv_attn_mfma_stream";
             hipLaunchKernelGGL(kern, grid, dim3(kThreads), Lds::kBytes, stream, a);
         } else {
             // wide steps: a launch takes eight chunks of 64 / group queries, one per wave (with more than
             // eight query heads per KV head a step of 64 queries has more chunks than that: further
             // launches, which run in order on the stream and share the workspace and the counters)
             const int per_launch = kWideChunks * (kRows / a.group);
+            c->last_attention = "pv_attn_mfma_wide";
             for (a.q0 = 0; a.q0 < a.n_q; a.q0 += per_launch) {
                 a.n_qc = a.n_q - a.q0 < per_launch ? a.n_q - a.q0 : per_launch;
                 c->launches++;

@@ -494,6 +494,7 @@ int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, in
     for (int b = 0; b < B; ++b) a.seq[b] = bm.seq[b];
     for (int b = B; b < MS_MAX_BATCH; ++b) a.seq[b] = 0;
     c->launches++;
+    c->last_attention = n_splits > 1 && !a.arrive ? "pv_attn_mfma_split+pv_attn_mfma_fold" : "pv_attn_mfma_split";
     hipLaunchKernelGGL(pv_attn_mfma_split, dim3(n_splits, a.n_kv_heads, B * a.n_chunks), dim3(kSplitThreads), split_lds_bytes(a.n_q), stream, a);
     if (n_splits > 1 && !a.arrive) {
         c->launches++;

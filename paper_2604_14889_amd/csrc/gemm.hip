@@ -925,6 +925,8 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     }
 }
 
+static thread_local const char* g_last_kernel = "";   // of the calling thread's last product
+
 static bool g_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Twice the compute units of the current device (the few-row kernel's workgroups per round; the
@@ -1096,6 +1098,7 @@ static int mid_launch_built(const GemmArgs& g, const MidUnits& units, hipStream_
     });
     if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
     const int slots = gemm_slots() / 2;   // the LDS stages take a whole compute unit
+    g_last_kernel = "gemm_rows_bf16";
     hipLaunchKernelGGL((gemm_rows_bf16<kMode, kWM, kMI, kRowsA>), dim3(units.units < slots ? units.units : slots), dim3(128 * kWM), lds, stream, g, units);
     return MS_OK;
 }
@@ -1125,6 +1128,7 @@ static int skinny_dispatch(const GemmArgs& g, const SkinnyPlan& v, hipStream_t s
         for (const void* f : builds) MS_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSkinnyLdsBytesWide));
         lds_allowed[dev] = true;
     }
+    g_last_kernel = "skinny_mfma_bf16";
     const dim3 grid((unsigned)(g.N / (4 / v.wk * 16 * v.nt)), (unsigned)v.parts);
     const dim3 block(kSkinnyThreads);
     if (swiglu) hipLaunchKernelGGL((skinny_mfma_bf16<4, 1, true>), grid, block, v.lds_bytes, stream, g, v.parts);
@@ -1171,6 +1175,7 @@ static int gemm_allow_lds() {
         result[dev] = e;
     });
     if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
+    g_last_kernel = "gemm_tn_bf16";
     return MS_OK;
 }
 
@@ -1295,6 +1300,8 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
 }
 
 }  // namespace ms
+
+extern "C" const char* ms_gemm_last_kernel(void) { return ms::g_last_kernel; }
 
 extern "C" size_t ms_gemm_workspace_bytes(int M, int N, int K, int split_k) {
     if (M < 1 || N < 1 || K < 1 || split_k < 1 || N % ms::kGemmNUnit || K % (ms::kGemmBK * split_k)) return 0;

@@ -101,6 +101,7 @@ struct ms_cache : ms::HostTables {
     int prof_open = 0;     // calls the open span still waits for
     int prof_seen = 0;
     long long launches = 0;   // kernels launched by calls on this cache so far
+    const char* last_attention = "";   // kernel(s) the last attention call ran
 };
 
 namespace ms {

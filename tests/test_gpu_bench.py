@@ -86,7 +86,7 @@ def test_compaction_bench_small():
 def test_wide_step_bench_small():
     r = run_bench("--workload", "wide_step", "--layers", "2", "--batch", "2", "--kv", "1000", "--queries", "41", "--steps", "2", "--warmup", "1")
     check_contract(r)
-    assert r["kernel_launches_per_call"] == 1.0 and r["roofline"]["kernel"] == "pv_attn_mfma_wide"
+    assert r["kernel_launches_per_call"] == 1.0 and r["roofline"]["kernel"] == "pv_attn_mfma_split"
 
 
 def test_decode_step_bench_small():
@@ -101,7 +101,7 @@ def test_decode_step_bench_small():
 def test_projections_bench_small():
     r = run_bench("--workload", "projections", "--rows", "63", "--steps", "2", "--warmup", "1")
     assert r["roofline"]["bound"] == "mfma" and r["roofline"]["peak"] == 2500.0 and len(r["projections"]) == 5
-    assert all(p["us"] > 0 for p in r["projections"]) and r["config"]["workload"] == "qwen2.5-7b_projections_rows63"
+    assert all(p["us"] > 0 and p["kernel"] == "gemm_rows_bf16" for p in r["projections"]) and r["config"]["workload"] == "qwen2.5-7b_projections_rows63"
 
 
 def test_more_than_one_gpu_is_refused():
