@@ -1179,6 +1179,20 @@ static int gemm_allow_lds() {
     return MS_OK;
 }
 
+// Plain products of at most 16 rows that the few-row kernel takes although gemm_rows_bf16 could.  With split_k:
+// all rows over the whole K in its LDS share are one launch without partials there, which is ahead up to 4 rows,
+// and above unless a last round of workgroups holds a few of them only.  us, few-row / row-tile, split_k 7 or 8:
+// 3584 x 3584 1 row 7.6 / 9.8, 7 rows 9.5 / 10.3; 4096 x 4096 1 row 8.5 / 11.4, 7 rows 10.4 / 11.8; 8192 x 8192
+// 1 row 29.8 / 33.4; 4608 x 3584 (288 workgroups) 1 row 10.7 / 11.4, 7 rows 12.2 / 11.7; 9216 x 3584 7 rows 18.9 /
+// 17.3.  Without: up to 8 rows over a short K, 65536 columns: K = 1024 1 row 24.3 / 25.4, 7 rows 23.2 / 24.9; K = 2048
+// 50.8 / 53.6, 51.2 / 51.8, 9 rows 52.0 / 51.5 (K = 3072, 152064 columns, 1 row 151 / 149).
+static bool few_rows_first(int M, int N, int K, int split_k) {
+    if (split_k == 1) return M <= 8 && K <= 2048;
+    if ((long)M * (K * 2 + 16) > kSkinnyLdsForA) return false;
+    const int cus = gemm_slots() / 2, left = N / 16 % cus;
+    return M <= 4 || left == 0 || left > cus / 4;
+}
+
 // Launches the tiles (and the reduction of the parts, if any).  g holds operands and destinations.
 static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, size_t ws_bytes, hipStream_t stream,
                        const NormTail* norm = nullptr) {
@@ -1195,7 +1209,8 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
     // 162, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.9 / 12.5 (252 units); 14 rows 52 / 47, 186 / 169, 38 /
     // 29, 14.6 / 13.0, 14.3 / 13.6.
     const bool mid_room = !mid.workspace_bytes || (workspace && ws_bytes >= mid.workspace_bytes && g_aligned16(workspace));
-    const bool mid_first = mid.bm && mid_room && !(norm && split_k == 1) && 8 * mid.units.units >= 3 * gemm_slots();
+    const bool mid_first = mid.bm && mid_room && !(norm && split_k == 1) && 8 * mid.units.units >= 3 * gemm_slots() &&
+                           (swiglu || norm || !few_rows_first(g.M, g.N, g.K, split_k));
     if (g.M <= kSkinnyMaxRows && mid_first) {
     } else if (swiglu) {   // few rows: four tiles per wave, the whole K in one part
         SkinnyPlan sk = skinny_plan(g.M, g.N, g.K);
@@ -1453,7 +1468,7 @@ extern "C" int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int v
     const MidPlan mid = mid_plan(M, vocab, K, 1);
     const int tiles = mid.units.tiles;
     // Up to 16 rows by the rule of gemm_launch.  (The 64-column groups take no more workspace.)
-    if (mid.bm && (sk.parts != 1 || 8 * tiles >= 3 * gemm_slots())) {
+    if (mid.bm && (sk.parts != 1 || (8 * tiles >= 3 * gemm_slots() && !few_rows_first(M, vocab, K, 1)))) {
         groups = vocab / kGemmColGroup;
         g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
         g.tail_col0 = vocab;

@@ -140,3 +140,27 @@ def test_equal_weight_rows_give_equal_logits(m):
                 tok = torch.empty(m, dtype=torch.int32, device="cuda")
                 M.ms_argmax_rows(out, n, tok)
                 assert int(tok.max()) < 128
+
+
+ROUTES = [
+    # M, N, K, split_k: plain products with one launch on the few-row kernel, or on the row tiles where that is ahead
+    (1, 3584, 3584, 8, "skinny_mfma_bf16"), (8, 3584, 3584, 8, "skinny_mfma_bf16"), (9, 3584, 3584, 8, "gemm_rows_bf16"),
+    (7, 4096, 4096, 8, "skinny_mfma_bf16"), (7, 6144, 4096, 4, "skinny_mfma_bf16"), (8, 4096, 4096, 8, "gemm_rows_bf16"),
+    (3, 8192, 8192, 8, "skinny_mfma_bf16"), (4, 8192, 8192, 8, "gemm_rows_bf16"),
+    (4, 4608, 3584, 7, "skinny_mfma_bf16"), (5, 4608, 3584, 7, "gemm_rows_bf16"),
+    (8, 65536, 1024, 1, "skinny_mfma_bf16"), (9, 65536, 1024, 1, "gemm_rows_bf16"), (8, 65536, 2048, 1, "skinny_mfma_bf16"),
+    (1, 65536, 3072, 1, "gemm_rows_bf16"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,split,kernel", ROUTES)
+def test_few_rows_run_on_the_kernel_that_is_ahead(m, n, k, split, kernel):
+    from paper_2604_14889_amd import binding as M
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule was measured on 256 compute units")
+    gen, a, w, ref = _inputs(m, n, k, m + n + k)
+    ws = torch.full((max(M.ms_gemm_workspace_bytes(m, n, k, split), 16),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
+    M.ms_gemm_bf16(a, w, None, [out], split, ws)
+    assert M.ms_gemm_last_kernel() == kernel
+    _close(out, ref)
