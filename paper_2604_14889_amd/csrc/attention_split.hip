@@ -436,7 +436,16 @@ static int split_chunks(int group, int n_q) { return (n_q + kRows / group - 1) /
 //   wide    64 queries: 1 x 100 16 / 35, 1 x 2000 19 / 140, 4 x 2000 35 / 109, 8 x 4000 87 / 114, 32 / 8
 //           heads 8 x 4000 91 / 97; 41 queries: 8 x 4000 68 / 100.  2.7 ns per (tile, KV head, chunk)
 //           there; the wide kernel reads the cache once and is ahead from about 32768 of them on
+// Shares are sized by the longest sequence, those of shorter ones end early, and nothing levels that: a
+// decode batch counts with the tiles it would have if all sequences were that long, a wide step (whose
+// throughput goes by the tiles there are) may have shares of up to 160 tiles.  us, this kernel / the other:
+//   decode  9 queries, 28 / 4 heads: 12000 + 15 x 100 tokens 75 / 30, 8 x 500 .. 8000 35 / 32, 16 x 500 ..
+//           4000 29 / 29, 4 x 1000 .. 16000 35 / 38, 8 x 200 .. 5000 26 / 29, 16 x 100 .. 1600 22 / 29; 32 / 8
+//           heads: 8000 + 7 x 64 55 / 28, 2000 + 7 x 64 24 / 39
+//   wide    one long sequence and 7 of 64 tokens, 64 queries: 5000 tokens (159 tiles) 105 / 134, 7000 (221)
+//           142 / 130, 9000 179 / 127; 32 / 8 heads, 41 queries: 5000 107 / 112, 6000 (190) 125 / 109
 constexpr long kSplitMaxTiles = 32768, kSplitMaxPairs = 64, kSplitMaxWideTiles = 32768;   // decode: over the root of the pairs
+constexpr long kSplitMaxWideShare = 160;
 int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, int* n_splits) {
     const long chunks = split_chunks(c->group, n_q), n_new = (n_q + kTile - 1) / kTile;
     long tiles = 0, longest = 0;
@@ -446,12 +455,10 @@ int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t
         longest = std::max(longest, t);
     }
     const long base = B * chunks * c->d.n_kv_heads;   // workgroups per share
-    const long work = tiles * c->d.n_kv_heads * chunks;
-    if (chunks == 1 && n_q <= kSplitDecodeQueries) {
-        if (base > kSplitMaxPairs || work > kSplitMaxTiles || work * work * base > kSplitMaxTiles * kSplitMaxTiles) return 0;
-    } else if (work > kSplitMaxWideTiles) {
-        return 0;
-    }
+    const bool wide = chunks > 1 || n_q > kSplitDecodeQueries;
+    const long work = (wide ? tiles : B * longest) * c->d.n_kv_heads * chunks;
+    if (!wide && (base > kSplitMaxPairs || work > kSplitMaxTiles || work * work * base > kSplitMaxTiles * kSplitMaxTiles)) return 0;
+    if (wide && work > kSplitMaxWideTiles) return 0;
     // one workgroup per compute unit; two where one would leave a quarter of the chip idle
     const long per = longest + n_new;
     long s = std::max(1L, c->n_cus / base);
@@ -460,6 +467,7 @@ int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t
     s = std::min(s, std::max(32L, per / 8));         // more partials than that cost the second launch what the first gains
     s = std::min(s, std::max(1L, (long)ws_partials / (B * chunks)));
     const long share = (per + s - 1) / s;
+    if (wide && share > kSplitMaxWideShare) return 0;
     *n_splits = (int)((per + share - 1) / share);
     return (int)share;
 }

@@ -158,3 +158,40 @@ def test_general_kernel_keeps_infinities_where_they_belong(dtype, hq, hkv, d, nv
     finite = np.isfinite(want)
     assert finite.sum() >= 0.3 * want.size and not finite.all()
     check_out(got, np.where(finite, want, np.nan), dtype, f"{where} {sh}"[:200])
+
+
+ROUTES = [
+    # Hq, Hkv, n_verify, n_foresight, lengths, kernel: one long sequence among short ones is levelled by the planned
+    # kernels only; with lengths not that far apart, or few tiles, the share-per-workgroup kernel is ahead
+    (28, 4, 5, 4, [12000] + 15 * [100], "pv_attn_mfma_stream"),
+    (28, 4, 5, 4, [500 + 1071 * i for i in range(8)], "pv_attn_mfma_stream"),
+    (32, 8, 5, 4, [8000] + 7 * [64], "pv_attn_mfma_stream"),
+    (28, 4, 5, 4, [100 + 100 * i for i in range(16)], "pv_attn_mfma_split"),
+    (28, 4, 4, 3, [16000, 100], "pv_attn_mfma_split"),
+    (28, 4, 4, 3, [4096], "pv_attn_mfma_split"),
+    (28, 4, 64, 0, [9000] + 7 * [64], "pv_attn_mfma_wide"),
+    (32, 8, 41, 0, [6000] + 7 * [64], "pv_attn_mfma_wide"),
+    (28, 4, 64, 0, [4000] + 7 * [64], "pv_attn_mfma_split"),
+    (28, 4, 64, 0, [2000], "pv_attn_mfma_split"),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,nv,nf,lengths,kernel", ROUTES)
+def test_skewed_batches_run_on_the_kernel_that_levels_them(hq, hkv, nv, nf, lengths, kernel):
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule was measured on 256 compute units")
+    M, S = _mods()
+    sh = W.AttnShape("skew", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
+    inp = W.attention_inputs(sh, 903, len(lengths))
+    ses, ora, ids = setup_pair(inp)
+    with ses:
+        pos = pids_for(inp, M)
+        got = run_gpu_attention(ses, inp, ids, pos)
+        assert M.ms_attention_last_kernel(ses.cache).split("+")[0] == kernel
+        from oracle import memosight_oracle as O
+        from tests.test_gpu_parity import as_f32
+        for b in (0, len(lengths) - 1):                        # the longest and a short one (or the other way round)
+            want = O.attention_rows(ora, 0, ids[b], as_f32(inp.q[b], "bf16"), as_f32(inp.k_new[b], "bf16"), as_f32(inp.v_new[b], "bf16"),
+                                    pos[b], O.default_ctx_new(nv, nf), rows=[(i, h) for i in (0, nv + nf - 1) for h in range(0, hq, 3)])
+            check_out(got[b], want, "bf16", f"sequence {b}")
