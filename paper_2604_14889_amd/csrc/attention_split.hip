@@ -12,8 +12,10 @@
 //   * A workgroup has four waves: wave w owns row block w % 2 (32 query rows, the rotated Q operand in
 //     registers) and every second tile of the share.  Only two waves hold states of the same rows, so
 //     the merge at the end moves 32 KB through LDS (eight waves with both row blocks each: 512 KB).
-//   * Up to 6 shares the workgroup that finishes last (they count themselves in; nobody waits) folds the
-//     others' partial results; more of them go to a second launch, where more workgroups read them.
+//   * The shares' partial results go to a second launch, where more workgroups read them: the share that
+//     finishes last folding them in the same launch was slower from 2 shares on (us inside / in a second
+//     launch: 1 x 64 tokens, 7 queries, 2 shares 12.0 / 10.2; 8 x 200 tokens, 9 queries 14.8 / 12.9; 2 x 2000
+//     tokens, 41 queries, 6 shares 22.3 / 20.6; 16 x 1000 tokens 20.6 / 20.1; never ahead).
 // Tile layout, rotation, rounding and softmax are the streaming kernel's (attention_mfma.hip).  Tiles
 // are assigned by index: results do not depend on timing.
 #include <algorithm>
@@ -26,10 +28,6 @@ namespace ms {
 
 constexpr int kSplitWaves = 4;
 constexpr int kSplitThreads = 64 * kSplitWaves;
-// Shares up to which the last one folds them.  us per call inside / in a second launch: 2 x 2000 tokens,
-// 41 queries (6 shares) 22.3 / 21.7 with a launch less for the host; 1 x 2000 tokens, 64 queries (8 shares)
-// 21.8 / 19.4, 8 x 1000 tokens, 7 queries (8 shares) 17.5 / 16.1.
-constexpr int kFoldInside = 6;
 
 struct SplitArgs {
     const uint16_t* pool_layer;
@@ -43,7 +41,6 @@ struct SplitArgs {
     const int* ctx_new;
     uint16_t* out;
     float* ws;              // partials [sequence][chunk][share][KV head] of kPartFloats
-    int* arrive;            // [sequence][chunk][KV head] shares finished, zero between calls; null: a second launch folds
     int n_q, n_verify, n_q_heads, n_kv_heads, group, max_pages;
     int n_chunks, per_chunk, n_splits, share_tiles;
     long page_elems;
@@ -275,10 +272,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
     const float f1 = __builtin_amdgcn_exp2f(m - mu), f2 = __builtin_amdgcn_exp2f(m2 - mu);   // a wave without tiles: 2^-inf = 0
     const float l_all = l * f1 + l2 * f2;
     const float norm = a.n_splits == 1 ? 1.f / l_all : 1.f;
-    const size_t part_at = ((size_t)((size_t)blockIdx.z * a.n_splits + split) * a.n_kv_heads + g) * kPartFloats;
-    float* part = a.ws + part_at;
-    const __amdgpu_buffer_rsrc_t rs = partials_descriptor(a.ws);
-    const uint32_t part_off = (uint32_t)(part_at * sizeof(float));   // (with counters: at most two partials per compute unit)
+    float* part = a.ws + ((size_t)((size_t)blockIdx.z * a.n_splits + split) * a.n_kv_heads + g) * kPartFloats;
     uint16_t* op = a.out + (((size_t)b * a.n_q + qi) * a.n_q_heads + g * a.group + (live ? row % a.group : 0)) * kD;
 #pragma unroll
     for (int d2 = 0; d2 < 2; ++d2)
@@ -290,9 +284,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
             const float4 got = *reinterpret_cast<const float4*>(other + ((d2 * 4 + i4) * 64 + lane) * 4);
             const float4 r = make_float4((own.x * f1 + got.x * f2) * norm, (own.y * f1 + got.y * f2) * norm, (own.z * f1 + got.z * f2) * norm,
                                          (own.w * f1 + got.w * f2) * norm);
-            if (a.n_splits > 1 && a.arrive) {
-                store_coherent4(rs, part_off + (2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4) * 4, r);
-            } else if (a.n_splits > 1) {
+            if (a.n_splits > 1) {
                 *reinterpret_cast<float4*>(part + 2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4) = r;
             } else if (live) {
                 uint2 pk;
@@ -301,70 +293,9 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
                 *reinterpret_cast<uint2*>(op + 32 * db + 8 * i4 + 4 * hf) = pk;
             }
         }
-    if (a.n_splits == 1) return;
-    if (ts == 0 && hf == 0) {
-        if (a.arrive) {
-            store_coherent(part + row, m_all);
-            store_coherent(part + kRows + row, l_all);
-        } else {
-            part[row] = m_all;
-            part[kRows + row] = l_all;
-        }
-    }
-    if (!a.arrive) return;
-    // ---- the share that finishes last folds all of them, in their order: the result does not depend on
-    // which one that is.  Every share's stores are complete before it counts itself in ----
-    stores_done();
-    __syncthreads();
-    int* flag = reinterpret_cast<int*>(smem);
-    if (tid == 0) {
-        int* ctr = a.arrive + (size_t)blockIdx.z * a.n_kv_heads + g;
-        const int ticket = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (ticket == a.n_splits - 1) __hip_atomic_store(ctr, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-        *reinterpret_cast<volatile int*>(flag) = ticket;
-    }
-    lds_barrier();
-    if (*reinterpret_cast<volatile int*>(flag) != a.n_splits - 1) return;
-    asm volatile("" ::: "memory");   // the partials are read after the count, also in the compiler's order
-    const size_t p0 = ((size_t)blockIdx.z * a.n_splits * a.n_kv_heads + g) * kPartFloats, stride = (size_t)a.n_kv_heads * kPartFloats;
-    float f[kFoldInside], mf = -INFINITY, lf = 0.f;
-#pragma unroll
-    for (int s = 0; s < kFoldInside; ++s) {   // past the end: the last one again, without weight
-        f[s] = load_coherent(a.ws + p0 + min(s, a.n_splits - 1) * stride + row);
-        mf = fmaxf(mf, f[s]);
-    }
-    const float muf = mf == -INFINITY ? 0.f : mf;
-#pragma unroll
-    for (int s = 0; s < kFoldInside; ++s) {
-        f[s] = s < a.n_splits ? __builtin_amdgcn_exp2f(f[s] - muf) : 0.f;
-        lf += f[s] * load_coherent(a.ws + p0 + min(s, a.n_splits - 1) * stride + kRows + row);
-    }
-    const float inv = 1.f / lf;
-#pragma unroll
-    for (int d2 = 0; d2 < 2; ++d2) {
-        const int db = 2 * ts + d2;
-        float4 px[kFoldInside][4];
-#pragma unroll
-        for (int s = 0; s < kFoldInside; ++s)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4)
-                px[s][i4] = load_coherent4(rs, (uint32_t)((p0 + min(s, a.n_splits - 1) * stride + 2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4) * 4));
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-            float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int s = 0; s < kFoldInside; ++s) {
-                if (s >= a.n_splits) continue;
-                r.x += px[s][i4].x * f[s];
-                r.y += px[s][i4].y * f[s];
-                r.z += px[s][i4].z * f[s];
-                r.w += px[s][i4].w * f[s];
-            }
-            uint2 pk;
-            pk.x = pack_bf16x2(r.x * inv, r.y * inv);
-            pk.y = pack_bf16x2(r.z * inv, r.w * inv);
-            if (live) *reinterpret_cast<uint2*>(op + 32 * db + 8 * i4 + 4 * hf) = pk;
-        }
+    if (a.n_splits > 1 && ts == 0 && hf == 0) {
+        part[row] = m_all;
+        part[kRows + row] = l_all;
     }
 }
 
@@ -494,17 +425,15 @@ int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, in
     a.per_chunk = kRows / ga.group;
     a.n_chunks = split_chunks(ga.group, ga.n_q);
     a.n_splits = n_splits;
-    // the counters are the streaming kernel's, two per (sequence, KV head)
-    a.arrive = n_splits <= kFoldInside && B * split_chunks(ga.group, ga.n_q) <= 2 * MS_MAX_BATCH ? c->d_arrive : nullptr;
     a.share_tiles = share_tiles;
     a.page_elems = ga.page_elems;
     a.scale_log2 = ga.scale * 1.44269504088896340736f;
     for (int b = 0; b < B; ++b) a.seq[b] = bm.seq[b];
     for (int b = B; b < MS_MAX_BATCH; ++b) a.seq[b] = 0;
     c->launches++;
-    c->last_attention = n_splits > 1 && !a.arrive ? "pv_attn_mfma_split+pv_attn_mfma_fold" : "pv_attn_mfma_split";
+    c->last_attention = n_splits > 1 ? "pv_attn_mfma_split+pv_attn_mfma_fold" : "pv_attn_mfma_split";
     hipLaunchKernelGGL(pv_attn_mfma_split, dim3(n_splits, a.n_kv_heads, B * a.n_chunks), dim3(kSplitThreads), split_lds_bytes(a.n_q), stream, a);
-    if (n_splits > 1 && !a.arrive) {
+    if (n_splits > 1) {
         c->launches++;
         const dim3 grid(8, a.n_kv_heads, B * a.n_chunks);
         if (n_splits <= 8) hipLaunchKernelGGL(pv_attn_mfma_fold<8>, grid, dim3(256), 0, stream, a);

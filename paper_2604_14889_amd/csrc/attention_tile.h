@@ -59,36 +59,6 @@ __device__ __forceinline__ uint4 load_stream(const char* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
-// Partials travel between workgroups on different XCDs, whose L2 caches are not coherent with each
-// other.  They are written and read with device-scope relaxed atomic accesses (write-through /
-// cache-bypassing), which needs no cache write-back or invalidation; ordering comes from waiting
-// for the stores (stores_done, then the workgroup barrier) before the arrival count is bumped.
-__device__ __forceinline__ void store_coherent(float* p, float v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_coherent(const float* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Waits until this thread's stores have been performed.  A workgroup barrier alone does not: its
-// release is of workgroup scope, for which the compiler leaves stores to device memory outstanding.
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// 16-byte accesses with the same cache policy (the bit device-scope atomics carry: the other XCDs'
-// L2s are bypassed), through a buffer descriptor over the partials: one instruction per float4
-// instead of two 8-byte atomics.  byte_off < 2 GiB.
-typedef uint32_t pv_u32x4_t __attribute__((ext_vector_type(4)));
-constexpr int kCoherentPolicy = 16;   // sc1
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t partials_descriptor(float* ws) {
-    return __builtin_amdgcn_make_buffer_rsrc(ws, 0, 0x7fffffff, 0x00020000);
-}
-__device__ __forceinline__ float4 load_coherent4(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off) {
-    const pv_u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, kCoherentPolicy);
-    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-}
-__device__ __forceinline__ void store_coherent4(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, float4 f) {
-    pv_u32x4_t v = {__float_as_uint(f.x), __float_as_uint(f.y), __float_as_uint(f.z), __float_as_uint(f.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)byte_off, 0, kCoherentPolicy);
-}
-
 // Read-only, wave-uniform control data (the work plan, position ids) is read through the constant
 // address space: scalar loads, which return out of order with respect to the vector loads and so do
 // not queue behind the tile loads in flight.

@@ -8,7 +8,13 @@ from tests.test_kernel_resources import compiled_kernels
 
 def test_partial_stores_are_waited_for_before_they_are_counted():
     assert waited_counts("attention_mfma.hip") >= 5      # four decode builds and the wide kernel
-    assert waited_counts("attention_split.hip") >= 1
+
+
+def test_kernels_that_hand_partials_to_a_second_launch_keep_no_counters():
+    """Counters outlive a call: one left in a bad state by another kernel's time-out would leave rows unwritten."""
+    text, kernels = compiled_kernels("attention_split.hip")
+    assert sum("pv_attn_mfma" in name for name in kernels) == 4
+    assert "atomic" not in "\n".join(ln.split(";")[0] for ln in text.split("\n"))
 
 
 def waited_counts(source):
