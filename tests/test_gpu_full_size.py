@@ -125,7 +125,7 @@ def test_config4_full_shape_compaction_then_attention_at_layers_0_13_27():
 
 
 @pytest.mark.parametrize("dtype,hq,hkv,d,nv,nf,lengths,scale", [
-    ("bf16", 28, 4, 128, 5, 4, [3000, 70, 0, 517], 0.2),        # streaming kernel; default would be 0.088
+    ("bf16", 28, 4, 128, 5, 4, [3000, 70, 0, 517], 0.2),        # default would be 0.088
     ("bf16", 28, 4, 128, 41, 0, [700], 0.03),                   # wide step
     ("f32", 8, 8, 64, 4, 3, [80, 333], 0.31),                   # general kernel; default would be 0.125
     ("bf16", 8, 2, 64, 2, 5, [77, 500], 1.0),

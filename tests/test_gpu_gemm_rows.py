@@ -1,6 +1,7 @@
-"""The projections at 17 to 256 rows (one row tile, K in steps of 64, loads straight into LDS): edges of
-the row blocks, K ranges shorter than the pipeline, uneven K parts, the divided last round.  Against the
-fp64 product; one bf16 rounding (2^-8 with a safety factor) plus the fp32 accumulation error."""
+"""The row-tile projections (up to 256 rows in one tile, K in steps of 64, loads straight into LDS): edges of
+the row blocks, K ranges shorter than the pipeline, uneven K parts, the divided last round, sums that do not
+depend on the tile, and which kernel a few rows run on.  Against the fp64 product; one bf16 rounding (2^-8 with
+a safety factor) plus the fp32 accumulation error."""
 import numpy as np
 import pytest
 import torch

@@ -163,8 +163,8 @@ BOUNDARY_LENGTHS = [0, 1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 511, 512, 513, 
 @pytest.mark.parametrize("case", range(16))
 def test_attention_random_batches_of_boundary_lengths(case):
     """Seeded random batches whose lengths sit on page (16), tile (32) and round (256) boundaries,
-    with random head groupings and step shapes: exercises the share planner (empty sequences,
-    segments that end exactly on a tile, shares crossing several sequences) on the streaming kernel."""
+    with random head groupings and step shapes: empty sequences, shares that end exactly on a tile
+    (test_gpu_planned_kernels.py runs the same on the kernels with a work plan)."""
     M, S = _mods()
     rng = W.make_rng(450, case)
     hq, hkv = [(28, 4), (32, 8), (8, 8), (16, 2), (64, 1)][case % 5]
@@ -264,8 +264,8 @@ def test_gpu_foresight_rows_independent_and_page_permutation_invariant():
 
 
 def test_layer_pool_above_4_gib():
-    """A 4.6 GB layer pool (140 000 pages): byte offsets of pages no longer fit 32 bits, the
-    streaming kernel's build with 64-bit page bases runs.  The same logical content is placed once
+    """A 4.6 GB layer pool (140 000 pages): byte offsets of pages no longer fit 32 bits (test_gpu_planned_kernels.py:
+    the streaming kernel's builds with 64-bit page bases).  The same logical content is placed once
     in a small pool and once on pages spread over the large one (some beyond the 4 GiB mark); with
     the fixed tile assignment both must give the same bits, and match the oracle."""
     M, S = _mods()
@@ -296,10 +296,9 @@ def test_layer_pool_above_4_gib():
 
 
 def test_repeated_launches_agree_with_many_partials_per_pair():
-    """Race check for the closing of (sequence, KV head) pairs: long sequences in a small batch are
-    cut into many shares (up to ~25 partials per pair here), and whichever share finishes last folds
-    the others.  Thirty launches in a row must give the same bits with the fixed tile assignment and
-    stay within rounding of them with the default one."""
+    """Long sequences in a small batch are cut into many shares (test_gpu_planned_kernels.py runs the same on the
+    streaming kernel, where whichever share of up to ~25 finishes last folds the others).  Thirty launches in a
+    row must give the same bits with the fixed tile assignment and stay within rounding of them with the default one."""
     M, S = _mods()
     sh = W.AttnShape("rep", "bf16", 5, 28, 4, 128, 5, 4, [9000, 100, 4000, 33, 7000], 0.5, 1000000.0, n_layers=2)
     inp = W.attention_inputs(sh, 403)
@@ -643,7 +642,7 @@ def test_device_side_commit_keeps_pace_with_host_commit_and_oracle():
 
 
 def test_wide_step_after_device_side_commits():
-    """A pass of 41 causal queries (the memory-token pass) right after device-side commits: the wide kernel goes by
+    """A pass of 41 causal queries (the memory-token pass) right after device-side commits: the kernel goes by
     the device's lengths and looks up the pages the commits added, while the host still holds the old tables."""
     M, S = _mods()
     rng = W.make_rng(418)
@@ -667,7 +666,7 @@ def test_wide_step_after_device_side_commits():
         pos_d = torch.empty(B, nq, dtype=torch.int32, device="cuda")
         wide_q = 41
         for step, acc in enumerate([[4, 4, 4, 4, 4], [4, 1, 4, 0, 3], [4, 4, 4, 4, 4], [2, 4, 4, 4, 4]]):
-            # a wide pass first: it sees what the commits so far have left (the plan is the one cut before them)
+            # a wide pass first: it sees what the commits so far have left (shares are the ones cut before them)
             qw = W.normal_bf16_bits(rng, (B, wide_q, Hq, D))
             kw, vw = W.normal_bf16_bits(rng, (B, wide_q, Hkv, D)), W.normal_bf16_bits(rng, (B, wide_q, Hkv, D))
             pw = np.stack([np.arange(f, f + wide_q) for f in first]).astype(np.int32)
