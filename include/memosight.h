@@ -223,8 +223,9 @@ int ms_predict_verify_attention_static(ms_cache* cache, int layer, int B, const 
                                        const int* ctx_new, float scale, void* out, void* stream);
 
 /* By default attention results are reproducible to rounding only: the streaming kernel (bf16,
- * head_dim 128, decode steps of more than a few short sequences) lets the waves of a workgroup take KV tiles first come, first served, so the
- * order in which a row's partial sums are added varies from call to call.  on != 0 fixes the
+ * head_dim 128, decode steps of more than a few short sequences) lets the waves of a workgroup take
+ * KV tiles first come, first served, so the order in which a row's partial sums are added varies
+ * from call to call.  on != 0 fixes the
  * assignment instead: calls with the same inputs, cache contents and page tables then return the
  * same bits, a few percent slower.  The other kernels are always reproducible. */
 int ms_attention_set_deterministic(ms_cache* cache, int on);
@@ -307,12 +308,14 @@ int ms_argmax_rows(const void* logits, int n, int vocab, long ld, int* out, void
  * aligned workspace.  With split_k == 1 that function returns what the call can use to split the
  * tiles of a partly filled last round over K (0 if the shape has none on the current device);
  * without that much workspace the call computes whole tiles throughout, with the same result up to
- * the order of the fp32 additions.  Up to 256 rows with K % 64 == 0
- * all rows go through one tile on workgroups that stream W through LDS.  With M <= 16 and K % 128 == 0
- * (the step of one or two sequences) a shape whose columns and K parts do not fill the chip that way
- * (or whose workspace does not hold the split_k parts) runs on a kernel that streams 16 weight rows
- * per wave through the matrix cores with all rows of A as the other operand; that one divides K by
- * what fits its LDS share (ms_gemm_workspace_bytes covers the partial sums) and ignores split_k. */
+ * the order of the fp32 additions.  Up to 16 rows and without split_k every column is summed the
+ * same way: equal rows of W give equal columns.  Up to 256 rows with K % 64 == 0 all rows go through
+ * one tile on workgroups that stream W through LDS, except outputs of 65536 columns and more above
+ * 128 rows without split_k, which take the 256 x 256 tiles of larger steps.  With M <= 16 and
+ * K % 128 == 0 (the step of one or two sequences) a shape that fills the chip better that way, or
+ * whose workspace does not hold the split_k parts, runs on a kernel that streams 16 weight rows per
+ * wave through the matrix cores with all rows of A as the other operand; that one divides K by what
+ * fits its LDS share (ms_gemm_workspace_bytes covers the partial sums) and ignores split_k. */
 size_t ms_gemm_workspace_bytes(int M, int N, int K, int split_k);
 int ms_gemm_bf16(const void* a, const void* w, const void* bias, int M, int N, int K, int n_out,
                  void* const* out, const int* out_col, int split_k, void* workspace, size_t ws_bytes,
@@ -323,8 +326,8 @@ int ms_gemm_bf16(const void* a, const void* w, const void* bias, int M, int N, i
  * [2 * inter][K] weight with the rows of both projections interleaved in blocks of 32: rows
  * 64 b .. 64 b + 32 are gate rows 32 b .. 32 b + 32, rows 64 b + 32 .. 64 b + 64 the up rows of the
  * same outputs.  inter % 64 == 0, K % 32 == 0; workspace as for ms_gemm_bf16 with N = 2 * inter and
- * split_k = 1 (optional).  Without it, or for narrow MLPs, M <= 16 with inter % 128 == 0 and K % 128 == 0 runs on the few-row
- * kernel of ms_gemm_bf16 when all rows of A over the whole K fit its LDS share (at K = 3584: up to
+ * split_k = 1 (optional).  Without it, or for narrow MLPs, M <= 16 with inter % 128 == 0 and
+ * K % 128 == 0 runs on the few-row kernel of ms_gemm_bf16 when all rows of A over the whole K fit its LDS share (at K = 3584: up to
  * 8 rows, and up to 16 rows for 2 * inter >= 32768, where a workgroup takes a whole compute unit). */
 int ms_gemm_swiglu_bf16(const void* a, const void* w_gate_up, int M, int inter, int K, void* out,
                         void* workspace, size_t ws_bytes, void* stream);

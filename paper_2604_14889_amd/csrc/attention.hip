@@ -219,8 +219,8 @@ __device__ __forceinline__ void redo_rows(uint64_t redo, const float* ml, float*
     }
 }
 
-// The general kernel: fp32 arithmetic throughout (both contractions on the fp32 matrix cores), any
-// supported dtype, head_dim and head grouping.  A workgroup of 4 waves takes one share of one
+// The general kernel: fp32 arithmetic throughout, any supported dtype, head_dim and head grouping (the
+// contractions run on the fp32 matrix cores, or for bf16 caches as exact sums of bf16 products).  A workgroup of 4 waves takes one share of one
 // (sequence, KV head)'s tokens and 16 kRB of its query rows (rows = queries x grouped heads); the
 // tokens are the cached ones in 16-token tiles (a tile is a page) followed by the in-flight ones,
 // and wave w takes tiles w, w + 4, ... of the share.

@@ -36,8 +36,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 
 // sin and cos of an fp32 angle of any size (RoPE angles reach 1e5 rad): the reduction by pi/2 is
-// done in fp64 (two-term constant), the kernels on [-pi/4, pi/4] are the classic single-precision
-// minimax polynomials.  About 1e-7 absolute error, far below the bf16 rounding of the rotated rows,
+// done in fp64 (two-term constant), the kernels on [-pi/4, pi/4] are the single-precision minimax
+// polynomials published in the Cephes mathematical library (S. Moshier, sinf / cosf).  About 1e-7 absolute error, far below the bf16 rounding of the rotated rows,
 // and much cheaper than the library routine's large-argument path.
 __device__ __forceinline__ void sincos_reduced(float x, float* sn, float* cs) {
     const double xd = (double)x;

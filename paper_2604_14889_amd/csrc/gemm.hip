@@ -29,7 +29,8 @@
 // Steps of up to 256 rows are bound by bringing W to the compute units and run on a second kernel,
 // further down (gemm_rows_bf16), that computes row tiles of the step's own height.  A third kernel, for
 // at most 16 rows, streams 16 weight rows per wave through the matrix cores; it keeps the products that
-// give the second one too few workgroups (narrow outputs without a K split or a workspace).
+// give the second one too few workgroups (narrow outputs without a K split or a workspace) or that it
+// finishes in one launch instead of two.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -704,7 +705,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // these sizes (37888 columns: 148 workgroups) and keep too few weights in flight.
 //   * Tile 32 kWM kMI (M) x 128 (N), K in steps of 64 through as many LDS stages as the compute unit
 //     holds.  Both tiles are loaded straight into LDS (global_load_lds_dwordx4: no registers, no LDS
-//     store instructions), up to five steps ahead; one barrier per step.  A workgroup of 2 kWM waves; a
+//     store instructions), a stage less than that ahead (up to 32 rows seven steps); one barrier per step.  A workgroup of 2 kWM waves; a
 //     wave owns 32 kMI rows x 64 columns (v_mfma_f32_32x32x16_bf16, W as the A operand), so a gate/up
 //     pair of the interleaved weight meets in one lane.
 //   * One workgroup per compute unit walks its units of work (whole column tiles, then K parts of the
@@ -1028,7 +1029,7 @@ static SkinnyPlan skinny_plan(int M, int N, int K, int min_parts = 1) {
     return p;
 }
 
-// 17 to 256 rows: the launch shape of gemm_rows_bf16 (bm 0: the shape runs on another kernel).
+// Up to 256 rows: the launch shape of gemm_rows_bf16 (bm 0: the shape runs on another kernel).
 struct MidPlan {
     int bm;
     MidUnits units;
@@ -1043,10 +1044,12 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     const int tiles = N / kMidBN;
     p.units = {tiles, tiles, 1, tiles};
     const int slots = gemm_slots() / 2, steps = K / kMidBK;
-    // Wide outputs that fill the chip with 256 x 256 tiles too: above 128 rows those bring in fewer bytes per
-    // column.  us here / there, 152064 columns: 128 rows 243 / 285, 160 rows 324 / 307, 192 rows 315 / 319, 208 rows
-    // 337 / 327, 224 rows 340 / 338, 256 rows 348 / 358; 128256 columns, K = 4096: 160 rows 301 / 297, 192 rows
-    // 294 / 307, 208 rows 325 / 314, 256 rows 327 / 329.
+    // Wide outputs that fill the chip with 256 x 256 tiles too stay there above 128 rows.  Which is ahead goes by K
+    // more than by the rows, and that is the side without large losses.  us here / there, 144, 192, 224, 256 rows:
+    // K = 3584, 152064 columns 294 / 296, 301 / 311, 329 / 328, 338 / 347; K = 4096, 128256 columns 277 / 277, 289 /
+    // 290, 316 / 306, 321 / 322; K = 5120, 73728 columns 199 / 211, 207 / 231, 230 / 241, 232 / 241; K = 8192,
+    // 65536 columns 276 / 253, 282 / 266, 309 / 280, 318 / 303; SwiGLU, K = 3584, 65536 columns 124 / 122, 124 / 123,
+    // 135 / 129, 139 / 135.  128 rows, K = 3584: 248 / 282.
     if (split_k == 1 && M > 128 && tiles >= 2 * slots) {
         p.bm = 0;
         return p;

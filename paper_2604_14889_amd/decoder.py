@@ -5,7 +5,8 @@ greedy-token kernels, acceptance, the cache update, and the dense projections (m
 fused forms: one launch fills the three Q/K/V tensors, the gate/up projection applies SwiGLU in its
 epilogue, the down projection's partial sums are added up by the kernel that also adds the
 residual and applies the next norm, the LM head can leave the greedy token instead of the logits).
-Up to 256 rows the projections run on the library's row-tile kernel, above on its 256 x 256 tiles.
+Up to 256 rows the projections run on the library's row-tile kernel (the LM head up to 128, plain products
+of a few rows on the few-row kernel where that is ahead), above on its 256 x 256 tiles.
 
 Nothing here computes on the CPU or in a library GEMM; every call fails if the HIP library is
 missing, and shapes the kernels do not take are refused when the Decoder is built.
