@@ -1208,8 +1208,8 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
     }
     // Up to 16 rows: gemm_rows_bf16 where its units fill three quarters of the chip and the workspace holds
     // their partials, the few-row kernel otherwise (narrow outputs without split_k, no workspace).  us per
-    // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16: 7 rows gate/up 49 / 46, LM head 168 /
-    // 162, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.9 / 12.5 (252 units); 14 rows 52 / 47, 186 / 169, 38 /
+    // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16: 7 rows gate/up 49 / 46, LM head 171 /
+    // 166, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.4 / 11.8 (252 units); 14 rows 52 / 47, 190 / 170, 38 /
     // 29, 14.6 / 13.0, 14.3 / 13.6.
     const bool mid_room = !mid.workspace_bytes || (workspace && ws_bytes >= mid.workspace_bytes && g_aligned16(workspace));
     const bool mid_first = mid.bm && mid_room && !(norm && split_k == 1) && 8 * mid.units.units >= 3 * gemm_slots() &&
