@@ -239,8 +239,8 @@ int ms_attention_set_deterministic(ms_cache* cache, int on);
  * puts the counters back to zero.  This call forces that condition from the host: poll_limit > 0
  * replaces the bound (0 restores the default, about a second), and every pair's "published"
  * counter is set to published_bias (0 = the healthy state) behind the work already queued on
- * `stream`.  Until a call with two zeros, calls that a kernel without such counters would take run
- * the streaming kernel too. */
+ * `stream`.  Until a call with two zeros, calls that the kernel without such counters would take run
+ * the streaming kernel (wide steps: the wide one) too. */
 int ms_attention_fault_injection(ms_cache* cache, int poll_limit, int published_bias, void* stream);
 
 /* ---- greedy longest-prefix acceptance (footnote of Section 2.1.1) -------------------------- */

@@ -220,10 +220,10 @@ __device__ __forceinline__ void redo_rows(uint64_t redo, const float* ml, float*
 }
 
 // The general kernel: fp32 arithmetic throughout, any supported dtype, head_dim and head grouping (the
-// contractions run on the fp32 matrix cores, or for bf16 caches as exact sums of bf16 products).  A workgroup of 4 waves takes one share of one
-// (sequence, KV head)'s tokens and 16 kRB of its query rows (rows = queries x grouped heads); the
-// tokens are the cached ones in 16-token tiles (a tile is a page) followed by the in-flight ones,
-// and wave w takes tiles w, w + 4, ... of the share.
+// contractions run on the fp32 matrix cores, or for bf16 caches as exact sums of bf16 products).  A
+// workgroup of 4 waves takes one share of one (sequence, KV head)'s tokens and 16 kRB of its query rows
+// (rows = queries x grouped heads); the tokens are the cached ones in 16-token tiles (a tile is a page)
+// followed by the in-flight ones, and wave w takes tiles w, w + 4, ... of the share.
 //
 // fp32 caches: v_mfma_f32_16x16x4_f32 twice: S^T = K . Q^T (A rows = tokens, B columns = query rows), then O^T =
 // V^T . P^T.  The contraction index of the first is the head dimension in any order, so a lane reads

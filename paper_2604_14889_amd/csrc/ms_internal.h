@@ -90,7 +90,7 @@ struct ms_cache : ms::HostTables {
     int* h_error = nullptr;      // pinned host word the streaming kernel sets when a closing workgroup times out
     int* d_error = nullptr;      // the same word as the device sees it
     int poll_limit = 0;          // polls before a closing workgroup gives up; 0 = the default (about a second)
-    bool stream_only = false;    // the fault injection is on: eligible calls run the streaming kernel, whose failure path it tests
+    bool stream_only = false;    // the fault injection is on: eligible calls run the streaming or the wide kernel, whose failure path it tests
     std::vector<int> plan_key;   // batch (ids, lengths) the plan was built for
     int plan_items = 0, plan_parts = 0, plan_B = 0;
     std::vector<hipEvent_t> prof_start, prof_stop;  // event pairs around the streaming kernel
