@@ -721,7 +721,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // (activations come from L2 but return in order behind the weights), so the weights' share
 // 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
 // kernel, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
-// 91 -> 67, 224 rows 101 -> 94; LM head 216 -> 170 (6.4 TB/s), 238 -> 195, 285 -> 243; down 36 ->
+// 91 -> 67, 224 rows 101 -> 94; LM head 220 -> 172 (6.3 TB/s), 238 -> 197, 283 -> 254; down 36 ->
 // 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMidMaxRows = 256;
@@ -814,8 +814,9 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     // kept apart (mid_range_begin), long K parts at a place that goes by their number.  SwiGLU's outputs are not
     // compared with each other: a sum per tile, 32 places.  us in step / spread: K = 4096, gate/up 7 rows 48 / 41,
     // LM head of 128256 columns 9 rows 202 / 172, 64 rows 224 / 195; K = 2048, 65536 columns, 16 rows 59 / 52; 8192 x
-    // 8192 in 4 parts, 17 rows 35 / 31.  Other K gain nothing and would pay for the ranges (K = 3584, LM head, 1
-    // row 165 / 169; K = 5120, 32000 columns, 7 rows 53 / 55).
+    // 8192 in 4 parts, 17 rows 35 / 31.  Other K would pay for the ranges (K = 3584, LM head, 1 row 165 / 169; K =
+    // 5120, 32000 columns, 7 rows 53 / 55) and have little to gain (K = 3584, 32 places and a sum per tile: nothing up
+    // to 64 rows, 254 / 248 at 128).
     const bool spread = steps % 32 == 0;
     const int place = blockIdx.x >> 3 & 31;
     auto first_step = [&]() {
@@ -1049,7 +1050,7 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     // K = 3584, 152064 columns 294 / 296, 301 / 311, 329 / 328, 338 / 347; K = 4096, 128256 columns 277 / 277, 289 /
     // 290, 316 / 306, 321 / 322; K = 5120, 73728 columns 199 / 211, 207 / 231, 230 / 241, 232 / 241; K = 8192,
     // 65536 columns 276 / 253, 282 / 266, 309 / 280, 318 / 303; SwiGLU, K = 3584, 65536 columns 124 / 122, 124 / 123,
-    // 135 / 129, 139 / 135.  128 rows, K = 3584: 248 / 282.
+    // 135 / 129, 139 / 135.  128 rows, K = 3584: 254 / 282.
     if (split_k == 1 && M > 128 && tiles >= 2 * slots) {
         p.bm = 0;
         return p;
