@@ -44,6 +44,7 @@ namespace ms {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 g_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float g_f32x16_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t g_u32x4_t;
 
 constexpr int kGemmBM = 256, kGemmBN = 256, kGemmBK = 32;
 constexpr int kGemmThreads = 512;
@@ -197,25 +198,60 @@ __device__ __forceinline__ void gemm_k_loop(char* smem, const uint16_t* const (&
 #undef MS_GEMM_STASH
 }
 
+// Rows of 128 bytes that a wave has in registers, a piece per lane, go to memory as whole lines: the pieces
+// pass through 4 KB of LDS that is the wave's own for the moment (32 rows of eight 16-byte chunks, chunk c of
+// row r at c ^ (r % 8)), and a store instruction then covers eight rows.
+constexpr int kWaveOutBytes = 4096;
+__device__ __forceinline__ char* wave_out_chunk(char* lds, int row, int chunk) { return lds + row * 128 + ((chunk ^ (row & 7)) << 4); }
+// 16 bytes to p, which is aligned to 16 bytes (wide) or to 8; kPast: not kept in the caches.
+template <bool kPast>
+__device__ __forceinline__ void store_16(void* p, uint4 v, bool wide) {
+    if (!wide) {
+        reinterpret_cast<uint2*>(p)[0] = make_uint2(v.x, v.y);
+        reinterpret_cast<uint2*>(p)[1] = make_uint2(v.z, v.w);
+    } else if (kPast) {
+        __builtin_nontemporal_store(__builtin_bit_cast(g_u32x4_t, v), reinterpret_cast<g_u32x4_t*>(p));
+    } else {
+        *reinterpret_cast<uint4*>(p) = v;
+    }
+}
+__device__ __forceinline__ void wave_lds_fence() {   // LDS operations of a wave are carried out in order: only the compiler has to keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // What a wave does with its 32 kMI rows x 64 columns of fp32 sums.  Accumulator i of a lane: n = n_wave +
-// 32 ni + 8 (i / 4) + 4 hf + i % 4, m = m_lane + 32 mi (hf = lane / 32; m_lane includes lane % 32).
-template <int kMode, int kMI>
-__device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x16_t (&acc)[2][kMI], bool to_partial, int k_part, int m_lane,
-                                                int n_wave, int hf) {
+// 32 ni + 8 (i / 4) + 4 hf + i % 4, m = m_wave + 32 mi + l32 (hf = lane / 32, l32 = lane % 32).  lds: kWaveOutBytes.
+// Stored straight from that layout, an instruction puts 8 bytes into each of 64 places of 32 rows, and and
+// the written lines push the activations out of L2; whole lines can pass the caches by.  us, before / now, cold weights: LM
+// head of 152064 columns, K = 3584, 24 rows 174 / 170, 56 rows 196 / 175, 128 rows 250 / 220, 448 rows 533 / 517; output
+// projection at 448 rows (7 fp32 parts, which stay in the caches for the reduction: past them it was no faster) 39.6 / 35.2.
+// Results of up to 16 rows stay in the caches for what follows (kPast false; the step of one sequence 653 / 647 us).
+template <int kMode, int kMI, bool kPast>
+__device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x16_t (&acc)[2][kMI], bool to_partial, int k_part, int m_wave,
+                                                int n_wave, int lane, char* lds) {
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int o_row = lane >> 3, o_chunk = lane & 7;   // + 8 j rows: this lane's 16 bytes of a store
     if (to_partial) {
         const int p_col0 = kMode == kGemmAllPartial ? 0 : g.tail_col0, p_ld = g.N - p_col0;
+        float* p = g.partial + ((size_t)k_part * g.M + m_wave + o_row) * p_ld + (n_wave - p_col0 + 4 * o_chunk);
 #pragma unroll
         for (int mi = 0; mi < kMI; ++mi) {
-            const int m = m_lane + 32 * mi;
-            if (m >= g.M) continue;
+            if (m_wave + 32 * mi >= g.M) continue;
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
+            for (int ni = 0; ni < 2; ++ni) {
+                wave_lds_fence();
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = n_wave + 32 * ni + 8 * q + 4 * hf;
-                    *reinterpret_cast<float4*>(g.partial + ((size_t)k_part * g.M + m) * p_ld + (n - p_col0)) =
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4*>(wave_out_chunk(lds, l32, 2 * q + hf)) =
                         make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
-                }
+                wave_lds_fence();
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (m_wave + 32 * mi + 8 * j + o_row < g.M)
+                        *reinterpret_cast<float4*>(p + (size_t)(32 * mi + 8 * j) * p_ld + 32 * ni) =
+                            *reinterpret_cast<const float4*>(wave_out_chunk(lds, 8 * j + o_row, o_chunk));
+            }
         }
         return;
     }
@@ -232,18 +268,22 @@ __device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x1
                     best = key_max(best, argmax_key(acc[ni][mi][i], n_wave + 32 * ni + 8 * (i >> 2) + 4 * hf + (i & 3)));
             const uint32_t lo = __shfl_xor((int)(uint32_t)best, 32, 64), hi = __shfl_xor((int)(uint32_t)(best >> 32), 32, 64);
             best = key_max(best, ((unsigned long long)hi << 32) | lo);
-            const int m = m_lane + 32 * mi;
+            const int m = m_wave + l32 + 32 * mi;
             if (m < g.M && hf == 0) g.keys[(size_t)(n_wave / kGemmColGroup) * g.M + m] = best;
         }
         return;
     }
     if (kMode == kGemmSwiglu) {
         // weight rows n_wave .. + 32 are gate rows, the next 32 the matching up rows: accumulators [0][mi]
-        // and [1][mi] hold gate and up of output column n_wave / 2 + ...
+        // and [1][mi] hold gate and up of output column n_wave / 2 + ...; two row blocks share the wave's LDS
+        // (chunks 0 .. 3 and 4 .. 7 of its rows), 64 bytes of a row each
+        const bool wide = (reinterpret_cast<uintptr_t>(g.out[0]) & 15u) == 0;
+        const int r4 = lane >> 2, c4 = lane & 3;
+        uint16_t* out = g.out[0] + (size_t)(m_wave + r4) * (g.N / 2) + n_wave / 2 + 8 * c4;
 #pragma unroll
         for (int mi = 0; mi < kMI; ++mi) {
-            const int m = m_lane + 32 * mi;
-            if (m >= g.M) continue;
+            if (m_wave + 32 * mi >= g.M) continue;
+            wave_lds_fence();
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float o[4];
@@ -252,26 +292,33 @@ __device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x1
                 uint2 pk;
                 pk.x = g_pack_bf16x2(o[0], o[1]);
                 pk.y = g_pack_bf16x2(o[2], o[3]);
-                *reinterpret_cast<uint2*>(g.out[0] + (size_t)m * (g.N / 2) + n_wave / 2 + 8 * q + 4 * hf) = pk;
+                *reinterpret_cast<uint2*>(wave_out_chunk(lds, l32, 4 * (mi & 1) + q) + 8 * hf) = pk;
             }
+            wave_lds_fence();
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if (m_wave + 32 * mi + 16 * j + r4 < g.M)
+                    store_16<kPast>(out + (size_t)(32 * mi + 16 * j) * (g.N / 2), *reinterpret_cast<const uint4*>(wave_out_chunk(lds, 16 * j + r4, 4 * (mi & 1) + c4)),
+                             wide);
         }
         return;
     }
     uint16_t* dst = nullptr;   // a wave's columns go to one destination: boundaries are multiples of 64
     int col0 = 0, ld = 0;
     pick_destination(g, n_wave, dst, col0, ld);
+    const bool wide = (reinterpret_cast<uintptr_t>(dst) & 15u) == 0;
+    dst += (size_t)(m_wave + o_row) * ld + (n_wave - col0 + 8 * o_chunk);
 #pragma unroll
     for (int mi = 0; mi < kMI; ++mi) {
-        const int m = m_lane + 32 * mi;
-        if (m >= g.M) continue;
+        if (m_wave + 32 * mi >= g.M) continue;
+        wave_lds_fence();
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int n = n_wave + 32 * ni + 8 * q + 4 * hf;
                 float4 v = make_float4(acc[ni][mi][4 * q], acc[ni][mi][4 * q + 1], acc[ni][mi][4 * q + 2], acc[ni][mi][4 * q + 3]);
                 if (g.bias) {
-                    const uint2 b = *reinterpret_cast<const uint2*>(g.bias + n);
+                    const uint2 b = *reinterpret_cast<const uint2*>(g.bias + n_wave + 32 * ni + 8 * q + 4 * hf);
                     v.x += bf16_bits_to_float(b.x & 0xffffu);
                     v.y += bf16_bits_to_float(b.x >> 16);
                     v.z += bf16_bits_to_float(b.y & 0xffffu);
@@ -280,8 +327,13 @@ __device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x1
                 uint2 pk;
                 pk.x = g_pack_bf16x2(v.x, v.y);
                 pk.y = g_pack_bf16x2(v.z, v.w);
-                *reinterpret_cast<uint2*>(dst + (size_t)m * ld + (n - col0)) = pk;
+                *reinterpret_cast<uint2*>(wave_out_chunk(lds, l32, 4 * ni + q) + 8 * hf) = pk;
             }
+        wave_lds_fence();
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (m_wave + 32 * mi + 8 * j + o_row < g.M)
+                store_16<kPast>(dst + (size_t)(32 * mi + 8 * j) * ld, *reinterpret_cast<const uint4*>(wave_out_chunk(lds, 8 * j + o_row, o_chunk)), wide);
     }
 }
 
@@ -361,7 +413,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_tn_bf16(GemmArgs g) {
     }
     if (mi_n == 0) return;   // nothing of the product in this wave's tile (no barrier follows)
 
-    store_wave_tile<kMode, 4>(g, acc, to_partial, k_part, m0 + 128 * wm + l32, n0 + kGemmColGroup * wn, hf);
+    // (every wave has read its last operands: the K loop ends with a barrier behind them)
+    store_wave_tile<kMode, 4, true>(g, acc, to_partial, k_part, m0 + 128 * wm, n0 + kGemmColGroup * wn, lane, smem + w * kWaveOutBytes);
 }
 
 // Sums the K parts of columns col0 .. N (partials [parts][M][N - col0]), adds the bias, rounds to
@@ -507,8 +560,6 @@ __global__ __launch_bounds__(256) void argmax_finish(const unsigned long long* k
     }
     if (threadIdx.x == 0) out[m] = red[0] ? (int)(0xffffffffu - (uint32_t)red[0]) : 0;
 }
-
-typedef __attribute__((ext_vector_type(4))) uint32_t g_u32x4_t;
 
 // ---------------------------------------------------------------------------------------------
 // At most 16 rows on the matrix cores (the step of one or two sequences).  The product is bound by
@@ -720,9 +771,9 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // What bounds it: a compute unit takes in about 32 bytes per ns over both tiles whatever their shape
 // (activations come from L2 but return in order behind the weights), so the weights' share
 // 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
-// kernel, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
-// 91 -> 67, 224 rows 101 -> 94; LM head 220 -> 172 (6.3 TB/s), 238 -> 197, 283 -> 254; down 36 ->
-// 29, 40 -> 32, 49 -> 40, 62 -> 54; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
+// kernel as it was then, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
+// 91 -> 63, 224 rows 101 -> 84; LM head 220 -> 170 (6.4 TB/s), 238 -> 175, 283 -> 220; down 36 ->
+// 29, 40 -> 31, 49 -> 36, 62 -> 47; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMidMaxRows = 256;
 constexpr int kMidBN = 128, kMidBK = 64;
@@ -789,6 +840,7 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     constexpr int kWaves = 2 * kWM, kS = mid_stages(kRowsA), kStage = mid_stage_bytes(kRowsA);
     constexpr int kChunks = (kRowsA + kMidBN) / 8, kLoads = (kChunks + kWaves - 1) / kWaves;
     constexpr bool kRanges = kMode != kGemmSwiglu && kMI == 1;   // (two row blocks per wave: not the registers for it)
+    static_assert(kWaves * kWaveOutBytes <= kStage, "room for the results");
     static_assert(kRowsA == 32 * kWM * kMI || (kWM * kMI == 1 && kRowsA < 32), "fewer rows than the tile's: one block of 32");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
@@ -874,7 +926,6 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 --in_flight;
-                issue();   // into the stage that was multiplied before the barrier
                 const char* ab = a_op + buf * kStage;
                 const char* wb = w_op + buf * kStage;
                 buf = buf + 1 == kS ? 0 : buf + 1;
@@ -887,6 +938,7 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
                     for (int mi = 0; mi < kMI; ++mi) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + at_a);
                 };
                 fetch(0, 0);
+                issue();   // into the stage that was multiplied before the barrier
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
                     if (kk < 3) fetch(kk + 1, (kk + 1) & 1);   // the next operands are on their way while these are multiplied
@@ -923,7 +975,13 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[ni][0] = ((range[0][ni] + range[1][ni]) + range[2][ni]) + range[3][ni];
         }
-        store_wave_tile<kMode, kMI>(g, acc, !cur.whole, cur.part, 32 * kMI * wm + l32, cur.n0 + 64 * wn, hf);
+        // The stage that was multiplied last is free until the next step's loads, which are asked for behind that
+        // step's barrier: the waves' 4 KB lie there.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        store_wave_tile<kMode, kMI, (kRowsA > 16)>(g, acc, !cur.whole, cur.part, 32 * kMI * wm, cur.n0 + 64 * wn, lane,
+                                    smem + (buf ? buf - 1 : kS - 1) * kStage + w * kWaveOutBytes);
     }
 }
 

@@ -165,3 +165,25 @@ def test_few_rows_run_on_the_kernel_that_is_ahead(m, n, k, split, kernel):
     M.ms_gemm_bf16(a, w, None, [out], split, ws)
     assert M.ms_gemm_last_kernel() == kernel
     _close(out, ref)
+
+
+@pytest.mark.parametrize("m", [1, 8, 17, 33, 100, 161, 256, 257, 300])
+@pytest.mark.parametrize("shift", [4, 8])
+def test_destinations_on_8_byte_boundaries(m, shift):
+    """Results leave as 16-byte pieces of whole lines where the destination allows it, as 8-byte ones otherwise;
+    the elements around a destination keep their values."""
+    from paper_2604_14889_amd import binding as M
+    from paper_2604_14889_amd.binding import interleave_gate_up
+    n, k = 384, 192
+    gen, a, w, ref = _inputs(m, n, k, m + shift)
+    bufs = [torch.full((m * c + 16,), 77.0, dtype=torch.bfloat16, device="cuda") for c in (128, 256)]
+    outs = [b[shift:shift + m * c].view(m, c) for b, c in zip(bufs, (128, 256))]
+    assert outs[0].data_ptr() % 16 == (8 if shift == 4 else 0)
+    M.ms_gemm_bf16(a, w, None, outs, 1, torch.empty(max(16, M.ms_gemm_workspace_bytes(m, n, k, 1)), dtype=torch.uint8, device="cuda"))
+    _close(torch.cat(outs, dim=1), ref)
+    gate, up = ref[:, :192], ref[:, 192:]
+    act = torch.full((m * 192 + 16,), 77.0, dtype=torch.bfloat16, device="cuda")
+    M.ms_gemm_swiglu_bf16(a, interleave_gate_up(w[:192].contiguous(), w[192:].contiguous()), act[shift:shift + m * 192].view(m, 192))
+    _close(act[shift:shift + m * 192].view(m, 192), gate * torch.sigmoid(gate) * up, 1e-5)
+    for b, c in ((bufs[0], 128), (bufs[1], 256), (act, 192)):
+        assert (b[:shift] == 77).all() and (b[shift + m * c:] == 77).all()
