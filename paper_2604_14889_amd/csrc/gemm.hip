@@ -985,6 +985,129 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// gate/up of up to 256 rows whose 128-column tiles would need a little more than a round of the chip: tiles of
+// 160 or 192 weight rows instead, one per workgroup and one round, so that no tile is divided over K and no
+// second launch adds up parts.  The same pipeline as gemm_rows_bf16 (both operands straight into LDS, K in steps
+// of 64, one barrier per step).  A wave owns all rows (above 128 half of them) x 32 weight rows: 16 gate rows and
+// the 16 up rows of the same outputs, which meet in one lane (accumulators 0 .. 7 and 8 .. 15).
+// Bound by HBM up to about 64 rows (W is read once), above by what a compute unit takes in.  us per call at 37888
+// columns, K = 3584 (272 MB), cold weights, 128-column tiles with a divided last round and its reduction / these: 7 rows
+// 46.9 / 44.0 (6.2 TB/s), 24 rows 46.7 / 42.7, 56 rows 51.3 / 47.7, 90 rows 57.3 / 51.2, 128 rows 65.9 / 60.1, 192 rows 81.0 /
+// 68.7, 224 rows 88.1 / 80.7, 256 rows 91.3 / 87.4.
+// ---------------------------------------------------------------------------------------------
+constexpr int wide_stage_bytes(int rows, int wn) { return (rows + 32 * wn) * kMidBK * 2; }
+constexpr int wide_stages(int rows, int wn) { return 160 * 1024 / wide_stage_bytes(rows, wn) < 8 ? 160 * 1024 / wide_stage_bytes(rows, wn) : 8; }
+
+template <int kWM, int kMI, int kWN, int kRowsA = 32 * kWM * kMI>
+__global__ __launch_bounds__(64 * kWM * kWN) void gate_up_wide_bf16(GemmArgs g) {
+    constexpr int kS = wide_stages(kRowsA, kWN), kStage = wide_stage_bytes(kRowsA, kWN), kRowsW = 32 * kWN;
+    constexpr int kChunks = (kRowsA + kRowsW) / 8, kWaves = kWM * kWN, kLoads = (kChunks + kWaves - 1) / kWaves;
+    constexpr int kOutRow = 2 * 16 * kWN + 16;   // bytes between rows of results in LDS
+    static_assert(kRowsA == 32 * kWM * kMI || (kWM * kMI == 1 && kRowsA < 32), "fewer rows than the tile's: one block of 32");
+    static_assert(32 * kWM * kMI * kOutRow <= kS * kStage, "room for the results");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w / kWN, wn = w % kWN;
+    const int steps = g.K / kMidBK, pair0 = blockIdx.x * kWN;   // first of the tile's groups of 16 outputs
+    // Row r of W's part of a stage: group pair0 + r / 32, gate rows first.  In memory two groups share 64 rows: 32 gate
+    // rows, then 32 up rows.
+    const int row0 = 64 * (pair0 >> 1);
+    uint32_t voff[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int c = min(w + i * kWaves, kChunks - 1), row = 8 * c + (lane >> 3);   // the last chunk may be loaded by several waves
+        int src;
+        if (row < kRowsA) {
+            src = min(row, g.M - 1);
+        } else {
+            const int r = row - kRowsA, p = pair0 + (r >> 5);
+            src = min(64 * (p >> 1) + ((r & 16) << 1) + 16 * (p & 1) + (r & 15), g.N - 1) - row0;   // past N: never stored
+        }
+        voff[i] = (uint32_t)src * (uint32_t)g.K * 2u + 16u * ((lane & 7) ^ ((row >> 1) & 7));
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const char* base_a = reinterpret_cast<const char*>(g.a);
+    const char* base_w = reinterpret_cast<const char*>(g.w + (size_t)row0 * g.K);
+    // Rows a multiple of 4 KB apart: workgroups start at different steps, as in gemm_rows_bf16.
+    int i_step = steps % 32 == 0 ? (int)((uint32_t)steps * (blockIdx.x >> 3 & 31) >> 5) : 0, i_left = steps, i_buf = 0, in_flight = 0;
+    auto issue = [&]() {
+        if (i_left == 0) return;
+        const size_t k_bytes = (size_t)i_step * (kMidBK * 2);
+        const char* ab = wave_uniform(base_a + k_bytes);
+        const char* wb = wave_uniform(base_w + k_bytes);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int c = min(w + i * kWaves, kChunks - 1);
+            const uint32_t lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)i_buf * kStage + 1024u * c);
+            if (8 * c < kRowsA) load_lds_1k<false>(lds, voff[i], ab);
+            else load_lds_1k<true>(lds, voff[i], wb);   // W passes through once
+        }
+        ++in_flight;
+        i_buf = i_buf + 1 == kS ? 0 : i_buf + 1;
+        i_step = i_step + 1 == steps ? 0 : i_step + 1;
+        --i_left;
+    };
+    const int l_a = kRowsA < 32 ? l32 & (kRowsA - 1) : l32;
+    const char* a_op = smem + (32 * kMI * wm + l_a) * (kMidBK * 2);
+    const char* w_op = smem + (kRowsA + 32 * wn + l32) * (kMidBK * 2);
+    const bool full = kWM == 1 || 32 * (kMI * wm + kMI - 1) < g.M;   // the wave's last block holds rows of the product
+    const int swz = ((kRowsA + l32) >> 1) & 7, swz_a = (l_a >> 1) & 7;
+#pragma unroll
+    for (int s = 0; s < kS - 1; ++s) issue();
+    g_f32x16_t acc[kMI];
+#pragma unroll
+    for (int mi = 0; mi < kMI; ++mi)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[mi][i] = 0.f;
+    int buf = 0;
+    for (int s = 0; s < steps; ++s) {
+        wait_steps<kS - 2, kLoads>(in_flight - 1);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        --in_flight;
+        const char* ab = a_op + buf * kStage;
+        const char* wb = w_op + buf * kStage;
+        buf = buf + 1 == kS ? 0 : buf + 1;
+        g_bf16x8_t wf[2], af[2][kMI];
+        auto fetch = [&](int kk, int set) {
+            wf[set] = *reinterpret_cast<const g_bf16x8_t*>(wb + ((2 * kk + hf) ^ swz) * 16);
+#pragma unroll
+            for (int mi = 0; mi < kMI; ++mi)
+                if (mi < kMI - 1 || full) af[set][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * (kMidBK * 2) + ((2 * kk + hf) ^ swz_a) * 16);
+        };
+        fetch(0, 0);
+        issue();   // into the stage that was multiplied before the barrier
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            if (kk < 3) fetch(kk + 1, (kk + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int mi = 0; mi < kMI; ++mi)
+                if (mi < kMI - 1 || full) acc[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1], af[kk & 1][mi], acc[mi], 0, 0, 0);
+        }
+    }
+    __syncthreads();   // every wave is done with the stages, and nothing is on its way into them
+    char* own = smem + (32 * kMI * wm + l32) * kOutRow + 32 * wn + 8 * hf;
+#pragma unroll
+    for (int mi = 0; mi < kMI; ++mi)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            uint2 pk;
+            pk.x = g_pack_bf16x2(swiglu_value(acc[mi][4 * q], acc[mi][4 * q + 8]), swiglu_value(acc[mi][4 * q + 1], acc[mi][4 * q + 9]));
+            pk.y = g_pack_bf16x2(swiglu_value(acc[mi][4 * q + 2], acc[mi][4 * q + 10]), swiglu_value(acc[mi][4 * q + 3], acc[mi][4 * q + 11]));
+            *reinterpret_cast<uint2*>(own + mi * 32 * kOutRow + 16 * q) = pk;
+        }
+    __syncthreads();
+    const int inter = g.N / 2, col0 = 16 * pair0, cols = min(16 * kWN, inter - col0);   // a multiple of 16
+    const bool wide = (reinterpret_cast<uintptr_t>(g.out[0]) & 15u) == 0;
+    for (int c = tid; c < g.M * 2 * kWN; c += 64 * kWaves) {   // 16-byte pieces, 2 kWN a row
+        const int row = c / (2 * kWN), col = 8 * (c % (2 * kWN));
+        if (col < cols)
+            store_16<(kRowsA > 16)>(g.out[0] + (size_t)row * inter + col0 + col, *reinterpret_cast<const uint4*>(smem + row * kOutRow + 2 * col), wide);
+    }
+}
+
 static thread_local const char* g_last_kernel = "";   // of the calling thread's last product
 
 static bool g_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1178,6 +1301,46 @@ static int mid_launch(const GemmArgs& g, int bm, const MidUnits& units, hipStrea
     }
 }
 
+// gate/up on gate_up_wide_bf16: the columns of a tile (0: not there).  One round of tiles of 160 or 192 columns where
+// 128-column ones need more than one; both sides' times stand at the kernel.  (Up to one round of 128-column tiles has
+// nothing to gain: 28672 columns are 224 whole tiles.  More than one of 192 has to be divided either way.)
+static int wide_columns(int M, int N, int K) {
+    const int slots = gemm_slots() / 2;
+    if (M > kMidMaxRows || K % kMidBK || K > 1 << 22 || N <= slots * kMidBN) return 0;
+    return (N + 159) / 160 <= slots ? 160 : (N + 191) / 192 <= slots ? 192 : 0;
+}
+template <int kWM, int kMI, int kWN, int kRowsA = 32 * kWM * kMI>
+static int wide_launch_built(const GemmArgs& g, hipStream_t stream) {
+    constexpr int lds = wide_stages(kRowsA, kWN) * wide_stage_bytes(kRowsA, kWN);
+    static std::once_flag once[64];
+    static hipError_t result[64];
+    int dev = 0;
+    MS_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) MS_FAIL(MS_ERR_UNSUPPORTED, "device index %d outside [0, 64)", dev);
+    std::call_once(once[dev], [&] {
+        result[dev] = hipFuncSetAttribute((const void*)gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
+    g_last_kernel = "gate_up_wide_bf16";
+    hipLaunchKernelGGL((gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>), dim3((unsigned)((g.N + 32 * kWN - 1) / (32 * kWN))), dim3(64 * kWM * kWN), lds, stream, g);
+    MS_HIP_TRY(hipGetLastError());
+    return MS_OK;
+}
+template <int kWN>
+static int wide_launch(const GemmArgs& g, hipStream_t stream) {
+    if (g.M <= 8) return wide_launch_built<1, 1, kWN, 8>(g, stream);
+    if (g.M <= 16) return wide_launch_built<1, 1, kWN, 16>(g, stream);
+    switch ((g.M + 31) / 32) {
+        case 1: return wide_launch_built<1, 1, kWN>(g, stream);
+        case 2: return wide_launch_built<1, 2, kWN>(g, stream);
+        case 3: return wide_launch_built<1, 3, kWN>(g, stream);
+        case 4: return wide_launch_built<1, 4, kWN>(g, stream);
+        case 5:
+        case 6: return wide_launch_built<2, 3, kWN>(g, stream);
+        default: return wide_launch_built<2, 4, kWN>(g, stream);
+    }
+}
+
 static int skinny_dispatch(const GemmArgs& g, const SkinnyPlan& v, hipStream_t stream, bool swiglu = false) {
     static bool lds_allowed[64] = {};   // per device: the builds may use more than the default 64 KB of dynamic LDS
     int dev = 0;
@@ -1258,6 +1421,10 @@ static bool few_rows_first(int M, int N, int K, int split_k) {
 // Launches the tiles (and the reduction of the parts, if any).  g holds operands and destinations.
 static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, size_t ws_bytes, hipStream_t stream,
                        const NormTail* norm = nullptr) {
+    if (swiglu) {
+        const int cols = wide_columns(g.M, g.N, g.K);
+        if (cols) return cols == 160 ? wide_launch<5>(g, stream) : wide_launch<6>(g, stream);
+    }
     MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
     // A plain product without split_k at up to 16 rows may be logits: every column's sum is taken the same way
     // (whole tiles throughout), so that equal weight rows give equal logits.

@@ -187,3 +187,20 @@ def test_destinations_on_8_byte_boundaries(m, shift):
     _close(act[shift:shift + m * 192].view(m, 192), gate * torch.sigmoid(gate) * up, 1e-5)
     for b, c in ((bufs[0], 128), (bufs[1], 256), (act, 192)):
         assert (b[:shift] == 77).all() and (b[shift + m * c:] == 77).all()
+
+
+@pytest.mark.parametrize("m", [1, 8, 9, 16, 17, 32, 33, 64, 65, 96, 97, 128, 129, 192, 193, 256])
+@pytest.mark.parametrize("inter,k", [(16384 + 64, 64), (18944, 704), (20480, 192), (20480 + 64, 2048), (24576, 640)])
+def test_gate_up_in_one_round_of_wide_tiles(m, inter, k):
+    """More 128-column tiles than compute units, at most as many of 160 or 192: odd numbers of groups, a last tile
+    that is partly past N, K shorter and longer than the pipeline, rows a multiple of 4 KB apart."""
+    from paper_2604_14889_amd import binding as M
+    gen, a, w, ref = _inputs(m, 2 * inter, k, m + inter + k)
+    buf = torch.full((m * inter + 8,), 77.0, dtype=torch.bfloat16, device="cuda")
+    out = buf[:m * inter].view(m, inter)
+    M.ms_gemm_swiglu_bf16(a, M.interleave_gate_up(w[:inter].contiguous(), w[inter:].contiguous()), out)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert M.ms_gemm_last_kernel() == "gate_up_wide_bf16"
+    gate, up = ref[:, :inter], ref[:, inter:]
+    _close(out, gate * torch.sigmoid(gate) * up, 1e-5)
+    assert (buf[m * inter:] == 77).all()
