@@ -195,3 +195,15 @@ def test_skewed_batches_run_on_the_kernel_that_levels_them(hq, hkv, nv, nf, leng
             want = O.attention_rows(ora, 0, ids[b], as_f32(inp.q[b], "bf16"), as_f32(inp.k_new[b], "bf16"), as_f32(inp.v_new[b], "bf16"),
                                     pos[b], O.default_ctx_new(nv, nf), rows=[(i, h) for i in (0, nv + nf - 1) for h in range(0, hq, 3)])
             check_out(got[b], want, "bf16", f"sequence {b}")
+
+
+@pytest.mark.parametrize("hq,hkv,nv,nf,lengths", [
+    # one launch sums the split kernel's shares, by blocks of 32 x 32 outputs or by quarters of them: at most 8, 16 and 32
+    # shares, more than one batch of them, one and two row blocks, on either side of the line between the two
+    (28, 4, 4, 3, [200]), (28, 4, 4, 3, [460]), (28, 4, 4, 3, [3000]), (8, 2, 1, 3, [9000]), (28, 4, 5, 4, [33, 700]),
+    (28, 4, 5, 4, [33, 700, 1]), (16, 8, 9, 0, [500]), (16, 8, 9, 0, [500, 64]), (28, 4, 41, 0, [130]),
+])
+def test_shares_are_summed_by_blocks_and_by_quarters(hq, hkv, nv, nf, lengths):
+    sh = W.AttnShape("fold", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
+    got, again = compare(sh, 950 + len(lengths))
+    assert np.array_equal(got, again)
