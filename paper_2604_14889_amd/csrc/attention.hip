@@ -589,7 +589,7 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
 // partial requested before the first is used.
 template <typename T, int D, int kMaxSplits>
 __global__ __launch_bounds__(256) void pv_attn_combine(const float* __restrict__ ws, void* __restrict__ out, int n_rows, int n_splits) {
-    const int row = blockIdx.x * (1024 / D) + threadIdx.x / (D / 4), d = threadIdx.x % (D / 4) * 4;
+    const int row = blockIdx.x * (4 * blockDim.x / D) + threadIdx.x / (D / 4), d = threadIdx.x % (D / 4) * 4;
     if (row >= n_rows) return;
     const float* op = ws + (size_t)row * n_splits * D + d;
     const float2* ml = reinterpret_cast<const float2*>(ws + (size_t)n_rows * n_splits * D) + (size_t)row * n_splits;
@@ -660,10 +660,15 @@ static int launch_general(ms_cache* c, AttnArgs& a, const BatchMeta& bm, int B, 
     c->last_attention = a.n_splits == 1 ? "pv_attn_rows" : "pv_attn_rows+pv_attn_combine";
     if (rc != MS_OK || a.n_splits == 1) return rc;
     const int rows = B * a.n_q * a.n_q_heads;
-    const dim3 grid((unsigned)((rows + 1024 / D - 1) / (1024 / D)));
+    // Workgroups of one wave as long as workgroups of four leave half of the compute units out, so that the partials come
+    // in through more of them (of four waves / of one, us per call of both launches: fp32, 8 / 8 heads of 64, 4 x 1000 tokens
+    // 11.7 / 11.1; bf16, 16 / 4 heads of 64, 1 x 3000 12.4 / 11.7, 4 x 3000 13.4 / 13.0, 64 queries 1 x 2000 20.5 / 20.1; level
+    // from there on: 16 x 4000 27.3 / 27.2).
+    const int threads = 2l * rows * D <= 1024l * c->n_cus ? 64 : 256, rows_per = 4 * threads / D;
+    const dim3 grid((unsigned)((rows + rows_per - 1) / rows_per)), block(threads);
     c->launches++;
-    if (a.n_splits <= 8) hipLaunchKernelGGL((pv_attn_combine<T, D, 8>), grid, dim3(256), 0, stream, a.ws, a.out, rows, a.n_splits);
-    else hipLaunchKernelGGL((pv_attn_combine<T, D, kMaxRowSplits>), grid, dim3(256), 0, stream, a.ws, a.out, rows, a.n_splits);
+    if (a.n_splits <= 8) hipLaunchKernelGGL((pv_attn_combine<T, D, 8>), grid, block, 0, stream, a.ws, a.out, rows, a.n_splits);
+    else hipLaunchKernelGGL((pv_attn_combine<T, D, kMaxRowSplits>), grid, block, 0, stream, a.ws, a.out, rows, a.n_splits);
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;
 }

@@ -207,3 +207,13 @@ def test_shares_are_summed_by_blocks_and_by_quarters(hq, hkv, nv, nf, lengths):
     sh = W.AttnShape("fold", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
     got, again = compare(sh, 950 + len(lengths))
     assert np.array_equal(got, again)
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,nv,lengths", [
+    # rows of the second launch of the general kernel: one, a workgroup of one wave full and one row more, as many rows as
+    # workgroups of one wave take (131072 elements on 256 compute units) and one query more
+    ("f32", 1, 1, 64, 1, [200]), ("f32", 4, 4, 64, 1, [130]), ("f32", 5, 5, 64, 1, [130]), ("f32", 3, 3, 128, 1, [300]),
+    ("bf16", 32, 8, 64, 64, [40]), ("bf16", 33, 11, 64, 63, [40]),
+])
+def test_partials_of_the_general_kernel_are_summed_by_one_or_four_waves(dtype, hq, hkv, d, nv, lengths):
+    compare(W.AttnShape("combine", dtype, len(lengths), hq, hkv, d, nv, 0, lengths, 1.0 if dtype == "f32" else 0.5, 10000.0), 970 + hq)
