@@ -27,7 +27,8 @@
 // weight rows interleaved in blocks of 32 (gate block, up block), a lane holds gate and up of the
 // same output element in two accumulators and writes silu(gate) * up directly.
 // Steps of up to 256 rows are bound by bringing W to the compute units and run on a second kernel,
-// further down (gemm_rows_bf16), that computes row tiles of the step's own height.  A third kernel, for
+// further down (gemm_rows_bf16), that computes row tiles of the step's own height (gate/up with a little more
+// than a round of its tiles: gate_up_wide_bf16, the same with wider ones).  A third kernel, for
 // at most 16 rows, streams 16 weight rows per wave through the matrix cores; it keeps the products that
 // give the second one too few workgroups (narrow outputs without a K split or a workspace) or that it
 // finishes in one launch instead of two.
@@ -771,7 +772,7 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 // What bounds it: a compute unit takes in about 32 bytes per ns over both tiles whatever their shape
 // (activations come from L2 but return in order behind the weights), so the weights' share
 // 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
-// kernel as it was then, us per call with the reduction: gate/up 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
+// kernel as it was then, us per call with the reduction: gate/up (on 128-column tiles) 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
 // 91 -> 63, 224 rows 101 -> 84; LM head 220 -> 170 (6.4 TB/s), 238 -> 175, 283 -> 220; down 36 ->
 // 29, 40 -> 31, 49 -> 36, 62 -> 47; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
 // ---------------------------------------------------------------------------------------------
@@ -1321,7 +1322,7 @@ static int wide_launch_built(const GemmArgs& g, hipStream_t stream) {
         result[dev] = hipFuncSetAttribute((const void*)gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
-    g_last_kernel = "gate_up_wide_bf16";
+    g_last_kernel = "gemm_rows_bf16";   // by the family: the row tiles' pipeline
     hipLaunchKernelGGL((gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>), dim3((unsigned)((g.N + 32 * kWN - 1) / (32 * kWN))), dim3(64 * kWM * kWN), lds, stream, g);
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;
