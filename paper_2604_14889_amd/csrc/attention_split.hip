@@ -303,14 +303,15 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
 // 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with kBatch
 // partials requested in one memory round trip.  Bound by those round trips: 26 shares (one sequence of
 // 4096 tokens, 7 queries) in four trips of 8 or one of 32: 17.4 / 16.7 us per call of both launches.
-// As long as there is a compute unit for each, a workgroup takes a quarter of a block's columns (kWaves 1), so that
+// As long as there is a compute unit for each, a workgroup of one wave takes a quarter of a block's columns, so that
 // the partials come in through more compute units: one sequence of 4096 tokens 4.9 / 4.1 us for this launch; us per
 // call of both launches, blocks / quarters, 28 / 4 heads: 1 x 1000 tokens 12.7 / 11.9, 1 x 4096 15.6 / 14.8, 1 x 16000
 // 22.6 / 21.3, 2 x 4096 17.3 / 17.0; 32 / 8 heads 1 x 4096 17.1 / 15.7; behind from there on: 3 x 4096 18.0 / 18.4, 7 x
 // 2000 17.1 / 18.2, 64 queries over 2 x 1000 18.6 / 19.3.
-template <int kBatch, int kWaves>
-__global__ __launch_bounds__(64 * kWaves) void pv_attn_mfma_fold(SplitArgs a) {
-    const int quarter = blockIdx.x * kWaves + (threadIdx.x >> 6), rb = quarter >> 4, db = quarter >> 2 & 3, g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
+template <int kBatch>
+__global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
+    const int quarter = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), rb = quarter >> 4, db = quarter >> 2 & 3;
+    const int g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
     const int lane = threadIdx.x & 63, i4 = quarter & 3, hf = lane >> 5, row = 32 * rb + (lane & 31);
     const int q0 = chunk * a.per_chunk, n_rows = min(a.per_chunk, a.n_q - q0) * a.group;
     if (row >= n_rows) return;
@@ -352,14 +353,6 @@ __global__ __launch_bounds__(64 * kWaves) void pv_attn_mfma_fold(SplitArgs a) {
     pk.x = pack_bf16x2(acc.x * inv, acc.y * inv);
     pk.y = pack_bf16x2(acc.z * inv, acc.w * inv);
     *reinterpret_cast<uint2*>(a.out + (((size_t)b * a.n_q + q0 + row / a.group) * a.n_q_heads + g * a.group + row % a.group) * kD + 32 * db + 8 * i4 + 4 * hf) = pk;
-}
-
-template <int kWaves>
-static void launch_fold(const SplitArgs& a, int B, hipStream_t stream) {
-    const dim3 grid(32 / kWaves, a.n_kv_heads, B * a.n_chunks), block(64 * kWaves);
-    if (a.n_splits <= 8) hipLaunchKernelGGL((pv_attn_mfma_fold<8, kWaves>), grid, block, 0, stream, a);
-    else if (a.n_splits <= 16) hipLaunchKernelGGL((pv_attn_mfma_fold<16, kWaves>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((pv_attn_mfma_fold<32, kWaves>), grid, block, 0, stream, a);
 }
 
 constexpr int kSplitDecodeQueries = 16;   // a decode step: the streaming kernel could take it
@@ -448,8 +441,11 @@ int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, in
     hipLaunchKernelGGL(pv_attn_mfma_split, dim3(n_splits, a.n_kv_heads, B * a.n_chunks), dim3(kSplitThreads), split_lds_bytes(a.n_q), stream, a);
     if (n_splits > 1) {
         c->launches++;
-        if (32l * a.n_kv_heads * B * a.n_chunks <= c->n_cus) launch_fold<1>(a, B, stream);
-        else launch_fold<4>(a, B, stream);
+        const int waves = 32l * a.n_kv_heads * B * a.n_chunks <= c->n_cus ? 1 : 4;
+        const dim3 grid(32 / waves, a.n_kv_heads, B * a.n_chunks), block(64 * waves);
+        if (n_splits <= 8) hipLaunchKernelGGL(pv_attn_mfma_fold<8>, grid, block, 0, stream, a);
+        else if (n_splits <= 16) hipLaunchKernelGGL(pv_attn_mfma_fold<16>, grid, block, 0, stream, a);
+        else hipLaunchKernelGGL(pv_attn_mfma_fold<32>, grid, block, 0, stream, a);
     }
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;
