@@ -1303,12 +1303,40 @@ static int mid_launch(const GemmArgs& g, int bm, const MidUnits& units, hipStrea
 }
 
 // gate/up on gate_up_wide_bf16: the columns of a tile (0: not there).  One round of tiles of 160 or 192 columns where
-// 128-column ones need more than one; both sides' times stand at the kernel.  (Up to one round of 128-column tiles has
-// nothing to gain: 28672 columns are 224 whole tiles.  More than one of 192 has to be divided either way.)
+// 128-column ones need more than one.  (Up to one round of 128-column tiles has nothing to gain: 28672 columns are 224
+// whole tiles.  More than one of 192 has to be divided either way.)
 static int wide_columns(int M, int N, int K) {
     const int slots = gemm_slots() / 2;
     if (M > kMidMaxRows || K % kMidBK || K > 1 << 22 || N <= slots * kMidBN) return 0;
     return (N + 159) / 160 <= slots ? 160 : (N + 191) / 192 <= slots ? 192 : 0;
+}
+// Whether they are ahead of 128-column tiles with a workspace for the K parts of the last round.  (Without one that round is
+// whole tiles, which are 2 to 90 % behind.)  A round of wide tiles takes as long however many there are, a divided round
+// goes by the tiles left over, and the launch saved, about 4.5 us, counts for less the longer K is.  us, 128-column tiles with the
+// reduction / wide tiles, cold weights, medians of three sessions:
+//   K, columns      7 rows    56 rows   97 rows    128 rows   192 rows   256 rows
+//   2048, 32896     28 / 23   28 / 26   31 / 32    32 / 34    44 / 38    46 / 48
+//   2048, 37888     30 / 26   32 / 28   38 / 34    41 / 36    56 / 41    59 / 53
+//   3584, 32896     43 / 40   44 / 44   50 / 53    54 / 56    71 / 66    73 / 82
+//   3584, 37888     46 / 43   49 / 46   58 / 57    63 / 59    85 / 71    92 / 87
+//   3584, 41088     49 / 47   52 / 52   64 / 59    68 / 60    94 / 70    94 / 96
+//   3584, 49152     56 / 54   60 / 57   75 / 65    78 / 65    112 / 78   115 / 102
+//   5120, 32896     58 / 60   63 / 64   72 / 77    77 / 81    96 / 96    102 / 116
+//   5120, 40960     66 / 66   74 / 69   86 / 85    93 / 86    123 / 104  132 / 129
+//   5120, 41088     69 / 72   77 / 77   89 / 83    95 / 84    126 / 101  132 / 140
+//   8192, 34816     96 / 86   95 / 89   111 / 123  114 / 126  158 / 145  175 / 185
+//   8192, 41088     113 / 99  112 / 105 131 / 128  136 / 131  190 / 153  204 / 204
+// The lines below leave calls up to 3 % behind, and calls where wide tiles would be up to 6 % ahead (K = 12288, 256 rows: 14 %).
+static bool wide_ahead(int M, int N, int K, int cols) {
+    const int slots = gemm_slots() / 2, left = N / kMidBN - slots, blocks = (M + 31) / 32;
+    const bool pow2 = (K & (K - 1)) == 0;   // rows a power of two apart cost the 128-column tiles about a tenth
+    if (left >= (cols == 160 ? slots / 5 : 3 * slots / 8)) return true;
+    if (blocks == 4 || blocks > 6) {
+        if (cols == 160) return 14336l * left >= (long)slots * (K - 1536);
+        return blocks == 4 || K <= 2048 || pow2;
+    }
+    if (M <= 16 || blocks == 2) return K <= 4608 || pow2;
+    return true;
 }
 template <int kWM, int kMI, int kWN, int kRowsA = 32 * kWM * kMI>
 static int wide_launch_built(const GemmArgs& g, hipStream_t stream) {
@@ -1422,10 +1450,6 @@ static bool few_rows_first(int M, int N, int K, int split_k) {
 // Launches the tiles (and the reduction of the parts, if any).  g holds operands and destinations.
 static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, size_t ws_bytes, hipStream_t stream,
                        const NormTail* norm = nullptr) {
-    if (swiglu) {
-        const int cols = wide_columns(g.M, g.N, g.K);
-        if (cols) return cols == 160 ? wide_launch<5>(g, stream) : wide_launch<6>(g, stream);
-    }
     MidPlan mid = mid_plan(g.M, g.N, g.K, split_k);
     // A plain product without split_k at up to 16 rows may be logits: every column's sum is taken the same way
     // (whole tiles throughout), so that equal weight rows give equal logits.
@@ -1439,6 +1463,10 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
     // 166, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.4 / 11.8 (252 units); 14 rows 52 / 47, 190 / 170, 38 /
     // 29, 14.6 / 13.0, 14.3 / 13.6.
     const bool mid_room = !mid.workspace_bytes || (workspace && ws_bytes >= mid.workspace_bytes && g_aligned16(workspace));
+    if (swiglu) {
+        const int cols = wide_columns(g.M, g.N, g.K);
+        if (cols && (!mid_room || wide_ahead(g.M, g.N, g.K, cols))) return cols == 160 ? wide_launch<5>(g, stream) : wide_launch<6>(g, stream);
+    }
     const bool mid_first = mid.bm && mid_room && !(norm && split_k == 1) && 8 * mid.units.units >= 3 * gemm_slots() &&
                            (swiglu || norm || !few_rows_first(g.M, g.N, g.K, split_k));
     if (g.M <= kSkinnyMaxRows && mid_first) {

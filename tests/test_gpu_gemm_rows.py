@@ -203,3 +203,36 @@ def test_gate_up_in_one_round_of_wide_tiles(m, inter, k):
     gate, up = ref[:, :inter], ref[:, inter:]
     _close(out, gate * torch.sigmoid(gate) * up, 1e-5)
     assert (buf[m * inter:] == 77).all()
+
+
+WIDE_ROUTES = [
+    # M, N, K, whether gate/up with a workspace takes one round of wide tiles (they write no K parts) or 128-column tiles
+    # whose last round is divided over K: on either side of the lines between the two
+    (7, 37888, 3584, True), (128, 37888, 3584, True), (256, 37888, 3584, True), (24, 32896, 5120, True), (192, 32896, 3584, True),
+    (96, 41088, 3584, True), (128, 41088, 3584, True), (256, 45056, 3584, True), (224, 32896, 1024, True), (7, 32896, 4096, True),
+    (16, 41088, 8192, True), (56, 39424, 6144, True), (256, 41088, 2048, True), (128, 34816, 2048, True),
+    (128, 32896, 3584, False), (97, 34816, 3584, False), (128, 37888, 8192, False), (193, 33664, 4096, False), (256, 34816, 5120, False),
+    (224, 41088, 3584, False), (256, 43008, 5120, False), (7, 33664, 5120, False), (16, 41088, 6144, False), (56, 34816, 6144, False),
+    (40, 53504, 4096, False), (160, 53504, 8192, False),
+]
+
+
+@pytest.mark.parametrize("m,n,k,wide", WIDE_ROUTES)
+def test_gate_up_takes_wide_tiles_where_they_are_ahead(m, n, k, wide):
+    from paper_2604_14889_amd import binding as M
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule was measured on 256 compute units")
+    gen, a, w, ref = _inputs(m, n, k, m + n + k)
+    blocks = ref.view(m, n // 64, 2, 32)          # gate and up rows interleaved in blocks of 32
+    gate, up = blocks[:, :, 0].reshape(m, n // 2), blocks[:, :, 1].reshape(m, n // 2)
+    want = gate * torch.sigmoid(gate) * up
+    need = M.ms_gemm_workspace_bytes(m, n, k, 1)
+    assert need > 0
+    # too small a workspace and one off its alignment are none: nothing is written there
+    buf = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+    for ws, parts in ((buf[:need], not wide), (buf[:64], False), (buf[8:8 + need], False), (None, False)):
+        buf.fill_(255)
+        act = torch.full((m, n // 2), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M.ms_gemm_swiglu_bf16(a, w, act, ws)
+        assert bool((buf != 255).any()) == parts
+        _close(act, want, 2e-5 * (gate.abs() + 1) * (up.abs() + 1))
