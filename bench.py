@@ -913,6 +913,7 @@ def projections_bench(args):
         weights = copies(n, kk)
         us = timed(fn, weights)
         flops = 2.0 * rows * n * kk
+        # ("kernel" is the family's name: gate/up's wide tiles are gate_up_wide_bf16 in a trace)
         row = {"projection": name, "rows": rows, "N": n, "K": kk, "call": what, "kernel": M.ms_gemm_last_kernel(), "us": round(us, 1), "pflops": round(flops / us / 1e9, 3),
                "frac_of_2.5_pflops": round(flops / us / 1e9 / 2.5, 3), "weight_gbps": round(n * kk * 2 / us / 1e3, 1)}
         if args.library_reference:   # a reference, not on any path of the library: the bare product through torch.mm

@@ -371,9 +371,11 @@ int ms_profile_attention(ms_cache* cache, int capacity, int stride, int span);
 int ms_profile_read(ms_cache* cache, float* ms_out, int cap, int* n);
 
 /* Names of the kernel(s) the last ms_predict_verify_attention call on this cache launched, joined by
- * "+" if there were two; "" before the first.  ms_gemm_last_kernel: the kernel of the calling
- * thread's last projection (its reduction not named).  For reports and tests: which kernel takes a
- * call is no part of the interface. */
+ * "+" if there were two; "" before the first.  ms_gemm_last_kernel: the kernel family of the
+ * calling thread's last projection (its reduction not named): "gemm_tn_bf16" (256 x 256 tiles),
+ * "gemm_rows_bf16" (one row tile; gate/up's 160- and 192-column tiles, gate_up_wide_bf16 in a
+ * kernel trace, are of this family) or "skinny_mfma_bf16" (few rows).  For reports and tests: which
+ * kernel takes a call is no part of the interface. */
 const char* ms_attention_last_kernel(ms_cache* cache);
 const char* ms_gemm_last_kernel(void);
 

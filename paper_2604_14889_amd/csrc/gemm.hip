@@ -1109,7 +1109,7 @@ __global__ __launch_bounds__(64 * kWM * kWN) void gate_up_wide_bf16(GemmArgs g) 
     }
 }
 
-static thread_local const char* g_last_kernel = "";   // of the calling thread's last product
+static thread_local const char* g_last_kernel = "";   // family of the calling thread's last product
 
 static bool g_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -1350,7 +1350,7 @@ static int wide_launch_built(const GemmArgs& g, hipStream_t stream) {
         result[dev] = hipFuncSetAttribute((const void*)gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
-    g_last_kernel = "gemm_rows_bf16";   // by the family: the row tiles' pipeline
+    g_last_kernel = "gemm_rows_bf16";   // the family's name: the row tiles' pipeline
     hipLaunchKernelGGL((gate_up_wide_bf16<kWM, kMI, kWN, kRowsA>), dim3((unsigned)((g.N + 32 * kWN - 1) / (32 * kWN))), dim3(64 * kWM * kWN), lds, stream, g);
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;

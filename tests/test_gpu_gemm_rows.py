@@ -199,7 +199,7 @@ def test_gate_up_in_one_round_of_wide_tiles(m, inter, k):
     buf = torch.full((m * inter + 8,), 77.0, dtype=torch.bfloat16, device="cuda")
     out = buf[:m * inter].view(m, inter)
     M.ms_gemm_swiglu_bf16(a, M.interleave_gate_up(w[:inter].contiguous(), w[inter:].contiguous()), out)
-    assert M.ms_gemm_last_kernel() == "gemm_rows_bf16"     # the row tiles' family
+    assert M.ms_gemm_last_kernel() == "gemm_rows_bf16"     # the family: which of its kernels, the K parts tell (below)
     gate, up = ref[:, :inter], ref[:, inter:]
     _close(out, gate * torch.sigmoid(gate) * up, 1e-5)
     assert (buf[m * inter:] == 77).all()
@@ -211,6 +211,8 @@ WIDE_ROUTES = [
     (7, 37888, 3584, True), (128, 37888, 3584, True), (256, 37888, 3584, True), (24, 32896, 5120, True), (192, 32896, 3584, True),
     (96, 41088, 3584, True), (128, 41088, 3584, True), (256, 45056, 3584, True), (224, 32896, 1024, True), (7, 32896, 4096, True),
     (16, 41088, 8192, True), (56, 39424, 6144, True), (256, 41088, 2048, True), (128, 34816, 2048, True),
+    (12, 37888, 3584, True), (90, 37888, 3584, True), (7, 41088, 3584, True), (20, 41088, 3584, True), (56, 45056, 3584, True),
+    (150, 41088, 3584, True),      # with those above every build of either width
     (128, 32896, 3584, False), (97, 34816, 3584, False), (128, 37888, 8192, False), (193, 33664, 4096, False), (256, 34816, 5120, False),
     (224, 41088, 3584, False), (256, 43008, 5120, False), (7, 33664, 5120, False), (16, 41088, 6144, False), (56, 34816, 6144, False),
     (40, 53504, 4096, False), (160, 53504, 8192, False),
