@@ -202,6 +202,7 @@ def test_skewed_batches_run_on_the_kernel_that_levels_them(hq, hkv, nv, nf, leng
     # shares, more than one batch of them, one and two row blocks, on either side of the line between the two
     (28, 4, 4, 3, [200]), (28, 4, 4, 3, [460]), (28, 4, 4, 3, [3000]), (8, 2, 1, 3, [9000]), (28, 4, 5, 4, [33, 700]),
     (28, 4, 5, 4, [33, 700, 1]), (16, 8, 9, 0, [500]), (16, 8, 9, 0, [500, 64]), (28, 4, 41, 0, [130]),
+    (8, 2, 1, 3, [11000]),                                 # 345 tiles in 39 shares (9000 tokens are 32: one batch)
 ])
 def test_shares_are_summed_by_blocks_and_by_quarters(hq, hkv, nv, nf, lengths):
     sh = W.AttnShape("fold", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
@@ -211,7 +212,7 @@ def test_shares_are_summed_by_blocks_and_by_quarters(hq, hkv, nv, nf, lengths):
 
 @pytest.mark.parametrize("dtype,hq,hkv,d,nv,lengths", [
     # rows of the second launch of the general kernel: one, a workgroup of one wave full and one row more, as many rows as
-    # workgroups of one wave take (131072 elements on 256 compute units) and one query more
+    # workgroups of one wave take (131072 elements on 256 compute units) and 31 rows more
     ("f32", 1, 1, 64, 1, [200]), ("f32", 4, 4, 64, 1, [130]), ("f32", 5, 5, 64, 1, [130]), ("f32", 3, 3, 128, 1, [300]),
     ("bf16", 32, 8, 64, 64, [40]), ("bf16", 33, 11, 64, 63, [40]),
 ])

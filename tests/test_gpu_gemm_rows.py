@@ -75,7 +75,8 @@ def test_divided_last_round_and_whole_tiles_without_workspace(m, n, k):
         out = torch.full((m, n), float("nan"), dtype=torch.bfloat16, device="cuda")
         M.ms_gemm_bf16(a, w, None, [out], 1, ws)
         _close(out, ref)
-    # SwiGLU over the same product: gate and up rows interleaved in blocks of 32
+    # SwiGLU over the same product: gate and up rows interleaved in blocks of 32 (33408 columns at K up to 1024 are one
+    # round of wide tiles with either; K parts of every height with SwiGLU: test_gate_up_takes_wide_tiles_where_they_are_ahead)
     blocks = ref.view(m, n // 64, 2, 32)
     gate, up = blocks[:, :, 0].reshape(m, n // 2), blocks[:, :, 1].reshape(m, n // 2)
     want = gate * torch.sigmoid(gate) * up
@@ -238,3 +239,25 @@ def test_gate_up_takes_wide_tiles_where_they_are_ahead(m, n, k, wide):
         M.ms_gemm_swiglu_bf16(a, w, act, ws)
         assert bool((buf != 255).any()) == parts
         _close(act, want, 2e-5 * (gate.abs() + 1) * (up.abs() + 1))
+
+
+@pytest.mark.parametrize("m", [1, 12, 24, 90, 150, 256])
+@pytest.mark.parametrize("inter", [16384 + 64, 20480 + 64])      # 160- and 192-column tiles, the last one partly past N
+def test_wide_tiles_repeat_their_bits_on_either_alignment(m, inter):
+    """16-byte pieces of a row where the destination allows it, 8-byte ones otherwise: the same bits, call after call, and
+    nothing around the destination."""
+    from paper_2604_14889_amd import binding as M
+    k = 256
+    gen, a, w, ref = _inputs(m, 2 * inter, k, m + inter)
+    blocks = ref.view(m, inter // 32, 2, 32)
+    gate, up = blocks[:, :, 0].reshape(m, inter), blocks[:, :, 1].reshape(m, inter)
+    first = None
+    for shift in (4, 8, 12, 8):
+        buf = torch.full((m * inter + 16,), 77.0, dtype=torch.bfloat16, device="cuda")
+        out = buf[shift:shift + m * inter].view(m, inter)
+        assert out.data_ptr() % 16 == 2 * shift % 16
+        M.ms_gemm_swiglu_bf16(a, w, out)
+        _close(out, gate * torch.sigmoid(gate) * up, 2e-5 * (gate.abs() + 1) * (up.abs() + 1))
+        assert (buf[:shift] == 77).all() and (buf[shift + m * inter:] == 77).all()
+        first = out.clone() if first is None else first
+        assert torch.equal(out.view(torch.int16), first.view(torch.int16))
