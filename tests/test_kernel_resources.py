@@ -45,6 +45,20 @@ def loops_with_priority_changes(lines, start, end):
     return loops
 
 
+def innermost_multiplying_loops(lines, name):
+    """Bodies of a kernel's loops (a backward branch to a label) that hold matrix instructions and no loop that does."""
+    start = next(i for i, ln in enumerate(lines) if ln.startswith(name + ":"))
+    end = next(i for i in range(start, len(lines)) if lines[i].startswith(".Lfunc_end"))
+    label_at = {ln.split(":")[0]: i for i, ln in enumerate(lines[start:end], start) if ln.startswith(".LBB") and ":" in ln}
+    loops = []
+    for i in range(start, end):
+        m = re.match(r"\s+s_c?branch\w*\s+(\.LBB\w+)", lines[i])
+        if m and m.group(1) in label_at and label_at[m.group(1)] < i and any("v_mfma" in ln for ln in lines[label_at[m.group(1)]:i]):
+            loops.append((label_at[m.group(1)], i))
+    inner = [(a, b) for a, b in loops if not any((c, d) != (a, b) and a <= c and d <= b for c, d in loops)]
+    return [[ln.split(";")[0] for ln in lines[a:b]] for a, b in inner]
+
+
 def test_projection_kernels_do_not_spill():
     """The few-row kernel keeps 16 loads in flight per wave and the tiled one runs two waves per SIMD
     (256 registers each): a spilled value inside their loops would put a wait for all loads there.  The
@@ -70,6 +84,20 @@ def test_projection_kernels_do_not_spill():
         assert multiplying >= 4, (name, loops)          # one K loop per number of valid row blocks (1 to 4; 0 only moves data)
     norm = [r for n, r in kernels.items() if "reduce_add_rmsnorm" in n]
     assert len(norm) == 1 and norm[0]["vgpr_spill_count"] == 0 and norm[0]["vgpr_count"] <= 128, norm
+    # the row tiles (two waves per SIMD at most: 256 registers) and gate/up's wide ones (up to three: 168) count their
+    # loads by hand.  Scalars may be parked in vector registers around a unit of work; the builds with two row blocks
+    # per wave also take up to eight back per step of 64 K (one cycle each of some thousand)
+    rows = {n: r for n, r in kernels.items() if "gemm_rows_bf16" in n}
+    wide = {n: r for n, r in kernels.items() if "gate_up_wide_bf16" in n}
+    assert len(rows) == 24 and len(wide) == 16, sorted(kernels)
+    for name, r in {**rows, **wide}.items():
+        assert r["vgpr_spill_count"] == 0 and r["private_segment_fixed_size"] == 0, (name, r)
+        assert r["vgpr_count"] <= (168 if name in wide else 256) and r["sgpr_spill_count"] <= (0 if name in wide else 20), (name, r)
+        bodies = innermost_multiplying_loops(lines, name)
+        assert bodies, name
+        for body in bodies:
+            assert not [ln for ln in body if "scratch_" in ln or "v_writelane" in ln], name
+            assert sum("v_readlane" in ln for ln in body) <= (8 if name in rows and re.search(r"ELi2ELi(192|256)E", name) else 0), name
 
 
 def test_decode_builds_of_the_stream_kernel_do_not_spill_in_the_stream_loop():
