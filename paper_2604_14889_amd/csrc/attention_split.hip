@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
 // Folds the shares' partials in their order, normalises and writes the bf16 rows.  A workgroup takes one
 // 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with kBatch
 // partials requested in one memory round trip.  Bound by those round trips: 26 shares (one sequence of
-// 4096 tokens, 7 queries) in four trips of 8 or one of 32: 17.4 / 16.7 us per call of both launches.
+// 4096 tokens, 7 queries) in four trips of 8 or one of 32: 17.4 / 16.7 us per call of both launches (by blocks).
 // As long as there is a compute unit for each, a workgroup of one wave takes a quarter of a block's columns, so that
 // the partials come in through more compute units: one sequence of 4096 tokens 4.9 / 4.1 us for this launch; us per
 // call of both launches, blocks / quarters, 28 / 4 heads: 1 x 1000 tokens 12.7 / 11.9, 1 x 4096 15.6 / 14.8, 1 x 16000

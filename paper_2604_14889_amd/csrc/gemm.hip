@@ -223,11 +223,12 @@ __device__ __forceinline__ void wave_lds_fence() {   // LDS operations of a wave
 
 // What a wave does with its 32 kMI rows x 64 columns of fp32 sums.  Accumulator i of a lane: n = n_wave +
 // 32 ni + 8 (i / 4) + 4 hf + i % 4, m = m_wave + 32 mi + l32 (hf = lane / 32, l32 = lane % 32).  lds: kWaveOutBytes.
-// Stored straight from that layout, an instruction puts 8 bytes into each of 64 places of 32 rows, and and
-// the written lines push the activations out of L2; whole lines can pass the caches by.  us, before / now, cold weights: LM
-// head of 152064 columns, K = 3584, 24 rows 174 / 170, 56 rows 196 / 175, 128 rows 250 / 220, 448 rows 533 / 517; output
-// projection at 448 rows (7 fp32 parts, which stay in the caches for the reduction: past them it was no faster) 39.6 / 35.2.
-// Results of up to 16 rows stay in the caches for what follows (kPast false; the step of one sequence 653 / 647 us).
+// Stored straight from that layout, an instruction puts 8 bytes into each of 64 places of 32 rows, and
+// the written lines push the activations out of L2; whole lines (SwiGLU, with 32 outputs a row: halves of them) can pass the
+// caches by.  us, before / now, cold weights, one session: LM head of 152064 columns, K = 3584, 24 rows 174 / 169, 56 rows
+// 197 / 175, 128 rows 250 / 219, 448 rows 544 / 527; output projection at 448 rows (7 fp32 parts, which stay in the caches
+// for the reduction: past them it was no faster) 37.8 / 35.0.  The row tiles of up to 16 rows keep their results in the
+// caches for what follows (kPast false; the step of one sequence 653 / 647 us); the 256 x 256 tiles never do.
 template <int kMode, int kMI, bool kPast>
 __device__ __forceinline__ void store_wave_tile(const GemmArgs& g, const g_f32x16_t (&acc)[2][kMI], bool to_partial, int k_part, int m_wave,
                                                 int n_wave, int lane, char* lds) {
@@ -771,10 +772,10 @@ __global__ __launch_bounds__(kSkinnyThreads) void skinny_mfma_bf16(GemmArgs g, i
 //     refilled one barrier after its last reader.
 // What bounds it: a compute unit takes in about 32 bytes per ns over both tiles whatever their shape
 // (activations come from L2 but return in order behind the weights), so the weights' share
-// 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, against the 256 x 256
-// kernel as it was then, us per call with the reduction: gate/up (on 128-column tiles) 17 rows 76 -> 47 (5.8 TB/s), 56 rows 80 -> 49, 128 rows
-// 91 -> 63, 224 rows 101 -> 84; LM head 220 -> 170 (6.4 TB/s), 238 -> 175, 283 -> 220; down 36 ->
-// 29, 40 -> 31, 49 -> 36, 62 -> 47; Q/K/V 19 -> 18, 21 -> 17, 27 -> 23, 33 -> 27.
+// 128 / (rows + 128) of that up to HBM's rate.  Measured at Qwen2.5-7B widths, cold weights, us per call with the reduction,
+// 17 / 56 / 128 / 224 rows, one session: gate/up on 128-column tiles 47 (5.8 TB/s) / 49 / 64 / 88; LM head 168 (6.5 TB/s) /
+// 175 / 219; down 29 / 30 / 36 / 48; Q/K/V 13 / 15 / 21 / 24.  The 256 x 256 kernel took 76 / 80 / 91 / 101, 220 / 238 /
+// 283, 36 / 40 / 49 / 62 and 19 / 21 / 27 / 33 when this one was built.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMidMaxRows = 256;
 constexpr int kMidBN = 128, kMidBK = 64;
@@ -869,7 +870,7 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
     // LM head of 128256 columns 9 rows 202 / 172, 64 rows 224 / 195; K = 2048, 65536 columns, 16 rows 59 / 52; 8192 x
     // 8192 in 4 parts, 17 rows 35 / 31.  Other K would pay for the ranges (K = 3584, LM head, 1 row 165 / 169; K =
     // 5120, 32000 columns, 7 rows 53 / 55) and have little to gain (K = 3584, 32 places and a sum per tile: nothing up
-    // to 64 rows, 254 / 248 at 128).
+    // to 64 rows, 254 / 248 at 128, before results left as whole lines).
     const bool spread = steps % 32 == 0;
     const int place = blockIdx.x >> 3 & 31;
     auto first_step = [&]() {
@@ -993,9 +994,11 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
 // of 64, one barrier per step).  A wave owns all rows (above 128 half of them) x 32 weight rows: 16 gate rows and
 // the 16 up rows of the same outputs, which meet in one lane (accumulators 0 .. 7 and 8 .. 15).
 // Bound by HBM up to about 64 rows (W is read once), above by what a compute unit takes in.  us per call at 37888
-// columns, K = 3584 (272 MB), cold weights, 128-column tiles with a divided last round and its reduction / these: 7 rows
-// 46.9 / 44.0 (6.2 TB/s), 24 rows 46.7 / 42.7, 56 rows 51.3 / 47.7, 90 rows 57.3 / 51.2, 128 rows 65.9 / 60.1, 192 rows 81.0 /
-// 68.7, 224 rows 88.1 / 80.7, 256 rows 91.3 / 87.4.
+// columns, K = 3584 (272 MB), cold weights, 128-column tiles with a divided last round and its reduction / these, one
+// session: 7 rows 46.1 / 43.3 (6.3 TB/s), 24 rows 46.9 / 42.9, 56 rows 49.1 / 46.5, 90 rows 58.5 / 52.1, 128 rows 63.8 / 61.1,
+// 192 rows 85.7 / 67.1, 224 rows 88.0 / 83.2, 256 rows 90.4 / 88.0.  Other widths and K: wide_ahead.
+// A column's sum is one chain over K, where 128-column tiles of a divided round add up parts: results differ in single bf16
+// roundings (K = 3584: 0.05 % of them), the error against 64 bits is the same to six digits.
 // ---------------------------------------------------------------------------------------------
 constexpr int wide_stage_bytes(int rows, int wn) { return (rows + 32 * wn) * kMidBK * 2; }
 constexpr int wide_stages(int rows, int wn) { return 160 * 1024 / wide_stage_bytes(rows, wn) < 8 ? 160 * 1024 / wide_stage_bytes(rows, wn) : 8; }
@@ -1227,12 +1230,15 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     const int tiles = N / kMidBN;
     p.units = {tiles, tiles, 1, tiles};
     const int slots = gemm_slots() / 2, steps = K / kMidBK;
-    // Wide outputs that fill the chip with 256 x 256 tiles too stay there above 128 rows.  Which is ahead goes by K
-    // more than by the rows, and that is the side without large losses.  us here / there, 144, 192, 224, 256 rows:
-    // K = 3584, 152064 columns 294 / 296, 301 / 311, 329 / 328, 338 / 347; K = 4096, 128256 columns 277 / 277, 289 /
-    // 290, 316 / 306, 321 / 322; K = 5120, 73728 columns 199 / 211, 207 / 231, 230 / 241, 232 / 241; K = 8192,
-    // 65536 columns 276 / 253, 282 / 266, 309 / 280, 318 / 303; SwiGLU, K = 3584, 65536 columns 124 / 122, 124 / 123,
-    // 135 / 129, 139 / 135.  128 rows, K = 3584: 254 / 282.
+    // Wide outputs that fill the chip with 256 x 256 tiles too stay there above 128 rows.  The line was drawn when the
+    // two were level up to K = 4096 and each ahead at one longer K.  Since results leave both as whole lines, us here /
+    // there, 144, 192, 224, 256 rows: K = 3584, 152064 columns 274 / 292, 287 / 301, 316 / 311, 323 / 327; K = 4096,
+    // 128256 columns 260 / 275, 274 / 275, 301 / 285, 306 / 302; K = 5120, 73728 columns 186 / 212, 197 / 225, 220 / 238,
+    // 231 / 237; K = 8192, 65536 columns 265 / 255, 275 / 260, 300 / 276, 309 / 293; 128256 columns 516 / 493, 542 / 501,
+    // 594 / 533, 610 / 570; SwiGLU, 160, 192, 224, 256 rows: K = 3584, 65536 columns 123 / 112, 127 / 117, 141 / 122,
+    // 140 / 130; K = 5120, 73728 columns 193 / 209, 202 / 222, 220 / 234, 228 / 233.  So plain products
+    // have come ahead here by 0 to 13 % up to 192 rows and K = 5120; with SwiGLU, at K = 8192, and from 193 rows on,
+    // which are staged as 256, it goes either way.  The line has not been moved for that.
     if (split_k == 1 && M > 128 && tiles >= 2 * slots) {
         p.bm = 0;
         return p;
@@ -1459,7 +1465,7 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
     }
     // Up to 16 rows: gemm_rows_bf16 where its units fill three quarters of the chip and the workspace holds
     // their partials, the few-row kernel otherwise (narrow outputs without split_k, no workspace).  us per
-    // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16: 7 rows gate/up 49 / 46, LM head 171 /
+    // call at Qwen2.5-7B widths, few-row kernel / gemm_rows_bf16 (gate/up on 128-column tiles): 7 rows gate/up 49 / 46, LM head 171 /
     // 166, down 30 / 28, output 14.2 / 12.3, Q/K/V 12.4 / 11.8 (252 units); 14 rows 52 / 47, 190 / 170, 38 /
     // 29, 14.6 / 13.0, 14.3 / 13.6.
     const bool mid_room = !mid.workspace_bytes || (workspace && ws_bytes >= mid.workspace_bytes && g_aligned16(workspace));
