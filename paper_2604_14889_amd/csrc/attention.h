@@ -45,8 +45,12 @@ namespace ms {
 int static_scratch(int device, void** ptr);
 
 // attention_split.hip
-int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, int* n_splits);
-int launch_split(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, int share_tiles, int n_splits, hipStream_t stream);
+// How a call is divided over workgroups (attention_split.hip).
+struct SplitPlan {
+    int share_tiles, n_splits, n_lean, new_shares, wg_blocks, late, lds_bytes;
+};
+bool split_plan(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, SplitPlan* p);
+int launch_split(ms_cache* c, const AttnArgs& a, const BatchMeta& bm, int B, const SplitPlan& p, hipStream_t stream);
 int split_allow_lds();
 
 // attention_mfma.hip

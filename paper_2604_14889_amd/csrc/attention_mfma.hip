@@ -1156,11 +1156,10 @@ int launch_mfma(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, hip
                             "output rows unwritten; the arrival counters have been reset, repeat the step");
     }
     const size_t part_bytes = (size_t)c->d.n_kv_heads * kPartFloats * sizeof(float);
-    int n_splits = 0;
-    const int share_tiles = c->stream_only ? 0 : split_share_tiles(c, bm.len, B, ga.n_q, mfma_workspace_bytes(c, B, ga.n_q) / part_bytes, &n_splits);
-    if (share_tiles > 0) {
+    SplitPlan split;
+    if (!c->stream_only && split_plan(c, bm.len, B, ga.n_q, mfma_workspace_bytes(c, B, ga.n_q) / part_bytes, &split)) {
         if (int rc = profile_open(c, stream)) return rc;
-        if (int rc = launch_split(c, ga, bm, B, share_tiles, n_splits, stream)) return rc;
+        if (int rc = launch_split(c, ga, bm, B, split, stream)) return rc;
         return profile_close(c, stream);
     }
     // plan: rebuilt only when the batch (ids, lengths) changed since the last call on this cache

@@ -2,22 +2,31 @@
 // chip on the streaming kernel's terms: a few short sequences, and wide steps (prompt chunks,
 // memory-token passes) over caches that fit the on-chip caches.
 //
-// What is computed: see attention.hip (MemoSight paper, Sections 2.1.1 and 2.3).  Such a call is bound
-// by the chain of dependent latencies inside a workgroup, not by bytes.  So:
-//   * No work plan: a (sequence, chunk of query rows, KV head) is cut into n_splits equal shares of
-//     32-token tiles, cached tiles first, the step's own (in-flight) tiles last.  Everything a
+// What is computed: see attention.hip (MemoSight paper, Sections 2.1.1 and 2.3).  Such a call is bound by the chain of
+// dependent steps inside a workgroup, not by bytes: a lone wave carries out an instruction per 4 to 5 cycles (2.2 ns), so
+// that what counts, once the tiles have been asked for, is how many there are.  So:
+//   * No work plan: (sequence, group of 32-row blocks, KV head) is cut into equal shares of 32-token tiles.  Everything a
 //     workgroup needs first follows from its index and the kernel arguments.
-//   * Steps of more than 64 rows per KV head are cut into chunks of 64 / group queries, a workgroup
-//     each: the cache is read once per chunk, from L2 after the first.
-//   * A workgroup has four waves: wave w owns row block w % 2 (32 query rows, the rotated Q operand in
-//     registers) and every second tile of the share.  Only two waves hold states of the same rows, so
-//     the merge at the end moves 32 KB through LDS (eight waves with both row blocks each: 512 KB).
+//   * A workgroup has four token streams, a wave each: stream ts takes every fourth tile of the share.  Tiles, query rows
+//     and frequencies go straight to LDS (no registers, no LDS store instructions; K and V rows swizzled by the order in
+//     which the lanes fetch them), two tiles of a stream ahead, counted by hand, so that waiting for the query rows
+//     leaves the tiles in flight.  A stream's tiles are its wave's own: the loop has no barrier.
+//   * With two row blocks a workgroup has eight waves, two a stream, which load a half of each tile (K, V) and share it.
+//     One block as long as the calls' workgroups then fit the chip twice over: the cache is read once per workgroup,
+//     from L2 after the first.
+//   * The query rows are rotated by all threads together (eight pairs each), the step's own keys in their place the same way.
+//   * At the end each wave of a row block keeps one of the four 32-column blocks of O and hands the others over.
+// Time stamps inside the kernel, one sequence of 4096 tokens, 7 queries, 28 / 4 heads (us from the first wave's start, before
+// with two row blocks of two waves each in every workgroup, tiles through registers and 26 shares / now with 27): page ids
+// 1.1 / 0.4, rows rotated 2.3 / 2.0, first tile done 4.6 / 3.4, everything stored 8.8 / 6.7; per call 15.7 / 13.4; what is left is launch,
+// page ids, the rows' way to LDS, sines, merge and the partials' way out.
 //   * The shares' partial results go to a second launch, where more workgroups read them: the share that
-//     finishes last folding them in the same launch was slower from 2 shares on (us inside / in a second
-//     launch: 1 x 64 tokens, 7 queries, 2 shares 12.0 / 10.2; 8 x 200 tokens, 9 queries 14.8 / 12.9; 2 x 2000
-//     tokens, 41 queries, 6 shares 22.3 / 20.6; 16 x 1000 tokens 20.6 / 20.1; never ahead).
-// Tile layout, rotation, rounding and softmax are the streaming kernel's (attention_mfma.hip).  Tiles
-// are assigned by index: results do not depend on timing.
+//     finishes last folding them in the same launch was slower from 2 shares on.  Up to 12 tiles stay in one workgroup.
+// Rotation, rounding and softmax are the streaming kernel's (attention_mfma.hip), except that the scale is applied to the
+// scores and not to the rotated rows (a multiplication less per element of a row).  Tiles are assigned by index: results do
+// not depend on timing.
+#include <float.h>
+
 #include <algorithm>
 
 #include "attention.h"
@@ -26,8 +35,8 @@
 
 namespace ms {
 
-constexpr int kSplitWaves = 4;
-constexpr int kSplitThreads = 64 * kSplitWaves;
+constexpr int kSplitMostThreads = 512;
+constexpr int kSplitDecodeQueries = 16;   // a decode step: the streaming kernel could take it
 
 struct SplitArgs {
     const uint16_t* pool_layer;
@@ -40,173 +49,292 @@ struct SplitArgs {
     const int* pos;
     const int* ctx_new;
     uint16_t* out;
-    float* ws;              // partials [sequence][chunk][share][KV head] of kPartFloats
+    float* ws;              // partials [sequence][row block][share][KV head] of kSplitPartFloats
     int n_q, n_verify, n_q_heads, n_kv_heads, group, max_pages;
-    int n_chunks, per_chunk, n_splits, share_tiles;
+    int n_blocks, n_groups, wg_blocks, n_splits, n_lean, new_shares, share_tiles, late;   // the last new_shares shares hold the step's own tiles   // row blocks of a sequence; groups of wg_blocks of them, a workgroup each
+    int units;                        // n_splits x KV heads x sequences
+    uint32_t group_inv, blocks_inv, groups_inv, splits_inv, heads_inv;   // for div_by
     long page_elems;
-    float scale_log2;
+    float scale_log2;   // > 0; `negate`: the scale is negative, the rotated rows change their sign
+    int negate;
     int seq[MS_MAX_BATCH];
 };
 
-// LDS: cos/sin of the position ids the workgroup needs, one V tile per wave; at the end each wave's
-// half of an O block (8 KB) and its softmax scalars lie over its V tile.
-constexpr int kSplitMergeBytes = 32 * 64 * 4 + 2 * 64 * 4;
-static_assert(kSplitMergeBytes <= kVTileBytes, "the merge region lies over the wave's V tile");
-static int split_lds_bytes(int n_q) { return kSplitWaves * kVTileBytes + n_q * 64 * (int)sizeof(float2); }
+// x / n with inv = inverse_of(n): exact while x n < 2^20 (rows of a sequence: 64 queries x 64 heads, n = 64; row blocks of a batch: 64 x
+// 128, n = 128; workgroups: split_plan looks).
+static uint32_t inverse_of(int n) { return (1u << 20) / n + 1; }
+__device__ __forceinline__ int div_by(uint32_t x, uint32_t inv) { return (int)((uint64_t)x * inv >> 20); }
 
-__global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
-    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31, l16 = lane & 15;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rb = w & 1, ts = w >> 1;
-    float2* cs = reinterpret_cast<float2*>(smem + kSplitWaves * kVTileBytes);
-    const int q0 = chunk * a.per_chunk, cn = min(a.per_chunk, a.n_q - q0), n_rows = cn * a.group;
+constexpr int kSplitRows = 32;                                       // query rows of a block
+constexpr int kSplitPartFloats = 2 * kSplitRows + kSplitRows * kD;   // m[32], l[32], O[4 d blocks][4][64 lanes][4]
+static_assert(2 * kSplitPartFloats <= kPartFloats, "two row blocks take no more than the other kernels' partials of 64 rows");
 
-    // ---- raw query rows of this wave's block: lane = row, d = 16 kk + 8 hf .. + 8 ----
-    const int row = 32 * rb + l32;
-    const bool live = row < n_rows;
-    const int qi = q0 + (live ? row / a.group : 0);
-    uint4 x[8];
-    {
-        const uint16_t* qp = a.q + (((size_t)b * a.n_q + qi) * a.n_q_heads + g * a.group + (live ? row % a.group : 0)) * kD + 8 * hf;
+// LDS: two stages of a tile (K, then V) for each of the four token streams, cos/sin of the position ids the workgroup needs,
+// and the set-up: the query rows (8 KB a row block) and the frequencies.  Steps of so many queries that this is more than
+// there is have the set-up where the second stages lie (late: those are filled behind it).  At the end a wave has in the
+// stages what it hands over of its O block (12 KB) and its softmax scalars.
+constexpr int kSplitStreams = 4;
+constexpr int kSplitTileBytes = kTile * kD * 2;                // K or V of a tile
+constexpr int kSplitStageBytes = 2 * kSplitTileBytes;
+constexpr int kSplitStreamBytes = 2 * kSplitStageBytes;
+constexpr int kSplitRingBytes = kSplitStreams * kSplitStreamBytes;
+constexpr int kSplitMergeFloats = 3 * 16 * 64 + 2 * 64;
+static_assert(kSplitMergeFloats * 4 <= kSplitStageBytes, "a wave hands over in one stage");
+constexpr int kSplitMostLds = 160 * 1024;
+static int split_lds_bytes(int wg_blocks, int n_q, bool late) {
+    return kSplitRingBytes + n_q * 64 * (int)sizeof(float2) + (late ? 0 : wg_blocks * kSplitTileBytes + 1024);
+}
+
+// Rotation of 16-byte chunks: lo holds elements i .. i + 8 of a row, hi elements i + 64 .. i + 72, f the pairs' cos/sin.
+__device__ __forceinline__ void rotate_chunks(uint4& lo, uint4& hi, const float2* f) {
+    const uint32_t w0[4] = {lo.x, lo.y, lo.z, lo.w}, w1[4] = {hi.x, hi.y, hi.z, hi.w};
+    uint32_t y0[4], y1[4];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) x[kk] = *reinterpret_cast<const uint4*>(qp + 16 * kk);
+    for (int e = 0; e < 4; ++e) {
+        float v0[2], v1[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float a0 = h ? __uint_as_float(w0[e] & 0xffff0000u) : __uint_as_float(w0[e] << 16);
+            const float a1 = h ? __uint_as_float(w1[e] & 0xffff0000u) : __uint_as_float(w1[e] << 16);
+            const float2 c = f[2 * e + h];
+            v0[h] = a0 * c.x - a1 * c.y;
+            v1[h] = a1 * c.x + a0 * c.y;
+        }
+        y0[e] = pack_bf16x2(v0[0], v0[1]);
+        y1[e] = pack_bf16x2(v1[0], v1[1]);
     }
-    const float inv_f = a.inv_freq[lane];
+    lo = make_uint4(y0[0], y0[1], y0[2], y0[3]);
+    hi = make_uint4(y1[0], y1[1], y1[2], y1[3]);
+}
 
-    // ---- this wave's tiles: every second one of the share.  Where a share begins does not depend on the
-    // device's length, so that the length and the first page ids are asked for together; the last share
-    // runs to the end, whatever has been committed since the host last looked ----
+// At most n of this wave's loads (0, 8, 16 or 32) are still on their way; its LDS reads are done.
+__device__ __forceinline__ void wait_loads_left(int n) {
+    if (n == 0) wait_loads<0>();
+    else if (n == 8) wait_loads<8>();
+    else if (n == 16) wait_loads<16>();
+    else wait_loads<32>();
+}
+
+__global__ __launch_bounds__(kSplitMostThreads, 1) void pv_attn_mfma_split(SplitArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    // Workgroups 8 apart share an XCD and its L2: the groups of row blocks of one (share, KV head, sequence), which read the same
+    // tiles, are 8 apart (the last, fewer than 8 of those: side by side).  28 / 4 heads, 9 queries, in launch order / so:
+    // 24 x 500 tokens 14.4 / 12.3 us per call, 32 x 1000 25.8 / 21.4.
+    int unit, group;
+    if (const int q = blockIdx.x >> 3; q < (a.units >> 3) * a.n_groups) {
+        const int of_8 = div_by(q, a.groups_inv);
+        group = q - of_8 * a.n_groups;
+        unit = 8 * of_8 + (blockIdx.x & 7);
+    } else {
+        const int at = blockIdx.x - (a.units & ~7) * a.n_groups, rest = a.units & 7;
+        group = at / rest;
+        unit = (a.units & ~7) + at % rest;
+    }
+    const int gb = div_by(unit, a.splits_inv), split = unit - gb * a.n_splits, b = div_by(gb, a.heads_inv), g = gb - b * a.n_kv_heads;
+    const int r0 = group * a.wg_blocks * kSplitRows;
+    const int tid = threadIdx.x, lane = tid & 63, hf = lane >> 5, l32 = lane & 31, l16 = lane & 15, l4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rb = w >> 2, ts = w & 3;   // row block, token stream
+    const bool paired = a.wg_blocks == 2;                                              // two waves a stream
+    float2* cs = reinterpret_cast<float2*>(smem + kSplitRingBytes);
+    char* rows = a.late ? smem + kSplitStageBytes : smem + kSplitRingBytes + a.n_q * 64 * (int)sizeof(float2);   // 8 KB a block; late: 32 KB apart
+    const int rows_step = a.late ? kSplitStreamBytes : kSplitTileBytes;
+    char* freq = a.late ? smem + 3 * kSplitStreamBytes + kSplitStageBytes : rows + a.wg_blocks * kSplitTileBytes;
+    auto lds_of = [](const char* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p; };
+    // rows of the workgroup, and the queries they belong to
+    const int n_rows = min(a.wg_blocks * kSplitRows, a.n_q * a.group - r0), q_lo = div_by(r0, a.group_inv), q_hi = div_by(r0 + n_rows - 1, a.group_inv);
+    auto query_of = [&](int r) { return div_by(r0 + min(r, n_rows - 1), a.group_inv); };   // rows past the end: the last one again, not stored
+
+    // ---- raw query rows and frequencies straight to LDS; 16-byte chunk c of row r lies at c ^ (r % 16) ----
+    {
+        const char* qp = reinterpret_cast<const char*>(a.q + ((size_t)b * a.n_q * a.n_q_heads + g * a.group) * kD);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int r = 8 * ts + 4 * j + l4, q = query_of(32 * rb + r), head = r0 + min(32 * rb + r, n_rows - 1) - q * a.group;
+            load_lds_1k<false>(__builtin_amdgcn_readfirstlane(lds_of(rows) + rb * rows_step + 1024u * (2 * ts + j)),
+                               (uint32_t)((q * a.n_q_heads + head) * kD * 2 + 16 * (l16 ^ (r & 15))), qp);
+        }
+        load_lds_1k<false>(__builtin_amdgcn_readfirstlane(lds_of(freq)), 16u * l16, a.inv_freq);   // every wave the same bytes
+    }
+
+    // ---- this workgroup's tiles: the share's new ones (of the step's own tokens), then its cached ones; stream ts takes every
+    // fourth.  Where a share begins does not depend on the device's length, so that the length and the first page ids are asked
+    // for together; the last share runs to the end, whatever has been committed since the host last looked ----
+    const bool last = split == a.n_splits - 1;
+    const int n_lean = a.n_lean, all_new = (a.n_q + kTile - 1) / kTile;
+    const bool has_new = split >= a.n_splits - a.new_shares;
+    const int n_new = !has_new ? 0 : a.new_shares == 1 ? all_new : 1;      // its new tiles: new_0 .. new_0 + n_new, items 0 .. n_new
+    const int new_0 = has_new && a.new_shares > 1 ? split - (a.n_splits - a.new_shares) : 0;
+    const int t_lo = min(split, n_lean) * a.share_tiles, t_base = t_lo - n_new;   // item i from n_new on: cached tile t_base + i
     const int seq = a.seq[b], L = uniform_load(a.d_len + seq);
     const int* pt = a.d_pt + (size_t)seq * a.max_pages;
-    const int t_lo = split * a.share_tiles;
-    const char* pool = reinterpret_cast<const char*>(a.pool_layer);
+    const char* pool = reinterpret_cast<const char*>(a.pool_layer) + (size_t)g * 2 * MS_PAGE_SIZE * kD * 2;
     const size_t page_bytes = (size_t)a.page_elems * 2;
-    const uint32_t lane_off_k = ((uint32_t)g * 2 * MS_PAGE_SIZE * kD + l16 * kD + 8 * hf) * 2;
-    const uint32_t lane_off_v = (((uint32_t)g * 2 + 1) * MS_PAGE_SIZE * kD + (lane >> 4) * kD + 8 * l16) * 2;
-    // a cached tile's pages; entries past the sequence's last page are stale page ids: read, not used
-    auto pages = [&](int t, int& pa, int& pb) {
-        pa = uniform_load(pt + min(2 * t, a.max_pages - 1));
-        pb = uniform_load(pt + min(2 * t + 1, a.max_pages - 1));
+    struct Pages {
+        int a, b;
     };
-    int t = t_lo + ts, pa, pb, pa_n, pb_n;
-    pages(t, pa, pb);
-    pages(t + 2, pa_n, pb_n);
-    const int n_cache = (L + kTile - 1) / kTile, n_tiles = n_cache + (a.n_q + kTile - 1) / kTile;   // in-flight tiles behind the cached ones
-    const int t_hi = split == a.n_splits - 1 ? n_tiles : min(n_tiles, t_lo + a.share_tiles);
-    uint4 k[8], v[8];
-    // tile T's rows (past the end: the last in-flight tile's again, so that loads are unconditional):
-    // k: token l32, d = 16 kk + 8 hf .. + 8; v[rr]: token 4 rr + lane / 16, d = 8 l16 .. + 8
-    auto load_k_tile = [&](int T, int pa, int pb) {
-        const char* base;
-        if (T < n_cache) {
-            const bool one_page = 2 * T + 1 >= (L + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE;   // the tile's second page does not exist
-            base = pool + (size_t)(uint32_t)((lane & 16) && !one_page ? pb : pa) * page_bytes + lane_off_k;
-        } else {
-            const int tok = min(kTile * (T - n_cache) + l32, a.n_q - 1);
-            base = reinterpret_cast<const char*>(a.k_new + (((size_t)b * a.n_q + tok) * a.n_kv_heads + g) * kD + 8 * hf);
-        }
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) k[kk] = *reinterpret_cast<const uint4*>(base + 32 * kk);
+    auto pages = [&](int i) {   // of item i (the step's own: any page); entries past the sequence's last page are stale page ids: not used
+        Pages p;
+        const int at = max(2 * (t_base + i), 0);
+        p.a = uniform_load(pt + min(at, a.max_pages - 1));
+        p.b = uniform_load(pt + min(at + 1, a.max_pages - 1));
+        return p;
     };
-    auto load_v_tile = [&](int T, int pa, int pb) {
-        const char* p[8];
-        if (T < n_cache) {
-            const bool one_page = 2 * T + 1 >= (L + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE;
-            const char* base_a = pool + (size_t)(uint32_t)pa * page_bytes + lane_off_v;
-            const char* base_b = pool + (size_t)(uint32_t)(one_page ? pa : pb) * page_bytes + lane_off_v;
-#pragma unroll
-            for (int rr = 0; rr < 8; ++rr) p[rr] = (rr < 4 ? base_a : base_b) + 4 * (rr & 3) * kD * 2;
-        } else {
-            const uint16_t* v0 = a.v_new + ((size_t)b * a.n_q * a.n_kv_heads + g) * kD + 8 * l16;
-#pragma unroll
-            for (int rr = 0; rr < 8; ++rr)
-                p[rr] = reinterpret_cast<const char*>(v0 + (size_t)(min(kTile * (T - n_cache) + 4 * rr + (lane >> 4), a.n_q - 1) * a.n_kv_heads) * kD);
-        }
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) v[rr] = *reinterpret_cast<const uint4*>(p[rr]);
-    };
-    load_k_tile(min(t, n_tiles - 1), pa, pb);
-    load_v_tile(min(t, n_tiles - 1), pa, pb);
+    const Pages p0 = pages(ts);
+    Pages next = pages(ts + kSplitStreams);
+    const int c_lo = has_new ? min(kTile * new_0, q_lo) : q_lo, c_hi = has_new ? max(min(kTile * (new_0 + n_new), a.n_q) - 1, q_hi) : q_hi;
+    int pid = uniform_load(a.pos + b * a.n_q + min(c_lo + w, a.n_q - 1));
+    const int n_cache = (L + kTile - 1) / kTile;
+    const int items = n_new + max(0, (last ? n_cache : has_new ? 0 : min(n_cache, t_lo + a.share_tiles)) - t_lo);
 
-    // ---- cos/sin of the chunk's position ids (of every in-flight key's in a share that reaches them) ----
-    const bool has_new = t_hi > n_cache && t_lo < t_hi;
-    const int c_lo = has_new ? 0 : q0, c_hi = has_new ? a.n_q : q0 + cn;
-    for (int i = c_lo + w; i < c_hi; i += kSplitWaves) {
+    // ---- tiles go straight to LDS: eight loads of 1 KB (4 tokens x 256 bytes) in lane order for K, eight for V; of two waves
+    // of a stream the first loads K, the second V.  The lanes fetch the 16-byte chunks of a row in an order that leaves the
+    // operand reads without bank conflicts: chunk c of K row r lies at c ^ (r % 16), of V row r at c ^ 4 (r % 4).  Their
+    // arrival is counted by hand ----
+    const int tile_loads = paired ? 8 : 16;
+    char* ring = smem + ts * kSplitStreamBytes;   // the stream's stages
+    auto issue_part = [&](int i, const Pages& p, int part) {
+        const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_of(ring) + (uint32_t)((i >> 2 & 1) * kSplitStageBytes + part * kSplitTileBytes));
+        uint32_t off[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) off[j] = (uint32_t)((4 * j + l4) * kD * 2 + 16 * (l16 ^ (part ? 4 * l4 : 4 * j + l4)));
+        if (__builtin_expect(i >= n_new, 1)) {
+            const bool one_page = (2 * (t_base + i) + 1) * MS_PAGE_SIZE >= L;   // the tile's second page does not exist
+            const char* base_a = wave_uniform(pool + (size_t)(uint32_t)p.a * page_bytes + part * MS_PAGE_SIZE * kD * 2);
+            const char* base_b = wave_uniform(pool + (size_t)(uint32_t)(one_page ? p.a : p.b) * page_bytes + part * MS_PAGE_SIZE * kD * 2);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) load_lds_1k<false>(lds + 1024u * j, off[j & 3], j < 4 ? base_a : base_b);
+        } else {   // the step's own rows; past their end the last one again
+            const char* base = wave_uniform(reinterpret_cast<const char*>((part ? a.v_new : a.k_new) + ((size_t)b * a.n_q * a.n_kv_heads + g) * kD));
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                load_lds_1k<false>(lds + 1024u * j, (uint32_t)(min(kTile * (new_0 + i) + 4 * j + l4, a.n_q - 1) * a.n_kv_heads * kD * 2) + (off[j & 3] & (kD * 2 - 1)), base);
+        }
+    };
+    auto issue = [&](int i, const Pages& p) {
+        if (i >= items) return;
+        if (!paired || rb == 0) issue_part(i, p, 0);
+        if (!paired || rb == 1) issue_part(i, p, 1);
+    };
+    issue(ts, p0);
+    int in_flight = ts < items ? tile_loads : 0;   // loads behind the set-up's
+    if (!a.late) {
+        issue(ts + kSplitStreams, next);
+        in_flight += ts + kSplitStreams < items ? tile_loads : 0;
+    }
+    wait_loads_left(in_flight);   // the query rows and the frequencies
+    const float inv_f = reinterpret_cast<const float*>(freq)[lane];
+    const int waves = kSplitStreams * a.wg_blocks;
+    for (int i = c_lo + w; i <= c_hi; i += waves) {   // cos/sin of the position ids
+        const int p = pid;
+        pid = uniform_load(a.pos + b * a.n_q + min(i + waves, a.n_q - 1));
         float sn, c;
-        sincos_reduced((float)uniform_load(a.pos + b * a.n_q + i) * inv_f, &sn, &c);
+        sincos_reduced((float)p * inv_f, &sn, &c);
         cs[i * 64 + lane] = make_float2(c, sn);
     }
+    if (has_new) wait_loads_left(in_flight > tile_loads ? tile_loads : 0);   // new keys are rotated in their place, like the query rows
     lds_barrier();
-    // element i pairs with i + 64: register kk with kk + 4
-    auto rotate = [&](uint4 (&r)[8], const float2* f, float scale) {
+    bf16x8_t x[8];   // the rotated rows as an operand: lane = row, d = 16 kk + 8 hf .. + 8
+    {
+        const int r = 8 * ts + (lane >> 3), c = lane & 7;   // a thread rotates eight pairs of one row
+        const int at_lo = r * kD * 2 + 16 * (c ^ (r & 15)), at_hi = r * kD * 2 + 16 * ((c + 8) ^ (r & 15));
+        auto rotate_row = [&](char* tile, int i) {
+            uint4 lo = *reinterpret_cast<const uint4*>(tile + at_lo), hi = *reinterpret_cast<const uint4*>(tile + at_hi);
+            rotate_chunks(lo, hi, cs + i * 64 + 8 * c);
+            *reinterpret_cast<uint4*>(tile + at_lo) = lo;
+            *reinterpret_cast<uint4*>(tile + at_hi) = hi;
+        };
+        rotate_row(rows + rb * rows_step, query_of(32 * rb + r));
+        for (int n = rb; n < n_new; n += a.wg_blocks) rotate_row(smem + n * kSplitStreamBytes, min(kTile * (new_0 + n) + r, a.n_q - 1));
+        lds_barrier();
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            const uint32_t w0[4] = {r[kk].x, r[kk].y, r[kk].z, r[kk].w};
-            const uint32_t w1[4] = {r[kk + 4].x, r[kk + 4].y, r[kk + 4].z, r[kk + 4].w};
-            uint32_t y0[4], y1[4];
+        for (int kk = 0; kk < 8; ++kk)
+            x[kk] = *reinterpret_cast<const bf16x8_t*>(rows + rb * rows_step + l32 * kD * 2 + ((16 * (hf ^ l16)) ^ (32 * kk)));
+        if (__builtin_expect(a.negate, 0)) {   // the maximum is taken before the scale
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float r0[2], r1[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const float a0 = h ? __uint_as_float(w0[e] & 0xffff0000u) : __uint_as_float(w0[e] << 16);
-                    const float a1 = h ? __uint_as_float(w1[e] & 0xffff0000u) : __uint_as_float(w1[e] << 16);
-                    const float2 c = f[16 * kk + 8 * hf + 2 * e + h];
-                    r0[h] = (a0 * c.x - a1 * c.y) * scale;
-                    r1[h] = (a1 * c.x + a0 * c.y) * scale;
-                }
-                y0[e] = pack_bf16x2(r0[0], r0[1]);
-                y1[e] = pack_bf16x2(r1[0], r1[1]);
-            }
-            r[kk] = make_uint4(y0[0], y0[1], y0[2], y0[3]);
-            r[kk + 4] = make_uint4(y1[0], y1[1], y1[2], y1[3]);
+            for (int kk = 0; kk < 8; ++kk) x[kk] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4_t, x[kk]) ^ 0x80008000u);
         }
-    };
-    rotate(x, cs + qi * 64, a.scale_log2);   // (rows past the chunk's: computed like row 0 of it, not stored)
+    }
+    if (a.late) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();   // the set-up's place is free
+        asm volatile("" ::: "memory");
+        issue(ts + kSplitStreams, next);
+    }
 
+    const bool live = 32 * rb + l32 < n_rows;   // this lane's query row
+    const int qi = query_of(32 * rb + l32);
     float m = -INFINITY, l = 0.f;   // row maximum in use (log2 units); this lane's share of the row sum
     f32x16_t o[4];                  // O^T accumulators per d block; lane column = query row
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
-    char* vl = smem + w * kVTileBytes;
-    char* vwrite = vl + (lane >> 4) * kVRowBytes + l16 * 16;
-    const char* vbase = vl + (4 * hf + (l16 >> 2)) * kVRowBytes + (16 * ((lane >> 4) & 1) + 4 * (l16 & 3)) * 2;   // see the streaming kernel
 
-    auto qk = [&](f32x16_t& s) {
+    // ---- a round: a tile for every stream ----
+    const char* k_op = ring + l32 * kD * 2;
+    const int k_at = 16 * (hf ^ l16);
+    // V operand of 16 tokens x 32 d: see the streaming kernel; rows of a lane are l16 / 4 modulo 4
+    char* v_op = ring + kSplitTileBytes + (4 * hf + (l16 >> 2)) * kD * 2 + 32 * (l4 & 1) + 8 * (l16 & 3);
+    for (int i = ts, i0 = 0; i0 < items; i += kSplitStreams, i0 += kSplitStreams) {
+        const int stage = (i0 >> 2 & 1) * kSplitStageBytes;
+        if (i0 == 0 && i + kSplitStreams < items) wait_loads_left(tile_loads);   // the second tile has been asked for
+        else wait_loads<0>();
+        if (paired) {
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        if (i0 > 0) issue(i + kSplitStreams, next);   // into the stage of the round before
+        if (i >= items) continue;
+        const int tile = t_base + i, valid = i >= n_new ? L - tile * kTile : a.n_q - kTile * (new_0 + i);   // tokens of the tile
+        bf16x8_t kt[8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        for (int kk = 0; kk < 8; ++kk) kt[kk] = *reinterpret_cast<const bf16x8_t*>(k_op + stage + (k_at ^ (32 * kk)));
+        f32x16_t s;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, k[kk]), __builtin_bit_cast(bf16x8_t, x[kk]), s, 0, 0, 0);
-    };
-    auto weigh = [&](f32x16_t& s) {   // scores to softmax weights, and what a new maximum does to the state
+        for (int j = 0; j < 16; ++j) s[j] = 0.f;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        next = pages(i + 2 * kSplitStreams);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[kk], x[kk], s, 0, 0, 0);
+        if (__builtin_expect(i < n_new, 0)) {
+            int ctx = a.ctx_new ? a.ctx_new[b * a.n_q + qi] : (qi < a.n_verify ? qi : a.n_verify);
+            ctx = live ? min(ctx, a.n_q) : 0;
+            const int tok0 = kTile * (new_0 + i);
+            mask_inflight(s, ctx - tok0, qi - tok0, hf);
+        } else if (__builtin_expect(valid < kTile, 0)) {
+            mask_tail(s, valid, hf);
+        }
+        // raw products to softmax weights, and what a new maximum does to the state
         float mx = s[0];
 #pragma unroll
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * a.scale_log2;
         const bool grow = mx > m + kRescaleThreshold;
         if (__any(grow)) {
-            const float f = grow ? __builtin_amdgcn_exp2f(m - mx) : 1.f;   // 2^-inf = 0 on the first tile
+            if (i0 > 0) {
+                const float f = grow ? __builtin_amdgcn_exp2f(m - mx) : 1.f;   // 2^-inf = 0: nothing seen so far
+                l *= f;
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) o[db][j] *= f;
+            }
             m = grow ? mx : m;
-            l *= f;
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[db][i] *= f;
         }
         const float mu = m == -INFINITY ? 0.f : m;   // nothing visible to the row so far: its weights are 2^-inf
         float sum = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            s[i] = __builtin_amdgcn_exp2f(s[i] - mu);
-            sum += s[i];
+        for (int j = 0; j < 16; ++j) {
+            s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], a.scale_log2, -mu));
+            sum += s[j];
         }
         l += sum;
-    };
-    auto pv = [&](const f32x16_t& s) {
+        if (__builtin_expect(valid < kTile, 0)) {   // rows past the end become zeros (stale pool bytes may be NaN; both waves of a stream write them)
+            for (int r = (valid & ~3) + l4; r < kTile; r += 4)
+                if (r >= valid) *reinterpret_cast<uint4*>(ring + stage + kSplitTileBytes + r * kD * 2 + 16 * l16) = make_uint4(0, 0, 0, 0);
+            wave_lds_fence();
+        }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             uint4 pw;
@@ -216,92 +344,101 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
             pw.w = pack_bf16x2(s[8 * ks + 6], s[8 * ks + 7]);
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
-                const char* p0 = vbase + (16 * ks) * kVRowBytes + 64 * db;
-                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p0));
-                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p0 + 8 * kVRowBytes));
+                char* p = v_op + stage + 64 * (db ^ (l16 >> 2)) + 16 * ks * kD * 2;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p);
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p + 8 * kD * 2));
                 const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, both), __builtin_bit_cast(bf16x8_t, pw), o[db], 0, 0, 0);
             }
         }
-    };
-
-    for (; t < t_hi; t += 2) {
-        const bool cached = t < n_cache;
-        const int tok0 = kTile * (t - n_cache);              // in-flight tile: its first token
-        const int valid = cached ? L - t * kTile : a.n_q - tok0;
-        if (!cached) rotate(k, cs + min(tok0 + l32, a.n_q - 1) * 64, 1.f);   // the step's own keys come as they are
-        f32x16_t s;
-        qk(s);
-        const int tn = min(t + 2, n_tiles - 1);
-        load_k_tile(tn, pa_n, pb_n);
-        if (cached) {
-            if (valid < kTile) mask_tail(s, valid, hf);
-        } else {
-            int ctx = a.ctx_new ? a.ctx_new[b * a.n_q + qi] : (qi < a.n_verify ? qi : a.n_verify);
-            ctx = live ? min(ctx, a.n_q) : 0;
-            mask_inflight(s, ctx - tok0, qi - tok0, hf);
-        }
-        weigh(s);
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr)   // rows past the end become zeros (stale pool bytes may be NaN)
-            *reinterpret_cast<uint4*>(vwrite + 4 * rr * kVRowBytes) = 4 * rr + (lane >> 4) < valid ? v[rr] : make_uint4(0, 0, 0, 0);
-        load_v_tile(tn, pa_n, pb_n);
-        pages(t + 4, pa_n, pb_n);
-        pv(s);
     }
 
-    // ---- the two waves of a row block: each keeps two of the four d blocks and hands the other two over ----
+    // ---- of a row block's four waves each keeps one of the d blocks and hands the others over: block db to stream db's, at
+    // (db - ts - 1) % 4 ----
+    if (paired) lds_barrier();   // the other wave of the stream is done with its stages
     l += __shfl_xor(l, 32, 64);   // the half-waves hold the two halves of a row's sum
-    float* mine = reinterpret_cast<float*>(smem + w * kVTileBytes);
-    const float* other = reinterpret_cast<const float*>(smem + (w ^ 2) * kVTileBytes);
+    auto handed = [&](int stream) { return reinterpret_cast<float*>(smem + stream * kSplitStreamBytes + rb * kSplitStageBytes); };
+    {
+        float* mine = handed(ts);
 #pragma unroll
-    for (int d2 = 0; d2 < 2; ++d2) {
+        for (int db = 0; db < 4; ++db) {
+            if (db == ts) continue;
+            float* p = mine + ((db - ts + 3) & 3) * 16 * 64;
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+                *reinterpret_cast<float4*>(p + (i4 * 64 + lane) * 4) = make_float4(o[db][4 * i4], o[db][4 * i4 + 1], o[db][4 * i4 + 2], o[db][4 * i4 + 3]);
+        }
+        mine[3 * 16 * 64 + lane] = m;
+        mine[3 * 16 * 64 + 64 + lane] = l;
+    }
+    lds_barrier();
+    float f[kSplitStreams], m_all = m, l_all = 0.f;   // in the streams' order: every wave sums alike
+#pragma unroll
+    for (int u = 0; u < kSplitStreams; ++u) {
+        f[u] = handed(u)[3 * 16 * 64 + lane];
+        m_all = fmaxf(m_all, f[u]);
+    }
+    const float mu = m_all == -INFINITY ? 0.f : m_all;
+#pragma unroll
+    for (int u = 0; u < kSplitStreams; ++u) {
+        f[u] = __builtin_amdgcn_exp2f(f[u] - mu);   // a wave without tiles: 2^-inf = 0
+        l_all += handed(u)[3 * 16 * 64 + 64 + lane] * f[u];
+    }
+    if (!live) return;
+    float4 r[4];
+#pragma unroll
+    for (int u = 0; u < kSplitStreams; ++u) {
+        const float* p = handed(u) + ((ts - u + 3) & 3) * 16 * 64;
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
-            const int i = 4 * i4;
-            const float4 give = ts == 0 ? make_float4(o[2 + d2][i], o[2 + d2][i + 1], o[2 + d2][i + 2], o[2 + d2][i + 3])
-                                        : make_float4(o[d2][i], o[d2][i + 1], o[d2][i + 2], o[d2][i + 3]);
-            *reinterpret_cast<float4*>(mine + ((d2 * 4 + i4) * 64 + lane) * 4) = give;
+            float4 v;
+            if (u == ts) {
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+                    if (db == ts) v = make_float4(o[db][4 * i4], o[db][4 * i4 + 1], o[db][4 * i4 + 2], o[db][4 * i4 + 3]);
+            } else {
+                v = *reinterpret_cast<const float4*>(p + (i4 * 64 + lane) * 4);
+            }
+            if (u == 0) r[i4] = make_float4(v.x * f[0], v.y * f[0], v.z * f[0], v.w * f[0]);
+            else r[i4] = make_float4(r[i4].x + v.x * f[u], r[i4].y + v.y * f[u], r[i4].z + v.z * f[u], r[i4].w + v.w * f[u]);
         }
     }
-    mine[32 * 64 + lane] = m;
-    mine[33 * 64 + lane] = l;
-    lds_barrier();
-    const float m2 = other[32 * 64 + lane], l2 = other[33 * 64 + lane];
-    const float m_all = fmaxf(m, m2), mu = m_all == -INFINITY ? 0.f : m_all;
-    const float f1 = __builtin_amdgcn_exp2f(m - mu), f2 = __builtin_amdgcn_exp2f(m2 - mu);   // a wave without tiles: 2^-inf = 0
-    const float l_all = l * f1 + l2 * f2;
-    const float norm = a.n_splits == 1 ? 1.f / l_all : 1.f;
-    float* part = a.ws + ((size_t)((size_t)blockIdx.z * a.n_splits + split) * a.n_kv_heads + g) * kPartFloats;
-    uint16_t* op = a.out + (((size_t)b * a.n_q + qi) * a.n_q_heads + g * a.group + (live ? row % a.group : 0)) * kD;
+    if (a.n_splits > 1) {
+        const size_t block = (size_t)b * a.n_blocks + r0 / kSplitRows + rb;
+        float* part = a.ws + ((block * a.n_splits + split) * a.n_kv_heads + g) * kSplitPartFloats;
+        float* p = part + 2 * kSplitRows + (ts * 4 * 64 + lane) * 4;
+        // Partials left in L2 are written back at the launch's end: past the caches 64 queries over 2000 tokens take 17.0 us per call
+        // instead of 17.7, but decode steps longer.  (The empty statements keep the compiler from making one plain store of the two.)
+        if (paired && a.n_q > kSplitDecodeQueries) {
+            asm volatile("");
 #pragma unroll
-    for (int d2 = 0; d2 < 2; ++d2)
+            for (int i4 = 0; i4 < 4; ++i4) __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, r[i4]), reinterpret_cast<u32x4_t*>(p + i4 * 64 * 4));
+            asm volatile("");
+        } else {
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-            const int db = 2 * ts + d2, i = 4 * i4;
-            const float4 own = ts == 0 ? make_float4(o[d2][i], o[d2][i + 1], o[d2][i + 2], o[d2][i + 3])
-                                       : make_float4(o[2 + d2][i], o[2 + d2][i + 1], o[2 + d2][i + 2], o[2 + d2][i + 3]);
-            const float4 got = *reinterpret_cast<const float4*>(other + ((d2 * 4 + i4) * 64 + lane) * 4);
-            const float4 r = make_float4((own.x * f1 + got.x * f2) * norm, (own.y * f1 + got.y * f2) * norm, (own.z * f1 + got.z * f2) * norm,
-                                         (own.w * f1 + got.w * f2) * norm);
-            if (a.n_splits > 1) {
-                *reinterpret_cast<float4*>(part + 2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4) = r;
-            } else if (live) {
-                uint2 pk;
-                pk.x = pack_bf16x2(r.x, r.y);
-                pk.y = pack_bf16x2(r.z, r.w);
-                *reinterpret_cast<uint2*>(op + 32 * db + 8 * i4 + 4 * hf) = pk;
-            }
+            for (int i4 = 0; i4 < 4; ++i4) *reinterpret_cast<float4*>(p + i4 * 64 * 4) = r[i4];
         }
-    if (a.n_splits > 1 && ts == 0 && hf == 0) {
-        part[row] = m_all;
-        part[kRows + row] = l_all;
+        if (ts == 0 && hf == 0) {
+            part[l32] = m_all;
+            part[kSplitRows + l32] = l_all;
+        }
+        return;
+    }
+    const float inv = 1.f / l_all;
+    const int head = r0 + 32 * rb + l32 - qi * a.group;
+    uint16_t* op = a.out + (((size_t)b * a.n_q + qi) * a.n_q_heads + g * a.group + head) * kD + 32 * ts + 4 * hf;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+        uint2 pk;
+        pk.x = pack_bf16x2(r[i4].x * inv, r[i4].y * inv);
+        pk.y = pack_bf16x2(r[i4].z * inv, r[i4].w * inv);
+        *reinterpret_cast<uint2*>(op + 8 * i4) = pk;
     }
 }
 
 // Folds the shares' partials in their order, normalises and writes the bf16 rows.  A workgroup takes one
-// 32-row x 32-column block of a (sequence, chunk, KV head); a thread four columns of a row, with kBatch
-// partials requested in one memory round trip.  Bound by those round trips: 26 shares (one sequence of
+// 32-row x 32-column block of a (sequence, row block, KV head); a thread four columns of a row, with kBatch
+// partials requested in one memory round trip.  Bound by those round trips (the figures: shares of 64 rows, four waves): 26 shares (one sequence of
 // 4096 tokens, 7 queries) in four trips of 8 or one of 32: 17.4 / 16.7 us per call of both launches (by blocks).
 // As long as there is a compute unit for each, a workgroup of one wave takes a quarter of a block's columns, so that
 // the partials come in through more compute units: one sequence of 4096 tokens 4.9 / 4.1 us for this launch; us per
@@ -310,14 +447,14 @@ __global__ __launch_bounds__(kSplitThreads, 2) void pv_attn_mfma_split(SplitArgs
 // 2000 17.1 / 18.2, 64 queries over 2 x 1000 18.6 / 19.3.
 template <int kBatch>
 __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
-    const int quarter = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), rb = quarter >> 4, db = quarter >> 2 & 3;
-    const int g = blockIdx.y, b = blockIdx.z / a.n_chunks, chunk = blockIdx.z % a.n_chunks;
-    const int lane = threadIdx.x & 63, i4 = quarter & 3, hf = lane >> 5, row = 32 * rb + (lane & 31);
-    const int q0 = chunk * a.per_chunk, n_rows = min(a.per_chunk, a.n_q - q0) * a.group;
-    if (row >= n_rows) return;
-    const size_t stride = (size_t)a.n_kv_heads * kPartFloats;
-    const float* p0 = a.ws + ((size_t)blockIdx.z * a.n_splits * a.n_kv_heads + g) * kPartFloats;
-    const int at = 2 * kRows + (((rb * 4 + db) * 4 + i4) * 64 + lane) * 4;
+    const int quarter = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), db = quarter >> 2, i4 = quarter & 3;
+    const int g = blockIdx.y, b = div_by(blockIdx.z, a.blocks_inv), r0 = ((int)blockIdx.z - b * a.n_blocks) * kSplitRows;
+    const int lane = threadIdx.x & 63, hf = lane >> 5, row = lane & 31;
+    if (r0 + row >= a.n_q * a.group) return;
+    const int qi = div_by(r0 + row, a.group_inv), head = r0 + row - qi * a.group;
+    const size_t stride = (size_t)a.n_kv_heads * kSplitPartFloats;
+    const float* p0 = a.ws + ((size_t)blockIdx.z * a.n_splits * a.n_kv_heads + g) * kSplitPartFloats;
+    const int at = 2 * kSplitRows + ((db * 4 + i4) * 64 + lane) * 4;
     float m = -INFINITY, l = 0.f;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = 0; s0 < a.n_splits; s0 += kBatch) {
@@ -327,7 +464,7 @@ __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
         for (int s = 0; s < kBatch; ++s) {   // past the end: the last one again, without weight
             const float* p = p0 + min(s0 + s, a.n_splits - 1) * stride;
             pm[s] = p[row];
-            pl[s] = p[kRows + row];
+            pl[s] = p[kSplitRows + row];
             px[s] = *reinterpret_cast<const float4*>(p + at);
         }
         float mn = m;
@@ -352,64 +489,93 @@ __global__ __launch_bounds__(256) void pv_attn_mfma_fold(SplitArgs a) {
     uint2 pk;
     pk.x = pack_bf16x2(acc.x * inv, acc.y * inv);
     pk.y = pack_bf16x2(acc.z * inv, acc.w * inv);
-    *reinterpret_cast<uint2*>(a.out + (((size_t)b * a.n_q + q0 + row / a.group) * a.n_q_heads + g * a.group + row % a.group) * kD + 32 * db + 8 * i4 + 4 * hf) = pk;
+    *reinterpret_cast<uint2*>(a.out + (((size_t)b * a.n_q + qi) * a.n_q_heads + g * a.group + head) * kD + 32 * db + 8 * i4 + 4 * hf) = pk;
 }
 
-constexpr int kSplitDecodeQueries = 16;   // a decode step: the streaming kernel could take it
+static int split_blocks(int group, int n_q) { return (n_q * group + kSplitRows - 1) / kSplitRows; }
 static int split_chunks(int group, int n_q) { return (n_q + kRows / group - 1) / (kRows / group); }
 
-// Tiles per share; 0: the call belongs on the streaming or the wide kernel.  Measured on 256 compute
-// units, us per call with the second launch against the kernel that would take the call otherwise
-// (7 queries, 28 / 4 heads unless said):
-//   decode  1 x 1000 tokens 15 / 18, 1 x 4096 17 / 21, 1 x 16000 23 / 32, 4 x 4096 19 / 24, 8 x 4096
-//           26 / 29, 16 x 2048 26 / 26; 32 x 2048 39 / 35, 16 x 8000 62 / 54.  The streaming kernel's last
-//           workgroup folds 256 / pairs shares by itself, this kernel's waves read the cache once per row
-//           block: the fewer the (sequence, KV head) pairs, the more (tile, KV head) pairs it takes until
-//           the bytes count.  9 queries: 4 pairs 1 x 96000 57 / 64, 1 x 128000 71 / 74; 8 pairs 2 x 40000 47 /
-//           51, 2 x 64000 68 / 65; 16 pairs 4 x 16000 38 / 40, 4 x 20000 46 / 46, 4 x 24000 52 / 50; 24 pairs
-//           3 x 10000 38 / 37; 32 pairs 8 x 6000 31 / 33, 8 x 8000 38 / 38; 64 pairs 16 x 3000 32 / 31: the
-//           break-even falls with the root of the pairs.  Below four shares per pair the streaming
-//           kernel's eight waves per share hide more (32 x 500 tokens: 20 / 19)
-//   wide    64 queries: 1 x 100 16 / 35, 1 x 2000 19 / 140, 4 x 2000 35 / 109, 8 x 4000 87 / 114, 32 / 8
-//           heads 8 x 4000 91 / 97; 41 queries: 8 x 4000 68 / 100.  2.7 ns per (tile, KV head, chunk)
-//           there; the wide kernel reads the cache once and is ahead from about 32768 of them on
-// Shares are sized by the longest sequence, those of shorter ones end early, and nothing levels that: a
-// decode batch counts with the tiles it would have if all sequences were that long, a wide step (whose
-// throughput goes by the tiles there are) may have shares of up to 160 tiles.  us, this kernel / the other:
-//   decode  9 queries, 28 / 4 heads: 12000 + 15 x 100 tokens 75 / 30, 8 x 500 .. 8000 35 / 32, 16 x 500 ..
-//           4000 29 / 29, 4 x 1000 .. 16000 35 / 38, 8 x 200 .. 5000 26 / 29, 16 x 100 .. 1600 22 / 29; 32 / 8
-//           heads: 8000 + 7 x 64 55 / 28, 2000 + 7 x 64 24 / 39
-//   wide    one long sequence and 7 of 64 tokens, 64 queries: 5000 tokens (159 tiles) 105 / 134, 7000 (221)
-//           142 / 130, 9000 179 / 127; 32 / 8 heads, 41 queries: 5000 107 / 112, 6000 (190) 125 / 109
+// How a call is divided; false: it belongs on the streaming or the wide kernel.  Measured on 256 compute units, us per call
+// with the second launch / on the kernel that would take the call otherwise (q: queries; 28 / 4 heads and 32 / 8 heads):
+//   few tiles  up to 12 with the new ones stay in one workgroup per (sequence, row blocks, KV head), whatever their number: 24 x
+//           200 tokens, 7 q 9.7 / 39.5 and 9.6 / 38.5; 64 x 200, 9 q 13.7 / 40.8 and 26.6 / 42.4; 64 x 330 16.6 / 32.1
+//           and 31.0 / 39.8
+//   decode, up to 64 (sequence, KV head) pairs: by the (tile, KV head) pairs times the root of the pairs.  The streaming kernel's last
+//           workgroup folds 256 / pairs shares by itself, this kernel's waves read the cache once per group of row
+//           blocks: the fewer the pairs, the more tiles it takes until the bytes count.  9 q, 28 / 4 heads: 8 x 8192 tokens 30 / 37, 2 x
+//           64000 58 / 61, 16 x 4096 32 / 34, 4 x 32768 59 / 57, 16 x 8192 60 / 53; 32 / 8 heads: 16 x 4096 56 / 51, 4 x 16384 58 / 54
+//   decode, more pairs: while everything is one round of workgroups and short.  9 q, 28 / 4 heads: 24 x 500 12.3 / 19.0, 24 x 1000 17.5 /
+//           21.9, 32 x 1000 21.4 / 24.2, 48 x 1500 37.1 / 41.1; 32 / 8 heads: 16 x 1000 20.5 / 23.8, 32 x 1000 32.0 / 33.2; 7 q
+//           (one row block): 24 x 1500 30.6 / 38.7, but 64 x 700 (two rounds of workgroups) 65 / 50
+//   wide    64 q: 1 x 2000 tokens 17.7 / 140, 8 x 4000 60 / 114 and 65 / 97, 8 x 6000 85 / 120 and 100 / 118, 2 x 30000 105 /
+//           184 and 113 / 153; two rounds of workgroups 16 x 4000 157 / 123 and 182 / 142
+// Shares are sized by the longest sequence, those of shorter ones end early, and nothing levels that: a decode batch
+// counts with the tiles it would have if all sequences were that long, a wide step whose lengths differ has shares of up to
+// 160 tiles, and the further half of either limit is for lengths that fill three quarters of the shares.  (With two row blocks of two
+// waves each in every workgroup: decode 12000 + 15 x 100 tokens 75 / 30, 8 x 500 .. 8000 35 / 32; wide one of 5000 tokens (159 tiles) and
+// 7 of 64 105 / 134, one of 7000 142 / 130.)
 constexpr long kSplitMaxTiles = 32768, kSplitMaxPairs = 64, kSplitMaxWideTiles = 32768;   // decode: over the root of the pairs
-constexpr long kSplitMaxWideShare = 160;
-int split_share_tiles(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, int* n_splits) {
-    const long chunks = split_chunks(c->group, n_q), n_new = (n_q + kTile - 1) / kTile;
+constexpr long kSplitMaxWideShare = 160, kSplitMostShares = 32, kSplitMostAlone = 12;
+bool split_plan(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_partials, SplitPlan* p) {
+    const long chunks = split_chunks(c->group, n_q);
     long tiles = 0, longest = 0;
     for (int b = 0; b < B; ++b) {
         const long t = (lens[b] + kTile - 1) / kTile;
         tiles += t;
         longest = std::max(longest, t);
     }
-    const long base = B * chunks * c->d.n_kv_heads;   // workgroups per share
+    const long blocks = split_blocks(c->group, n_q), n_new = (n_q + kTile - 1) / kTile, heads = c->d.n_kv_heads, cus = c->n_cus;
     const bool wide = chunks > 1 || n_q > kSplitDecodeQueries;
-    const long work = (wide ? tiles : B * longest) * c->d.n_kv_heads * chunks;
-    if (!wide && (base > kSplitMaxPairs || work > kSplitMaxTiles || work * work * base > kSplitMaxTiles * kSplitMaxTiles)) return 0;
-    if (wide && work > kSplitMaxWideTiles) return 0;
-    // one workgroup per compute unit; two where one would leave a quarter of the chip idle
-    const long per = longest + n_new;
-    long s = std::max(1L, c->n_cus / base);
-    if (4 * s * base < 3 * c->n_cus) s = std::max(1L, 2 * c->n_cus / base);
-    s = std::min(s, (per + 1) / 2);                  // a tile for every wave
-    s = std::min(s, std::max(32L, per / 8));         // more partials than that cost the second launch what the first gains
-    s = std::min(s, std::max(1L, (long)ws_partials / (B * chunks)));
-    const long share = (per + s - 1) / s;
-    if (wide && share > kSplitMaxWideShare) return 0;
-    *n_splits = (int)((per + share - 1) / share);
-    return (int)share;
+    const bool alone = longest + n_new <= kSplitMostAlone, level = 4 * tiles >= 3 * B * longest;
+    const long room = (long)(ws_partials * kPartFloats / kSplitPartFloats) / (B * blocks);   // partials of a row block and KV head that the workspace holds
+    const long most = std::min(std::max(kSplitMostShares, longest / 8), room);               // more than that cost the second launch what the first gains
+    // Row blocks a workgroup.  Decode: one if the workgroups of a share then fit the chip, us with one / two, 28 / 4 heads: 4 x 4096 tokens, 7
+    // queries 15.4 / 17.8, 8 x 8192 33.7 / 33.8, 32 x 500, 9 queries 16.2 / 19.1 (24 x 500 at 32 / 8 heads, 384 workgroups: 19.9 / 16.8), unless
+    // whole shares leave a fifth of the chip idle over many tiles (12 x 4096 32.2 / 28.5).  Wide steps: one as long as that gives every tile a wave.
+    const long ones = B * blocks * heads;
+    if (blocks == 1) p->wg_blocks = 1;
+    else if (wide) p->wg_blocks = ones * std::min(most, (longest + kSplitStreams - 1) / kSplitStreams) > 2 * cus ? 2 : 1;
+    else p->wg_blocks = ones > cus || (longest > 64 && 5 * (cus / ones * ones) < 4 * cus) ? 2 : 1;
+    const long groups = B * ((blocks + p->wg_blocks - 1) / p->wg_blocks) * heads;   // workgroups per share
+    const long pairs = B * chunks * heads, work = (wide ? tiles : B * longest) * heads * chunks;
+    if (wide) {
+        if (work > (level && groups <= cus ? 2 : 1) * kSplitMaxWideTiles) return false;
+    } else if (pairs <= kSplitMaxPairs) {
+        if (!alone && (work > kSplitMaxTiles || work * work * pairs > (level ? 2 : 1) * kSplitMaxTiles * kSplitMaxTiles)) return false;
+    } else if (!alone) {
+        const bool one_share = 4 * groups >= 3 * cus || blocks == 1;
+        if (!level || groups > cus || longest > (one_share ? 48 : 24)) return false;
+    }
+    auto share_of = [&](long extra) {   // shares of the cached tiles, `extra` workgroups of a group being for something else
+        long n = std::max(1L, std::min(most, cus / groups) - extra);
+        n = std::max(1L, std::min(n, (longest + kSplitStreams - 1) / kSplitStreams));
+        return std::max(1L, (longest + n - 1) / n);
+    };
+    // The new tiles go in front of the last share's cached ones or have shares of their own (n_new more partials): what
+    // has the shorter longest share (a new tile of two row blocks counted twice), more workgroups than compute units counting half as much again.
+    const long front = share_of(0), n_front = std::max(1L, (longest + front - 1) / front), own = share_of(n_new), n_own = (longest + own - 1) / own + n_new;
+    const long most_front = std::max(front, longest - (n_front - 1) * front + p->wg_blocks * n_new);
+    if (alone || n_own > most || 2 * most_front <= (groups * n_own > cus && groups * n_front <= cus ? 3 : 2) * own) {
+        p->share_tiles = (int)(alone ? std::max(1L, longest) : front);
+        p->new_shares = 1;
+        p->n_splits = (int)std::max(1L, (longest + p->share_tiles - 1) / p->share_tiles);
+        p->n_lean = p->n_splits - 1;
+    } else {
+        p->share_tiles = (int)own;
+        p->new_shares = (int)n_new;
+        p->n_splits = (int)n_own;
+        p->n_lean = (int)(n_own - n_new);
+    }
+    if (wide && !level && p->share_tiles > kSplitMaxWideShare) return false;
+    const long units = p->n_splits * heads * B, n_groups = (blocks + p->wg_blocks - 1) / p->wg_blocks, most_by = std::max(n_groups * n_groups / 8 + 1, std::max((long)p->n_splits, heads));
+    if (units * most_by >= 1l << 20) return false;   // div_by
+    p->late = split_lds_bytes(p->wg_blocks, n_q, false) > kSplitMostLds;
+    p->lds_bytes = split_lds_bytes(p->wg_blocks, n_q, p->late);
+    return true;
 }
 
-int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, int share_tiles, int n_splits, hipStream_t stream) {
+int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, const SplitPlan& p, hipStream_t stream) {
+    const int n_splits = p.n_splits;
     SplitArgs a;
     a.pool_layer = (const uint16_t*)ga.pool_layer;
     a.d_pt = ga.d_pt;
@@ -428,31 +594,42 @@ int launch_split(ms_cache* c, const AttnArgs& ga, const BatchMeta& bm, int B, in
     a.n_kv_heads = ga.n_kv_heads;
     a.group = ga.group;
     a.max_pages = ga.max_pages;
-    a.per_chunk = kRows / ga.group;
-    a.n_chunks = split_chunks(ga.group, ga.n_q);
+    a.n_blocks = split_blocks(ga.group, ga.n_q);
+    a.group_inv = inverse_of(ga.group);
+    a.blocks_inv = inverse_of(a.n_blocks);
+    a.wg_blocks = p.wg_blocks;
+    a.n_groups = (a.n_blocks + p.wg_blocks - 1) / p.wg_blocks;
+    a.new_shares = p.new_shares;
+    a.n_lean = p.n_lean;
+    a.late = p.late;
+    a.groups_inv = inverse_of(a.n_groups);
+    a.units = n_splits * ga.n_kv_heads * B;
+    a.splits_inv = inverse_of(n_splits);
+    a.heads_inv = inverse_of(ga.n_kv_heads);
     a.n_splits = n_splits;
-    a.share_tiles = share_tiles;
+    a.share_tiles = p.share_tiles;
     a.page_elems = ga.page_elems;
-    a.scale_log2 = ga.scale * 1.44269504088896340736f;
+    a.scale_log2 = fmaxf(fabsf(ga.scale * 1.44269504088896340736f), FLT_MIN);   // (masked scores are -infinity times this)
+    a.negate = ga.scale < 0.f;
     for (int b = 0; b < B; ++b) a.seq[b] = bm.seq[b];
     for (int b = B; b < MS_MAX_BATCH; ++b) a.seq[b] = 0;
     c->launches++;
     c->last_attention = n_splits > 1 ? "pv_attn_mfma_split+pv_attn_mfma_fold" : "pv_attn_mfma_split";
-    hipLaunchKernelGGL(pv_attn_mfma_split, dim3(n_splits, a.n_kv_heads, B * a.n_chunks), dim3(kSplitThreads), split_lds_bytes(a.n_q), stream, a);
+    hipLaunchKernelGGL(pv_attn_mfma_split, dim3(a.units * a.n_groups), dim3(64 * kSplitStreams * p.wg_blocks), p.lds_bytes, stream, a);
     if (n_splits > 1) {
         c->launches++;
-        const int waves = 32l * a.n_kv_heads * B * a.n_chunks <= c->n_cus ? 1 : 4;
-        const dim3 grid(32 / waves, a.n_kv_heads, B * a.n_chunks), block(64 * waves);
+        const int waves = 16l * a.n_kv_heads * B * a.n_blocks <= c->n_cus ? 1 : 4;
+        const dim3 grid(16 / waves, a.n_kv_heads, B * a.n_blocks), block(64 * waves);
         if (n_splits <= 8) hipLaunchKernelGGL(pv_attn_mfma_fold<8>, grid, block, 0, stream, a);
         else if (n_splits <= 16) hipLaunchKernelGGL(pv_attn_mfma_fold<16>, grid, block, 0, stream, a);
-        else hipLaunchKernelGGL(pv_attn_mfma_fold<32>, grid, block, 0, stream, a);
+        else hipLaunchKernelGGL(pv_attn_mfma_fold<kSplitMostShares + 2>, grid, block, 0, stream, a);
     }
     MS_HIP_TRY(hipGetLastError());
     return MS_OK;
 }
 
 int split_allow_lds() {
-    MS_HIP_TRY(hipFuncSetAttribute((const void*)pv_attn_mfma_split, hipFuncAttributeMaxDynamicSharedMemorySize, split_lds_bytes(MS_MAX_QUERIES)));
+    MS_HIP_TRY(hipFuncSetAttribute((const void*)pv_attn_mfma_split, hipFuncAttributeMaxDynamicSharedMemorySize, kSplitMostLds));
     return MS_OK;
 }
 

@@ -216,10 +216,6 @@ __device__ __forceinline__ void store_16(void* p, uint4 v, bool wide) {
         *reinterpret_cast<uint4*>(p) = v;
     }
 }
-__device__ __forceinline__ void wave_lds_fence() {   // LDS operations of a wave are carried out in order: only the compiler has to keep them so
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // What a wave does with its 32 kMI rows x 64 columns of fp32 sums.  Accumulator i of a lane: n = n_wave +
 // 32 ni + 8 (i / 4) + 4 hf + i % 4, m = m_wave + 32 mi + l32 (hf = lane / 32, l32 = lane % 32).  lds: kWaveOutBytes.
@@ -781,23 +777,6 @@ constexpr int kMidMaxRows = 256;
 constexpr int kMidBN = 128, kMidBK = 64;
 constexpr int mid_stage_bytes(int rows) { return (rows + kMidBN) * kMidBK * 2; }
 constexpr int mid_stages(int rows) { return 160 * 1024 / mid_stage_bytes(rows) < 8 ? 160 * 1024 / mid_stage_bytes(rows) : 8; }   // the whole LDS
-
-// 64 lanes x 16 bytes from base + voff into LDS at lds .. lds + 1024, lane order.
-template <bool kStream>
-__device__ __forceinline__ void load_lds_1k(uint32_t lds, uint32_t voff, const void* base) {
-    if (kStream) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
-}
-// An address that is the same in every lane, in scalar registers.
-__device__ __forceinline__ const char* wave_uniform(const char* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (const char*)(((uint64_t)hi << 32) | lo);
-}
-template <int kN>
-__device__ __forceinline__ void wait_loads() {   // at most kN of this wave's loads are still on their way; its LDS reads are done
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kN) : "memory");
-}
 
 // At most n steps of kLoads loads are still on their way (kMost: the most there can be).
 template <int kMost, int kLoads>

@@ -35,6 +35,28 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
     return t;
 }
 
+// 64 lanes x 16 bytes from base + voff into LDS at lds .. lds + 1024, lane order.
+template <bool kStream>
+__device__ __forceinline__ void load_lds_1k(uint32_t lds, uint32_t voff, const void* base) {
+    if (kStream) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+}
+// An address that is the same in every lane, in scalar registers.
+__device__ __forceinline__ const char* wave_uniform(const char* p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const char*)(((uint64_t)hi << 32) | lo);
+}
+template <int kN>
+__device__ __forceinline__ void wait_loads() {   // at most kN of this wave's loads are still on their way; its LDS reads are done
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kN) : "memory");
+}
+
+__device__ __forceinline__ void wave_lds_fence() {   // LDS operations of a wave are carried out in order: only the compiler has to keep them so
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Row kernels with a norm (one workgroup per row, the row held in registers between the two passes):
 // threads per row and 8-element chunks per thread; rows of up to 8192 elements.
 constexpr int kNormThreads = 512;

@@ -1,0 +1,72 @@
+"""The share-per-workgroup attention kernel's plan against the oracle: where a call starts to be divided, one and two row blocks
+a workgroup, an odd number of blocks, new tiles in front of the last share's or in shares of their own, the set-up behind the
+second stages (many queries), batches of more pairs than the streaming kernel used to leave to it.  Tolerances of
+test_gpu_parity.py; pool bytes past a sequence's end are NaN."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.test_gpu_attention_paths import compare
+from tests.test_gpu_parity import _mods, pids_for, run_gpu_attention, setup_pair
+
+pytestmark = pytest.mark.gpu
+
+SHARES = [
+    # Hq, Hkv, n_verify, n_foresight, lengths
+    (28, 4, 4, 3, [352]),                                  # 12 tiles with the new one: one workgroup per row block and KV head
+    (28, 4, 4, 3, [353]),                                  # 13: divided
+    (28, 4, 4, 3, [4096, 4096]),                           # whole tiles only, two sequences
+    (28, 4, 5, 4, [10 * i for i in range(20)]),            # 80 (sequence, KV head) pairs, few tiles
+    (32, 8, 5, 4, [690, 700, 710, 720, 690, 700, 710, 700, 690, 700, 690, 700]),   # 96 pairs, 36 rows: a second block of four
+    (28, 4, 10, 0, [3000, 2900]),                          # 70 rows: three blocks
+    (28, 4, 33, 0, [1500]),                                # two new tiles with shares of their own, the second with one token
+    (28, 4, 64, 0, [1504, 200, 1000]),                     # two blocks a workgroup, set-up behind the second stages
+    (7, 1, 64, 0, [5000]),
+    (4, 4, 1, 0, [2081]),                                  # one row
+    (64, 1, 16, 0, [1000]),                                # a query a pair of blocks
+]
+
+
+@pytest.mark.parametrize("hq,hkv,nv,nf,lengths", SHARES)
+def test_shares_against_the_oracle(hq, hkv, nv, nf, lengths):
+    sh = W.AttnShape("shares", "bf16", len(lengths), hq, hkv, 128, nv, nf, lengths, 0.5, 1000000.0)
+    got, again = compare(sh, hq * 100 + nv)
+    assert (got == again).all()
+    n_q = nv + nf
+    ctx = np.asarray([[(i * 7 + b) % (n_q + 1) for i in range(n_q)] for b in range(len(lengths))], np.int32)
+    compare(sh, hq * 100 + nv, ctx)
+
+
+@pytest.mark.parametrize("hq,hkv,nv,nf,batch,length", [(32, 8, 5, 4, 24, 700), (28, 4, 64, 0, 64, 400), (28, 4, 41, 0, 8, 1000), (28, 4, 5, 4, 64, 1000)])
+def test_partials_stay_inside_the_workspace(hq, hkv, nv, nf, batch, length):
+    """The workspace holds few partials per row block for many sequences: bytes behind it stay as they are."""
+    import torch
+    M, S = _mods()
+    sh = W.AttnShape("room", "bf16", batch, hq, hkv, 128, nv, nf, [length] * batch, 0.5, 1000000.0)
+    inp = W.attention_inputs(sh, 904)
+    ses, ora, ids = setup_pair(inp)
+    with ses:
+        pos = pids_for(inp, M)
+        need = M.ms_attention_workspace_bytes(ses.cache, batch, sh.n_q)
+        guarded = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+        q, kn, vn = (S.to_device(x, M.MS_BF16) for x in (inp.q, inp.k_new, inp.v_new))
+        out = torch.empty_like(q)
+        M.ms_predict_verify_attention(ses.cache, 0, ids, nv, nf, q, kn, vn, S.ints_dev(pos).view(batch, sh.n_q), None, 0.0, out, guarded[:need])
+        torch.cuda.synchronize()
+        assert bool((guarded[need:] == 0x5A).all())
+        assert np.array_equal(S.to_host_f32(out), run_gpu_attention(ses, inp, ids, pos))
+
+
+def test_a_negative_scale_is_the_positive_one_of_negated_queries():
+    import torch
+    M, S = _mods()
+    sh = W.AttnShape("scale", "bf16", 2, 28, 4, 128, 5, 4, [700, 90], 0.5, 1000000.0)
+    inp = W.attention_inputs(sh, 905)
+    ses, ora, ids = setup_pair(inp)
+    with ses:
+        pos = S.ints_dev(pids_for(inp, M)).view(2, 9)
+        q, kn, vn = (S.to_device(x, M.MS_BF16) for x in (inp.q, inp.k_new, inp.v_new))
+        got = ses.attention(0, ids, 5, 4, q, kn, vn, pos, scale=-0.2)
+        assert M.ms_attention_last_kernel(ses.cache).startswith("pv_attn_mfma_split")
+        assert torch.equal(got, ses.attention(0, ids, 5, 4, -q, kn, vn, pos, scale=0.2))
+        assert not torch.equal(got, ses.attention(0, ids, 5, 4, q, kn, vn, pos, scale=0.2))
