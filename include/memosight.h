@@ -374,7 +374,8 @@ int ms_profile_read(ms_cache* cache, float* ms_out, int cap, int* n);
  * "+" if there were two; "" before the first.  ms_gemm_last_kernel: the kernel family of the
  * calling thread's last projection (its reduction not named): "gemm_tn_bf16" (256 x 256 tiles),
  * "gemm_rows_bf16" (one row tile; gate/up's 160- and 192-column tiles, gate_up_wide_bf16 in a
- * kernel trace, are of this family) or "skinny_mfma_bf16" (few rows).  For reports and tests: which
+ * kernel trace, are of this family), "gemm_cols_bf16" (one row tile, 256 columns wide) or
+ * "skinny_mfma_bf16" (few rows).  For reports and tests: which
  * kernel takes a call is no part of the interface. */
 const char* ms_attention_last_kernel(ms_cache* cache);
 const char* ms_gemm_last_kernel(void);

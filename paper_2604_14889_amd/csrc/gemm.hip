@@ -28,7 +28,7 @@
 // same output element in two accumulators and writes silu(gate) * up directly.
 // Steps of up to 256 rows are bound by bringing W to the compute units and run on a second kernel,
 // further down (gemm_rows_bf16), that computes row tiles of the step's own height (gate/up with a little more
-// than a round of its tiles: gate_up_wide_bf16, the same with wider ones).  A third kernel, for
+// than a round of its tiles: gate_up_wide_bf16, the same with wider ones; LM heads above 128 rows: gemm_cols_bf16, 256 columns wide).  A third kernel, for
 // at most 16 rows, streams 16 weight rows per wave through the matrix cores; it keeps the products that
 // give the second one too few workgroups (narrow outputs without a K split or a workspace) or that it
 // finishes in one launch instead of two.
@@ -799,12 +799,13 @@ struct MidUnit {
     int n0, part, s_lo, s_hi;
     bool whole;
 };
+template <int kBN = kMidBN>
 __device__ __forceinline__ MidUnit mid_unit(const MidUnits& t, int u, int steps) {
     MidUnit r;
     r.whole = u < t.main_tiles;
     const int tail = t.tiles - t.main_tiles, v = u - t.main_tiles;
     r.part = r.whole ? 0 : v / tail;
-    r.n0 = (r.whole ? u : t.main_tiles + v % tail) * kMidBN;
+    r.n0 = (r.whole ? u : t.main_tiles + v % tail) * kBN;
     r.s_lo = r.whole ? 0 : (int)((uint32_t)steps * r.part / t.parts);   // parts <= 64, steps < 2^25
     r.s_hi = r.whole ? steps : (int)((uint32_t)steps * (r.part + 1) / t.parts);
     return r;
@@ -963,6 +964,188 @@ __global__ __launch_bounds__(128 * kWM, 2) void gemm_rows_bf16(GemmArgs g, MidUn
         asm volatile("" ::: "memory");
         store_wave_tile<kMode, kMI, (kRowsA > 16)>(g, acc, !cur.whole, cur.part, 32 * kMI * wm, cur.n0 + 64 * wn, lane,
                                     smem + (buf ? buf - 1 : kS - 1) * kStage + w * kWaveOutBytes);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Wide outputs (LM heads) of a step of up to 256 rows: tiles of the step's own height (in blocks of 32 rows) x 256 columns.
+// What a compute unit takes in per multiplication falls with the tile's width: 224 rows x 128 columns bring 352 rows of
+// operands per step of K for 224 x 128 products, x 256 columns 480 for twice as many.
+// LM head of 152064 columns, K = 3584, cold weights, us with 256 x 256 tiles of gemm_tn_bf16 / here: 130 rows 290 / 225, 160 rows 297 / 236, 192
+// rows 303 / 254, 224 rows 314 / 275, 256 rows 333 / 291.  Bound by what a compute unit takes in: 224 rows without the
+// multiplications 251, without the operand reads 267; W alone at 17 rows 170 (6.4 TB/s).
+//   * Both operands go straight to LDS.  W comes in whole lines, K in steps of 64, a part of 128 columns at a time (half lines in
+//     steps of 32 were fetched twice when they passed the caches by: 224 rows 388 us, kept in them 317), A, which stays in L2,
+//     in steps of 32.  A's 16-byte chunks of row r lie at c ^ (r / 4 % 4), W's at c ^ (r / 2 % 8): operand reads without bank
+//     conflicts.  Half of the waves load A, the other W: loads arrive in order, and A's would wait behind W's (256 rows 304 / 291).
+//   * The two waves of a SIMD take turns, as in gemm_tn_bf16: a half step (32 K) of a wave is a data phase (its operand reads, the
+//     loads of a later half step) and a multiply phase, a barrier behind each, and the second half of
+//     the waves runs one phase behind the first.  A wave waits for its loads of half step h + 1 at the end of the phase
+//     before the first reader's (the first half's multiply phase, the second half's data phase of h); a stage is
+//     filled again in the data phase behind its last reader's.
+//   * One workgroup per compute unit walks its units (whole tiles, then K parts of the last round's) without draining its loads.
+// ---------------------------------------------------------------------------------------------
+constexpr int kColsBN = 256, kColsWaves = 8, kColsStagesA = 3;
+constexpr int kColsPartBytes = 128 * 128;                                        // W: 128 columns x 64 K
+constexpr int cols_stage_a(int blocks) { return 32 * blocks * 64; }              // A: 32 K
+constexpr int cols_parts(int blocks) {
+    return (160 * 1024 - kColsStagesA * cols_stage_a(blocks)) / kColsPartBytes < 8 ? (160 * 1024 - kColsStagesA * cols_stage_a(blocks)) / kColsPartBytes : 8;
+}
+constexpr int cols_lds_bytes(int blocks) { return cols_parts(blocks) * kColsPartBytes + kColsStagesA * cols_stage_a(blocks); }
+
+template <int kMode, int kBlocks>
+__global__ __launch_bounds__(64 * kColsWaves, 2) void gemm_cols_bf16(GemmArgs g, MidUnits t) {
+    constexpr int kStageA = cols_stage_a(kBlocks), kParts = cols_parts(kBlocks), kMI = (kBlocks + 1) / 2;
+    constexpr int kChunksA = 2 * kBlocks, kLoadsA = (kChunksA + 3) / 4;                 // of A per half step: 4 waves, the last chunk may be loaded twice
+    constexpr int kAheadA = kColsStagesA - 1, kAheadW = kParts - 2;                     // half steps between a load and its data phase
+    static_assert(kParts >= 5 && 4 * kWaveOutBytes <= kColsPartBytes, "room for the results in the last two of W's parts");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 2, wn = w & 3;   // waves w and w + 4 share a SIMD
+    const int steps = g.K / 64;
+    const bool full = kBlocks % 2 == 0 || wm == 0;   // the second half of the waves may have a block less
+    // The first half of the waves loads A, the second W: a wave's loads arrive in order, and A's, which come from L2, would wait behind
+    // W's.  Chunks of 1 KB: A 16 rows of 64 bytes, wn + 4 i of a stage's; W 8 rows of 128 bytes, 16 part + wn + 4 i.
+    uint32_t off_a[kLoadsA];
+#pragma unroll
+    for (int i = 0; i < kLoadsA; ++i) {
+        const int row = 16 * min(wn + 4 * i, kChunksA - 1) + (lane >> 2);
+        off_a[i] = (uint32_t)min(row, g.M - 1) * (uint32_t)g.K * 2u + 16u * ((lane & 3) ^ ((row >> 2) & 3));   // rows past M: the last one again, never stored
+    }
+    const uint32_t off_w = (uint32_t)(8 * wn + (lane >> 3)) * (uint32_t)g.K * 2u + 16u * ((lane & 7) ^ ((8 * wn + (lane >> 3)) >> 1 & 7));
+    const uint32_t lds_0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
+    const uint32_t lds_w = lds_0 + 1024u * wn, lds_a = lds_0 + kParts * kColsPartBytes;
+    const uint32_t row32 = 32u * (uint32_t)g.K * 2u;
+    // Where the next loads come from and go to: they run ahead into the next unit, and behind the last one read its last half
+    // step again (never used).  Kept as running pointers: every scalar instruction of a data phase is in the way.
+    struct Stream {
+        const char* from;
+        uint32_t to;
+        int left, u;   // loads of a unit, the unit
+    };
+    auto unit_begin = [&](Stream& st, bool of_w) {
+        const MidUnit v = mid_unit<kColsBN>(t, st.u, steps);
+        st.left = (of_w ? 1 : 2) * (v.s_hi - v.s_lo);
+        st.from = reinterpret_cast<const char*>(of_w ? g.w + (size_t)v.n0 * g.K : g.a) + (size_t)v.s_lo * 128;
+        return g.N - v.n0 < kColsBN;
+    };
+    Stream sa = {nullptr, lds_a, 0, (int)blockIdx.x}, sw = {nullptr, lds_w, 0, (int)blockIdx.x};
+    unit_begin(sa, false);
+    size_t second = unit_begin(sw, true) ? 0 : (size_t)4 * row32;   // from the first 128 of a tile's columns to the rest (a tile of 128: they again)
+    auto issue_a = [&]() {
+#pragma unroll
+        for (int i = 0; i < kLoadsA; ++i) load_lds_1k<false>(sa.to + 1024u * min(wn + 4 * i, kChunksA - 1), off_a[i], sa.from);
+        sa.to = sa.to == lds_a + (kColsStagesA - 1) * kStageA ? lds_a : sa.to + kStageA;
+        if (--sa.left > 0) {
+            sa.from += 64;
+        } else if (sa.u + (int)gridDim.x < t.units) {
+            sa.u += gridDim.x;
+            unit_begin(sa, false);
+        } else {
+            sa.left = 1;
+        }
+    };
+    auto issue_w = [&](int part) {
+        const char* from = part ? sw.from + second : sw.from;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // W passes through once
+            load_lds_1k<true>(sw.to + 4096u * i, off_w, from);
+            from += row32;
+        }
+        sw.to = sw.to == lds_w + (kParts - 1) * kColsPartBytes ? lds_w : sw.to + kColsPartBytes;
+        if (!part) return;
+        if (--sw.left > 0) {
+            sw.from += 128;
+        } else if (sw.u + (int)gridDim.x < t.units) {
+            sw.u += gridDim.x;
+            second = unit_begin(sw, true) ? 0 : (size_t)4 * row32;
+        } else {
+            sw.left = 1;
+        }
+    };
+    auto arrived = [&]() {   // this wave's loads of the next half step are here
+        if (wm == 0) wait_loads<(kAheadA - 1) * kLoadsA>();
+        else wait_loads<(kAheadW - 2) * 4>();   // (both parts of a step of 64)
+    };
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+    };
+    const int swz_a = (l32 >> 2) & 3, swz_w = (l32 >> 1) & 7;
+    const char* a_op = smem + kParts * kColsPartBytes + (32 * kMI * wm + l32) * 64;
+    const char* w_op = smem + ((64 * wn & 127) + l32) * 128;   // in the wave's part of a step
+#pragma unroll
+    for (int i = 0; i < kAheadA; ++i)
+        if (wm == 0) issue_a();
+#pragma unroll
+    for (int i = 0; i < kAheadW; ++i)
+        if (wm) issue_w(i & 1);
+    int buf_a = 0, at_w = wn >> 1;   // the wave's part in the ring
+    arrived();
+    for (int u = blockIdx.x; u < t.units; u += gridDim.x) {
+        const MidUnit cur = mid_unit<kColsBN>(t, u, steps);
+        g_f32x16_t acc[2][kMI];
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < kMI; ++mi)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[ni][mi][i] = 0.f;
+        barrier();             // the first half step is here, the results' stage is free
+        if (wm) barrier();     // a phase behind
+        for (int s = cur.s_lo; s < cur.s_hi; ++s) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                g_bf16x8_t wf[2][2], af[2][kMI];
+                const char* ab = a_op + buf_a * kStageA;
+                const char* wb = w_op + at_w * kColsPartBytes;
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+                        wf[kk][ni] = *reinterpret_cast<const g_bf16x8_t*>(wb + ni * 32 * 128 + 16 * ((4 * half + 2 * kk + hf) ^ swz_w));
+#pragma unroll
+                    for (int mi = 0; mi < kMI; ++mi)
+                        if (mi < kMI - 1 || full) af[kk][mi] = *reinterpret_cast<const g_bf16x8_t*>(ab + mi * 32 * 64 + 16 * ((2 * kk + hf) ^ swz_a));
+                }
+                if (wm) {
+                    issue_w((kAheadW + half) & 1);
+                    arrived();
+                } else {
+                    issue_a();
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                barrier();
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                        for (int mi = 0; mi < kMI; ++mi)
+                            if (mi < kMI - 1 || full) acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk][ni], af[kk][mi], acc[ni][mi], 0, 0, 0);
+                __builtin_amdgcn_s_setprio(0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (!wm) arrived();
+                barrier();
+                buf_a = buf_a + 1 == kColsStagesA ? 0 : buf_a + 1;
+                if (half) at_w = at_w + 2 >= kParts ? at_w + 2 - kParts : at_w + 2;
+            }
+        }
+        if (!wm) barrier();
+        // every wave has read the unit's last operands: the last step's parts are free until the next unit's first loads
+        const int of_last = at_w - (wn >> 1) + wm - 2;
+        char* out_lds = smem + (of_last < 0 ? of_last + kParts : of_last) * kColsPartBytes + wn * kWaveOutBytes;
+        if (u + (int)gridDim.x >= t.units) {   // the loads behind the last unit may go anywhere
+            wait_loads<0>();
+            barrier();
+        }
+        if (cur.n0 + 64 * wn < g.N)
+            store_wave_tile<kMode, kMI, true>(g, acc, !cur.whole, cur.part, 32 * kMI * wm, cur.n0 + 64 * wn, lane, out_lds);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
 }
 
@@ -1197,31 +1380,30 @@ static SkinnyPlan skinny_plan(int M, int N, int K, int min_parts = 1) {
 // Up to 256 rows: the launch shape of gemm_rows_bf16 (bm 0: the shape runs on another kernel).
 struct MidPlan {
     int bm;
+    bool cols;   // tiles of 256 columns (gemm_cols_bf16)
     MidUnits units;
     size_t workspace_bytes;
 };
 static MidPlan mid_plan(int M, int N, int K, int split_k) {
-    MidPlan p = {0, {0, 0, 1, 0}, 0};
+    MidPlan p = {0, false, {0, 0, 1, 0}, 0};
     if (M < 1 || M > kMidMaxRows || K % kMidBK || N % kMidBN || K / kMidBK < split_k) return p;
     if (K > 1 << 22) return p;   // a tile's rows are addressed with 32-bit byte offsets
     const int blocks = (M + 31) / 32;
     p.bm = M <= 8 ? 8 : M <= 16 ? 16 : blocks <= 4 ? 32 * blocks : blocks <= 6 ? 192 : 256;
-    const int tiles = N / kMidBN;
-    p.units = {tiles, tiles, 1, tiles};
+    int tiles = N / kMidBN, width = kMidBN;
     const int slots = gemm_slots() / 2, steps = K / kMidBK;
-    // Wide outputs that fill the chip with 256 x 256 tiles too stay there above 128 rows.  The line was drawn when the
-    // two were level up to K = 4096 and each ahead at one longer K.  Since results leave both as whole lines, us here /
-    // there, 144, 192, 224, 256 rows: K = 3584, 152064 columns 274 / 292, 287 / 301, 316 / 311, 323 / 327; K = 4096,
-    // 128256 columns 260 / 275, 274 / 275, 301 / 285, 306 / 302; K = 5120, 73728 columns 186 / 212, 197 / 225, 220 / 238,
-    // 231 / 237; K = 8192, 65536 columns 265 / 255, 275 / 260, 300 / 276, 309 / 293; 128256 columns 516 / 493, 542 / 501,
-    // 594 / 533, 610 / 570; SwiGLU, 160, 192, 224, 256 rows: K = 3584, 65536 columns 123 / 112, 127 / 117, 141 / 122,
-    // 140 / 130; K = 5120, 73728 columns 193 / 209, 202 / 222, 220 / 234, 228 / 233.  So plain products
-    // have come ahead here by 0 to 13 % up to 192 rows and K = 5120; with SwiGLU, at K = 8192, and from 193 rows on,
-    // which are staged as 256, it goes either way.  The line has not been moved for that.
+    // Wide outputs above 128 rows: tiles of 256 columns where there are enough of them for the chip.  us, 128-column tiles / these, 160, 192, 224,
+    // 256 rows: K = 3584, 152064 columns 278 / 236, 287 / 254, 316 / 275, 323 / 291 (256 x 256 tiles of gemm_tn_bf16 297, 303, 314, 333); K =
+    // 4096, 128256 columns 264 / 242, 274 / 248, 301 / 256, 306 / 266; K = 5120, 73728 columns 190 / 178, 197 / 190, 220 / 210, 231 /
+    // 225; SwiGLU, K = 3584, 65536 columns 123 / 96, 127 / 101, 141 / 108, 140 / 114.  Up to 128 rows both are bound by W's way
+    // from HBM (128 rows 222 / 222, 64 rows 179 / 182), and where its rows lie 8 KB apart 128-column tiles spread their starts (K = 4096, 64 rows 176 / 225).
     if (split_k == 1 && M > 128 && tiles >= 2 * slots) {
-        p.bm = 0;
-        return p;
+        p.cols = true;
+        p.bm = 32 * blocks;
+        width = kColsBN;
+        tiles = (N + kColsBN - 1) / kColsBN;
     }
+    p.units = {tiles, tiles, 1, tiles};
     if (split_k > 1) {
         // at most split_k parts: the number that leaves the shortest chain of steps, the fewest of equals
         int parts = 2;
@@ -1233,17 +1415,19 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     }
     // The tiles of the last round are divided over K: as many parts as fill the chip if it is at most 60 %
     // full; otherwise the number that leaves the shortest round, ceil(rem * parts / slots) / parts of a
-    // whole one (steps * 0.6 us), with a second launch and the partials' way to memory and back counted in.
+    // whole one (0.6 us a step, of 256-column tiles 2 us), with a second launch and the partials' way to memory and back counted in.
     const int rem = tiles % slots;
     if (tiles <= slots || rem == 0) return p;
     const int most = steps / 4 < 8 ? steps / 4 : 8;
+    const long tail_cols = (long)N - (long)(tiles - rem) * width;
+    const double step_us = p.cols ? 2.0 : 0.6;
     int best = 1;
     if (10 * rem <= 6 * slots) {
         best = slots / rem < most ? slots / rem : most;
     } else {
-        double best_us = 0.6 * steps;
+        double best_us = step_us * steps;
         for (int parts = 2; parts <= most; ++parts) {
-            const double us = 0.6 * steps * ((rem * parts + slots - 1) / slots) / parts + 5.0 + 2.0 * parts * M * rem * kMidBN * 4 / 4.0e6;
+            const double us = step_us * steps * ((rem * parts + slots - 1) / slots) / parts + 5.0 + 2.0 * parts * M * tail_cols * 4 / 4.0e6;
             if (us < best_us) {
                 best_us = us;
                 best = parts;
@@ -1252,7 +1436,7 @@ static MidPlan mid_plan(int M, int N, int K, int split_k) {
     }
     if (best <= 1) return p;
     p.units = {tiles, tiles - rem, best, tiles - rem + rem * best};
-    p.workspace_bytes = (size_t)best * M * rem * kMidBN * sizeof(float);
+    p.workspace_bytes = (size_t)best * M * tail_cols * sizeof(float);
     return p;
 }
 
@@ -1273,9 +1457,34 @@ static int mid_launch_built(const GemmArgs& g, const MidUnits& units, hipStream_
     hipLaunchKernelGGL((gemm_rows_bf16<kMode, kWM, kMI, kRowsA>), dim3(units.units < slots ? units.units : slots), dim3(128 * kWM), lds, stream, g, units);
     return MS_OK;
 }
+template <int kMode, int kBlocks>
+static int cols_launch_built(const GemmArgs& g, const MidUnits& units, hipStream_t stream) {
+    constexpr int lds = cols_lds_bytes(kBlocks);
+    static std::once_flag once[64];
+    static hipError_t result[64];
+    int dev = 0;
+    MS_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) MS_FAIL(MS_ERR_UNSUPPORTED, "device index %d outside [0, 64)", dev);
+    std::call_once(once[dev], [&] {
+        result[dev] = hipFuncSetAttribute((const void*)gemm_cols_bf16<kMode, kBlocks>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (result[dev] != hipSuccess) MS_FAIL(MS_ERR_HIP, "hipFuncSetAttribute(MaxDynamicSharedMemorySize) failed: %s", hipGetErrorString(result[dev]));
+    const int slots = gemm_slots() / 2;   // the LDS stages take a whole compute unit
+    g_last_kernel = "gemm_cols_bf16";
+    hipLaunchKernelGGL((gemm_cols_bf16<kMode, kBlocks>), dim3(units.units < slots ? units.units : slots), dim3(64 * kColsWaves), lds, stream, g, units);
+    return MS_OK;
+}
 template <int kMode>
-static int mid_launch(const GemmArgs& g, int bm, const MidUnits& units, hipStream_t stream) {
-    switch (bm) {
+static int mid_launch(const GemmArgs& g, const MidPlan& p, const MidUnits& units, hipStream_t stream) {
+    if (p.cols) {
+        switch (p.bm / 32) {
+            case 5: return cols_launch_built<kMode, 5>(g, units, stream);
+            case 6: return cols_launch_built<kMode, 6>(g, units, stream);
+            case 7: return cols_launch_built<kMode, 7>(g, units, stream);
+            default: return cols_launch_built<kMode, 8>(g, units, stream);
+        }
+    }
+    switch (p.bm) {
         case 8: return mid_launch_built<kMode, 1, 1, 8>(g, units, stream);
         case 16: return mid_launch_built<kMode, 1, 1, 16>(g, units, stream);
         case 32: return mid_launch_built<kMode, 1, 1>(g, units, stream);
@@ -1493,9 +1702,9 @@ static int gemm_launch(GemmArgs& g, int split_k, bool swiglu, void* workspace, s
             mid.units = {mid.units.tiles, mid.units.tiles, 1, mid.units.tiles};   // no room for the parts: whole tiles throughout
         const int tail = mid.units.tiles - mid.units.main_tiles, parts = mid.units.parts;
         g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
-        g.tail_col0 = mid.units.main_tiles * kMidBN;
+        g.tail_col0 = mid.units.main_tiles * (mid.cols ? kColsBN : kMidBN);
         g.partial = tail ? (float*)workspace : nullptr;
-        const int rc = swiglu ? mid_launch<kGemmSwiglu>(g, mid.bm, mid.units, stream) : mid_launch<kGemmPlain>(g, mid.bm, mid.units, stream);
+        const int rc = swiglu ? mid_launch<kGemmSwiglu>(g, mid, mid.units, stream) : mid_launch<kGemmPlain>(g, mid, mid.units, stream);
         if (rc != MS_OK) return rc;
         if (norm) {
             hipLaunchKernelGGL(reduce_add_rmsnorm, dim3((unsigned)g.M), dim3(kNormThreads), 0, stream, (const float*)g.partial, parts, g.M, g.N,
@@ -1715,7 +1924,7 @@ extern "C" int ms_lm_head_argmax_bf16(const void* a, const void* w, int M, int v
         groups = vocab / kGemmColGroup;
         g.k_per_split = g.tail_k = g.tail_first = g.tail_blocks = 0;
         g.tail_col0 = vocab;
-        rc = mid_launch<kGemmArgmax>(g, mid.bm, {tiles, tiles, 1, tiles}, stream);   // whole tiles throughout
+        rc = mid_launch<kGemmArgmax>(g, mid, {tiles, tiles, 1, tiles}, stream);   // whole tiles throughout
         if (rc != MS_OK) return rc;
     } else if (sk.parts == 1) {
         g.tail_first = g.tail_blocks = g.tail_k = g.tail_col0 = 0;
