@@ -9,7 +9,11 @@
 // from an ascending list of free pages, and apply_device_commits() replays its log here.
 #pragma once
 
-#include <set>
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <iterator>
 #include <string>
 #include <vector>
 
@@ -17,9 +21,96 @@
 
 namespace ms {
 
+// A set of page ids in ascending order, a bit each: no allocation per element (std::set's interface as far as it is used).
+class PageSet {
+  public:
+    class iterator {
+      public:
+        using iterator_category = std::forward_iterator_tag;
+        using value_type = int;
+        using difference_type = ptrdiff_t;
+        using pointer = const int*;
+        using reference = int;
+        iterator() = default;
+        int operator*() const { return at_; }
+        iterator& operator++() {
+            at_ = set_->next(at_ + 1);
+            return *this;
+        }
+        iterator operator++(int) {
+            iterator was = *this;
+            ++*this;
+            return was;
+        }
+        bool operator==(const iterator& o) const { return at_ == o.at_; }
+        bool operator!=(const iterator& o) const { return at_ != o.at_; }
+
+      private:
+        friend class PageSet;
+        iterator(const PageSet* set, int at) : set_(set), at_(at) {}
+        const PageSet* set_ = nullptr;
+        int at_ = 0;
+    };
+
+    // n ids, all of them in the set or none
+    void init(int n, bool full) {
+        n_ = n;
+        words_.assign(((size_t)n + 63) / 64, full ? ~0ull : 0ull);
+        if (full && n % 64) words_.back() = (1ull << (n % 64)) - 1;
+        size_ = full ? (size_t)n : 0;
+        low_ = 0;
+    }
+    size_t size() const { return size_; }
+    bool empty() const { return size_ == 0; }
+    bool count(int p) const { return p >= 0 && p < n_ && (words_[(size_t)p >> 6] >> (p & 63) & 1); }
+    iterator begin() const { return iterator(this, next(0)); }
+    iterator end() const { return iterator(this, n_); }
+    iterator rbegin() const {   // at the highest element
+        size_t w = words_.size();
+        while (w > 0 && !words_[w - 1]) --w;
+        return w ? iterator(this, (int)(64 * w) - 1 - __builtin_clzll(words_[w - 1])) : end();
+    }
+    bool insert(int p) {   // 0 <= p < n; false: it was there
+        uint64_t& w = words_[(size_t)p >> 6];
+        const uint64_t bit = 1ull << (p & 63);
+        if (w & bit) return false;
+        w |= bit;
+        ++size_;
+        low_ = std::min(low_, (size_t)p >> 6);
+        return true;
+    }
+    void erase(int p) {
+        if (!count(p)) return;
+        words_[(size_t)p >> 6] &= ~(1ull << (p & 63));
+        --size_;
+    }
+    void erase(iterator i) { erase(*i); }
+
+  private:
+    // the lowest element >= from, n if there is none
+    int next(int from) const {
+        if (from >= n_) return n_;
+        size_t w = (size_t)from >> 6;
+        uint64_t bits = words_[w] & (~0ull << (from & 63));
+        if (w < low_) {   // nothing below the first word that can hold an element
+            w = low_;
+            bits = w < words_.size() ? words_[w] : 0;
+        }
+        const bool from_low = w == low_ && from <= (int)(64 * low_);
+        while (!bits && ++w < words_.size()) bits = words_[w];
+        if (from_low) low_ = bits ? w : words_.size();
+        return bits ? (int)(64 * w) + __builtin_ctzll(bits) : n_;
+    }
+
+    std::vector<uint64_t> words_;
+    int n_ = 0;
+    size_t size_ = 0;
+    mutable size_t low_ = 0;   // no element lies in a word before this one
+};
+
 struct HostTables {
     int n_pages = 0, max_seqs = 0, max_pages_per_seq = 0;
-    std::set<int> free_pages;    // ordered: *begin() is the lowest free page
+    PageSet free_pages;          // ordered: *begin() is the lowest free page
     std::vector<std::vector<int>> pt;
     std::vector<int> len;
     std::vector<char> live;
@@ -30,6 +121,7 @@ struct HostTables {
     // queues page entries sends the batch before it returns (creates and frees queue lengths only).
     std::vector<int> pending_pt;
     unsigned version = 0;        // bumped by every change of lengths or page tables
+    PageSet listed;              // pages_importable()'s own; empty between calls
 
     static int pages_for(long n) { return (int)((n + MS_PAGE_SIZE - 1) / MS_PAGE_SIZE); }
 
@@ -37,8 +129,8 @@ struct HostTables {
         n_pages = n_pages_;
         max_seqs = max_seqs_;
         max_pages_per_seq = max_pages_per_seq_;
-        free_pages.clear();
-        for (int p = 0; p < n_pages; ++p) free_pages.insert(free_pages.end(), p);
+        free_pages.init(n_pages, true);
+        listed.init(n_pages, false);
         pt.assign(max_seqs, {});
         len.assign(max_seqs, 0);
         live.assign(max_seqs, 0);
@@ -101,11 +193,11 @@ struct HostTables {
     }
 
     // Every page in range, free and listed once?
-    bool pages_importable(const int* pages, int n) const {
-        std::set<int> seen;
-        for (int i = 0; i < n; ++i)
-            if (pages[i] < 0 || pages[i] >= n_pages || !free_pages.count(pages[i]) || !seen.insert(pages[i]).second) return false;
-        return true;
+    bool pages_importable(const int* pages, int n) {
+        int i = 0;
+        while (i < n && free_pages.count(pages[i]) && listed.insert(pages[i])) ++i;
+        for (int j = 0; j < i; ++j) listed.erase(pages[j]);
+        return i == n;
     }
 
     // Gives the (new, empty) sequence s the listed pages and the length; pages_importable() held.
