@@ -244,6 +244,7 @@ __device__ __forceinline__ void redo_rows(uint64_t redo, const float* ml, float*
 // 320 .. 1500 tokens, 8 / 8 heads of 64, fp32, 7 queries 60 -> 12 us.  What bounds it: the fp32 matrix
 // rate (256 FLOP per cycle and compute unit) on fp32 caches from two row blocks on, the vector work on the
 // scores on bf16 caches; with one block, the two launches and a chain of four memory round trips.
+constexpr float kRowsRescale = 24.0f;   // log2 units
 template <typename T, int D, int kRB>
 __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, BatchMeta bm) {
     constexpr int kE = 16 / (int)sizeof(T);   // elements of a 16-byte load of K (or Q)
@@ -367,17 +368,17 @@ __global__ __launch_bounds__(kGenThreads, 2) void pv_attn_rows(AttnArgs a, Batch
     // softmax weights of one tile's scores (in place), and what they do to the state
     auto softmax = [&](f32x4_t& s, int rb) {
         float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float mn = fmaxf(m[rb], mx);
-        const float mu = mn == -INFINITY ? 0.f : mn;   // nothing visible to the row so far
-        if (__any(mn > m[rb])) {
-            const float f = __builtin_amdgcn_exp2f(m[rb] - mu);
-            m[rb] = mn;
+        mx = max_across_32(max_across_16(mx));
+        // the state is scaled again only when the weights would pass 2^24 otherwise
+        const bool grow = mx > m[rb] + kRowsRescale;
+        if (__any(grow)) {
+            const float f = grow ? __builtin_amdgcn_exp2f(m[rb] - mx) : 1.f;   // 2^-inf = 0: nothing visible to the row before
+            m[rb] = grow ? mx : m[rb];
             l[rb] *= f;
 #pragma unroll
             for (int e = 0; e < kEV; ++e) o[rb][e] *= f;
         }
+        const float mu = m[rb] == -INFINITY ? 0.f : m[rb];   // nothing visible to the row so far
 #pragma unroll
         for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r] - mu);
         l[rb] += (s[0] + s[1]) + (s[2] + s[3]);

@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kSplitMostThreads, 1) void pv_attn_mfma_split(Split
         float mx = s[0];
 #pragma unroll
         for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * a.scale_log2;
+        mx = max_across_32(mx) * a.scale_log2;
         const bool grow = mx > m + kRescaleThreshold;
         if (__any(grow)) {
             if (i0 > 0) {

@@ -57,6 +57,16 @@ __device__ __forceinline__ void wave_lds_fence() {   // LDS operations of a wave
     __builtin_amdgcn_wave_barrier();
 }
 
+// The larger of x and its value 16 or 32 lanes away (lane ^ 16, lane ^ 32): a row or half swap in the vector unit, no trip through LDS.
+__device__ __forceinline__ float max_across_16(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float max_across_32(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // Row kernels with a norm (one workgroup per row, the row held in registers between the two passes):
 // threads per row and 8-element chunks per thread; rows of up to 8192 elements.
 constexpr int kNormThreads = 512;
