@@ -11,13 +11,12 @@
 //     and frequencies go straight to LDS (no registers, no LDS store instructions; K and V rows swizzled by the order in
 //     which the lanes fetch them), two tiles of a stream ahead, counted by hand, so that waiting for the query rows
 //     leaves the tiles in flight.  A stream's tiles are its wave's own: the loop has no barrier.
-//   * With two row blocks a workgroup has eight waves, two a stream, which load a half of each tile (K, V) and share it.
-//     One block as long as the calls' workgroups then fit the chip twice over: the cache is read once per workgroup,
-//     from L2 after the first.
+//   * With two row blocks a workgroup has eight waves, two a stream, which load a half of each tile (K, V) and share it;
+//     split_plan says when.  The cache is read once per workgroup, from L2 after the first.
 //   * The query rows are rotated by all threads together (eight pairs each), the step's own keys in their place the same way.
 //   * At the end each wave of a row block keeps one of the four 32-column blocks of O and hands the others over.
 // Time stamps inside the kernel, one sequence of 4096 tokens, 7 queries, 28 / 4 heads (us from the first wave's start, before
-// with two row blocks of two waves each in every workgroup, tiles through registers and 26 shares / now with 27): page ids
+// with two row blocks of two waves each in every workgroup, tiles through registers and 26 shares / these streams when they had 27 shares): page ids
 // 1.1 / 0.4, rows rotated 2.3 / 2.0, first tile done 4.6 / 3.4, everything stored 8.8 / 6.7; per call 15.7 / 13.4; what is left is launch,
 // page ids, the rows' way to LDS, sines, merge and the partials' way out.
 //   * The shares' partial results go to a second launch, where more workgroups read them: the share that
@@ -60,8 +59,8 @@ struct SplitArgs {
     int seq[MS_MAX_BATCH];
 };
 
-// x / n with inv = inverse_of(n): exact while x n < 2^20 (rows of a sequence: 64 queries x 64 heads, n = 64; row blocks of a batch: 64 x
-// 128, n = 128; workgroups: split_plan looks).
+// x / n with inv = inverse_of(n): exact while x n < 2^20 (rows of a sequence: 64 queries x 64 heads, n = 64; workgroups: split_plan
+// and the second launch's row blocks: split_plan looks).
 static uint32_t inverse_of(int n) { return (1u << 20) / n + 1; }
 __device__ __forceinline__ int div_by(uint32_t x, uint32_t inv) { return (int)((uint64_t)x * inv >> 20); }
 
@@ -507,8 +506,8 @@ static int split_chunks(int group, int n_q) { return (n_q + kRows / group - 1) /
 //   decode, more pairs: while everything is one round of workgroups and short.  9 q, 28 / 4 heads: 24 x 500 12.3 / 19.0, 24 x 1000 17.5 /
 //           21.9, 32 x 1000 21.4 / 24.2, 48 x 1500 37.1 / 41.1; 32 / 8 heads: 16 x 1000 20.5 / 23.8, 32 x 1000 32.0 / 33.2; 7 q
 //           (one row block): 24 x 1500 30.6 / 38.7, but 64 x 700 (two rounds of workgroups) 65 / 50
-//   wide    64 q: 1 x 2000 tokens 17.7 / 140, 8 x 4000 60 / 114 and 65 / 97, 8 x 6000 85 / 120 and 100 / 118, 2 x 30000 105 /
-//           184 and 113 / 153; two rounds of workgroups 16 x 4000 157 / 123 and 182 / 142
+//   wide    64 q: 1 x 2000 tokens 17.7 / 140, 8 x 4000 60 / 114 and 65 / 97, 8 x 6000 83 / 115 and 90 / 113, 2 x 30000 102 /
+//           184 and 110 / 154; two rounds of workgroups 16 x 4000 157 / 123 and 182 / 142
 // Shares are sized by the longest sequence, those of shorter ones end early, and nothing levels that: a decode batch
 // counts with the tiles it would have if all sequences were that long, a wide step whose lengths differ has shares of up to
 // 160 tiles, and the further half of either limit is for lengths that fill three quarters of the shares.  (With two row blocks of two
@@ -568,7 +567,7 @@ bool split_plan(const ms_cache* c, const int* lens, int B, int n_q, size_t ws_pa
     }
     if (wide && !level && p->share_tiles > kSplitMaxWideShare) return false;
     const long units = p->n_splits * heads * B, n_groups = (blocks + p->wg_blocks - 1) / p->wg_blocks, most_by = std::max(n_groups * n_groups / 8 + 1, std::max((long)p->n_splits, heads));
-    if (units * most_by >= 1l << 20) return false;   // div_by
+    if (units * most_by >= 1l << 20 || (p->n_splits > 1 && B * blocks * blocks >= 1l << 20)) return false;   // div_by
     p->late = split_lds_bytes(p->wg_blocks, n_q, false) > kSplitMostLds;
     p->lds_bytes = split_lds_bytes(p->wg_blocks, n_q, p->late);
     return true;
